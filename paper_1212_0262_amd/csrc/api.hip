@@ -1021,8 +1021,9 @@ int md_energy(md_ctx *c, const double *q, const double *p, double *out_dev3)
         return fail(c, MD_EINVAL, "md_energy: null or misaligned pointer");
     DeviceGuard g(c->dev);
     if (g.err != hipSuccess) return dev_fail(c, g.err, "md_energy: set device");
+    // both record the finiteness of the values (a single system's in its last kernel)
     MD_TRY(c->batch ? batch_energy(c, q, p, out_dev3) : launch_energy(c, q, p, out_dev3), "energy");
-    MD_TRY(launch_finite_flag(c, out_dev3, 3 * (c->batch ? c->batch->nb : 1)), "energy: finiteness");
+    if (c->batch) MD_TRY(launch_finite_flag(c, out_dev3, 3 * c->batch->nb), "energy: finiteness");
     c->checkable = true;
     return MD_OK;
 }

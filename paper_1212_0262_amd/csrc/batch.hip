@@ -18,6 +18,7 @@
 // (k_batch_sym) instead takes tile pairs within each realization, each pair of
 // particles evaluated once.
 #include "device.h"
+#include "energy_terms.h"
 #include "md_internal.h"
 #include "pair_terms.h"
 
@@ -170,7 +171,8 @@ __global__ __launch_bounds__(256) void k_batch_update(const int4 *__restrict__ r
     }
 }
 
-// Energy work item (b, i0, i1, j0) + j1: pairs i < j with i in [i0, i1), j in [j0, j1).
+// Energy work item (b, i0, i1, j0) + j1: pairs i < j with i in [i0, i1), j in [j0, j1)
+// (the wavefronts' pass of energy_terms.h, 4 i a lane).
 template <int MODEL>
 __global__ __launch_bounds__(256) void k_batch_energy_pairs(const PairItem *__restrict__ items,
                                                             const double *__restrict__ q,
@@ -178,27 +180,9 @@ __global__ __launch_bounds__(256) void k_batch_energy_pairs(const PairItem *__re
                                                             double *__restrict__ red)
 {
     __shared__ double lds[4];
+    __shared__ EnergyWin<MODEL> win[4];
     const PairItem it = items[blockIdx.x];
-    const int i = it.i0 + threadIdx.x;
-    const double eps = beps[it.b];
-    double acc = 0.0;
-    if (i < it.i1) {
-        const int j0 = max(it.j0, i + 1);
-        if (MODEL == MD_GRAV2D) {
-            const double xi = q[i], yi = q[ntot + i];
-            for (int j = j0; j < it.j1; ++j) {
-                const double dx = xi - q[j];
-                const double dy = yi - q[ntot + j];
-                acc += log(dx * dx + dy * dy + eps);
-            }
-        } else {
-            const double ti = q[i];
-            for (int j = j0; j < it.j1; ++j) {
-                const double h = sin(0.5 * (ti - q[j]));
-                acc += 1.0 / sqrt(2.0 * h * h + eps);
-            }
-        }
-    }
+    const double acc = energy_block<MODEL, 4>(q, (size_t)ntot, it.i0, it.i1, it.j0, it.j1, beps[it.b], win);
     const double s = block_sum(acc, lds);
     if (threadIdx.x == 0) red[blockIdx.x] = s;
 }

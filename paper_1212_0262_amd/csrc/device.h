@@ -117,6 +117,14 @@ __device__ __forceinline__ void sincos32(float x, float *sp, float *cp)
     *cp = ((q + 1) & 2) ? -b : b;
 }
 
+// Makes a wavefront's LDS writes visible to all its lanes' later reads.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sum over the 64 lanes of a wavefront (xor butterfly; every lane gets the total).
 __device__ __forceinline__ double wave_sum(double v)
 {

@@ -6,91 +6,113 @@
 // Every sum is a per-thread FP64 partial over a fixed index set, a fixed
 // block tree, and a one-block finalize in a fixed order: bitwise reproducible.
 #include "device.h"
+#include "energy_terms.h"
 #include "md_internal.h"
 
 namespace md {
 namespace {
 
-constexpr int kKinGrid = 1024;
+static_assert(kEnergyBlock == 4 * kWave, "energy_block: four wavefronts");
+constexpr int64_t kEnergyBlocks = 65536;  // most pair partials
+constexpr int64_t kEnergyManyBlocks = 8192;
+static_assert(kEnergyBlocks <= kRedSlots / 2, "the pair partials have half of the reduction scratch");
+constexpr int kKinGrid = 1024;    // most blocks of sum p^2
+constexpr int kFinThreads = 1024;  // threads of the one-block finalize
+constexpr int kFinBatch = 8;       // loads in flight per thread
 
-// Pair partial sums of the potential over i < j.  Block (bx, by) covers the 256
-// particles i of block bx against j in the by-th j range; red[by*gx + bx].
-// Ring term: 1/sqrt(2 sin^2((ti - tj)/2) + eps) (= 1/sqrt(1 - cos(ti - tj) + eps)).
-// 2D term: log(|r_i - r_j|^2 + eps).
-template <int MODEL>
-__global__ __launch_bounds__(kEnergyBlock) void k_energy_pairs(const double *__restrict__ q, int n, int jlen,
-                                                               double eps, double *__restrict__ red)
+// One block's part of sum p^2 over len values (block `block` of `blocks`, 256 threads,
+// grid-stride).
+__device__ __forceinline__ double sumsq_part(const double *__restrict__ p, int64_t len, int block, int blocks)
 {
-    __shared__ double lds[kEnergyBlock / kWave];
-    const int ib = blockIdx.x * kEnergyBlock;
-    const int i = ib + threadIdx.x;
-    const int j0 = max((int)blockIdx.y * jlen, ib + 1);
-    const int j1 = min(n, ((int)blockIdx.y + 1) * jlen);
     double acc = 0.0;
-    if (i < n) {
-        if (MODEL == MD_GRAV2D) {
-            const double xi = q[i], yi = q[n + i];
-            for (int j = j0; j < j1; ++j) {
-                const double dx = xi - q[j];
-                const double dy = yi - q[n + j];
-                if (j > i) acc += log(dx * dx + dy * dy + eps);
-            }
-        } else {
-            const double ti = q[i];
-            for (int j = j0; j < j1; ++j) {
-                const double h = sin(0.5 * (ti - q[j]));
-                if (j > i) acc += 1.0 / sqrt(2.0 * h * h + eps);
-            }
-        }
-    }
-    const double b = block_sum(acc, lds);
-    if (threadIdx.x == 0) red[blockIdx.y * gridDim.x + blockIdx.x] = b;
+    const int64_t stride = (int64_t)blocks * 256;
+    for (int64_t k = (int64_t)block * 256 + threadIdx.x; k < len; k += stride) acc += p[k] * p[k];
+    return acc;
 }
 
-// Block partials of sum p^2 over len values (grid-stride, fixed grid).
+// Block partials of the potential's pair sum and of sum p^2 (one launch).  Block t <
+// ng nc takes the i group t mod ng (64 IPL particles) against the j range t / ng of
+// jlen particles (the blocks below the diagonal have nothing to do and write 0); the
+// nk blocks after them the grid-stride sum of p^2 over len values.
+template <int MODEL, int IPL>
+__global__ __launch_bounds__(kEnergyBlock) void k_energy_pairs(const double *__restrict__ q,
+                                                               const double *__restrict__ p, int n, int64_t len,
+                                                               int ng, int nc, int jlen, int nk, double eps,
+                                                               double *__restrict__ redV, double *__restrict__ redK)
+{
+    __shared__ double lds[kEnergyBlock / kWave];
+    __shared__ EnergyWin<MODEL> win[kEnergyBlock / kWave];
+    const int t = (int)blockIdx.x;
+    if (t < ng * nc) {
+        const int i0 = (t % ng) * kWave * IPL, j0 = (t / ng) * jlen;
+        const int64_t jend = (int64_t)j0 + jlen;
+        const int j1 = jend < n ? (int)jend : n;
+        double acc = 0.0;
+        if (j1 > i0 + 1) acc = energy_block<MODEL, IPL>(q, (size_t)n, i0, n, j0, j1, eps, win);
+        const double b = block_sum(acc, lds);
+        if (threadIdx.x == 0) redV[t] = b;
+        return;
+    }
+    const double b = block_sum(sumsq_part(p, len, t - ng * nc, nk), lds);
+    if (threadIdx.x == 0) redK[t - ng * nc] = b;
+}
+
+// Block partials of sum p^2 over len values (HMF).
 __global__ __launch_bounds__(256) void k_sumsq(const double *__restrict__ p, int64_t len,
                                                double *__restrict__ red)
 {
     __shared__ double lds[4];
-    double acc = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < len; k += stride) acc += p[k] * p[k];
-    const double b = block_sum(acc, lds);
+    const double b = block_sum(sumsq_part(p, len, (int)blockIdx.x, (int)gridDim.x), lds);
     if (threadIdx.x == 0) red[blockIdx.x] = b;
 }
 
-// Sum of red[0 .. m) in a fixed order (valid in thread 0).
-__device__ double ordered_sum(const double *__restrict__ red, int m, int stride, double *lds)
+// This thread's part of the sum of red[b stride], b < m, in a fixed order: kFinBatch
+// loads at a time (one load, wait and add at a time leaves the one-block kernel bound
+// by the memory latency: 65,536 partials took 256 of them in a row).
+__device__ __forceinline__ double ordered_part(const double *__restrict__ red, int m, int stride)
 {
     double acc = 0.0;
-    for (int b = threadIdx.x; b < m; b += blockDim.x) acc += red[(size_t)b * stride];
-    return block_sum(acc, lds);
+    for (int b0 = 0; b0 < m; b0 += kFinThreads * kFinBatch) {
+        double v[kFinBatch];
+#pragma unroll
+        for (int k = 0; k < kFinBatch; ++k) {
+            const int b = b0 + (int)threadIdx.x + kFinThreads * k;
+            v[k] = b < m ? red[(size_t)b * stride] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < kFinBatch; ++k) acc += v[k];
+    }
+    return acc;
 }
 
-// out = {K, V, K + V}.  redV: nv pair partials (Ring, 2D) or hmf_grid pairs of
-// (sum cos, sum sin) (HMF).  redK: nk partials of sum p^2.
-__global__ __launch_bounds__(256) void k_energy_finalize(const double *__restrict__ redV, int nv,
-                                                         const double *__restrict__ redK, int nk, int model,
-                                                         int n, double *__restrict__ out)
+// out = {K, V, K + V} and the finiteness flag of the three (md_check).  redV: nv pair
+// partials (Ring, 2D) or hmf_grid pairs of (sum cos, sum sin) (HMF).  redK: nk
+// partials of sum p^2.
+__global__ __launch_bounds__(kFinThreads) void k_energy_finalize(const double *__restrict__ redV, int nv,
+                                                                 const double *__restrict__ redK, int nk, int model,
+                                                                 int n, double *__restrict__ out,
+                                                                 unsigned *__restrict__ flag)
 {
-    __shared__ double lds[3][4];
-    const double k2 = ordered_sum(redK, nk, 1, lds[0]);
+    __shared__ double lds[3][kFinThreads / kWave];
+    const double pk = ordered_part(redK, nk, 1);
+    const double pv = ordered_part(redV, nv, model == MD_HMF ? 2 : 1);
+    const double ps = model == MD_HMF ? ordered_part(redV + 1, nv, 2) : 0.0;
+    const double k2 = block_sum(pk, lds[0]);
+    const double sv = block_sum(pv, lds[1]);
+    const double ss = block_sum(ps, lds[2]);
+    if (threadIdx.x != 0) return;
     double v;
     if (model == MD_HMF) {
-        const double sc = ordered_sum(redV, nv, 2, lds[1]);
-        const double ss = ordered_sum(redV + 1, nv, 2, lds[2]);
-        const double mx = sc / (double)n, my = ss / (double)n;
+        const double mx = sv / (double)n, my = ss / (double)n;
         v = 0.5 * (double)n * (1.0 - mx * mx - my * my);
     } else {
-        const double sv = ordered_sum(redV, nv, 1, lds[1]);
         v = model == MD_GRAV2D ? sv / (double)n : -sv / (sqrt(2.0) * (double)n);
     }
-    if (threadIdx.x == 0) {
-        const double kin = 0.5 * k2;
-        out[0] = kin;
-        out[1] = v;
-        out[2] = kin + v;
-    }
+    const double kin = 0.5 * k2;
+    out[0] = kin;
+    out[1] = v;
+    out[2] = kin + v;
+    *flag = isfinite(kin) && isfinite(v) && isfinite(kin + v) ? 0u : 1u;
 }
 
 // flag = 1 if any of v[0 .. count) is not finite, else 0 (one block).
@@ -111,22 +133,43 @@ hipError_t launch_finite_flag(md_ctx *c, const double *vals, int count)
     return hipGetLastError();
 }
 
-// Layout of the reduction scratch: [0, kRedSlots/2) potential partials,
-// [kRedSlots/2, kRedSlots/2 + kKinGrid) kinetic partials.
-int energy_jsplit(int64_t n)
+// The i groups and j ranges of the pair sum: groups of 64 i (1 a lane) up to n = 16,384,
+// where blocks are few, of 256 (4 a lane: a window's LDS read serves four) above, and
+// j ranges of 256 (one 64-j window for each of a block's wavefronts) doubled while there
+// are more than kEnergyManyBlocks blocks, up to 4096, and within kEnergyBlocks partials.
+// Measured, md_energy in us, 1 / 4 a lane: 2D n = 4097 14.0 / 25.7, 8192 21.1 / 25.7,
+// 16,384 49.4 / 55.2; Ring FP64 18.9 / 32.9, 30.2 / 37.0, 84.7 / 89.2.  Blocks at most
+// 8192 / 16,384 / 32,768 / 65,536 (4 a lane): 2D n = 65,536 490 / 512 / 545 / 622,
+// 262,144 6856 / 6346 / 6139 / 6100.
+struct EnergyGrid {
+    int ipl, ng, nc, jlen;
+};
+
+EnergyGrid energy_grid(int64_t n)
 {
-    const int64_t ib = (n + kEnergyBlock - 1) / kEnergyBlock;
-    int64_t s = 8;
-    while (s > 1 && ib * s > kRedSlots / 2) s >>= 1;
-    return (int)s;
+    EnergyGrid g;
+    g.ipl = n > 16384 ? 4 : 1;
+    const int64_t per = (int64_t)kWave * g.ipl;
+    const int64_t ng = (n + per - 1) / per;
+    int64_t jlen = 4 * kWave;
+    auto blocks = [&]() { return ng * ((n + jlen - 1) / jlen); };
+    while ((blocks() > kEnergyManyBlocks && jlen < 4096) || blocks() > kEnergyBlocks) jlen *= 2;
+    g.ng = (int)ng;
+    g.nc = (int)((n + jlen - 1) / jlen);
+    g.jlen = (int)jlen;
+    return g;
 }
 
+// Layout of the reduction scratch: [0, kRedSlots/2) potential partials,
+// [kRedSlots/2, kRedSlots/2 + kKinGrid) kinetic partials.
 hipError_t launch_energy(md_ctx *c, const double *q, const double *p, double *out3)
 {
     const int n = (int)c->n;
-    const int d = dims(c->model);
+    const int64_t len = (int64_t)dims(c->model) * n;
     double *redV = c->red;
     double *redK = c->red + kRedSlots / 2;
+    const int64_t kb = (len + 1023) / 1024;  // 4 values a thread at least
+    const int nk = (int)(kb < kKinGrid ? kb : kKinGrid);
     int nv;
     if (c->model == MD_HMF) {
         // block partials of sum cos, sum sin of q (added here in FP64, in a fixed order; the pass's
@@ -136,22 +179,25 @@ hipError_t launch_energy(md_ctx *c, const double *q, const double *p, double *ou
         if (e != hipSuccess) return e;
         nv = hmf_grid(c->n);
         redV = const_cast<double *>(hmf_partials(c));
+        hipLaunchKernelGGL(k_sumsq, dim3((unsigned)nk), dim3(256), 0, c->stream, p, len, redK);
     } else {
-        const int gx = (n + kEnergyBlock - 1) / kEnergyBlock;
-        const int s = energy_jsplit(c->n);
-        const int jlen = (n + s - 1) / s;
-        const dim3 grid((unsigned)gx, (unsigned)s);
-        if (c->model == MD_GRAV2D)
-            hipLaunchKernelGGL(k_energy_pairs<MD_GRAV2D>, grid, dim3(kEnergyBlock), 0, c->stream, q, n, jlen,
-                               c->eps, redV);
-        else
-            hipLaunchKernelGGL(k_energy_pairs<MD_RING>, grid, dim3(kEnergyBlock), 0, c->stream, q, n, jlen,
-                               c->eps, redV);
-        nv = gx * s;
+        const EnergyGrid g = energy_grid(c->n);
+        const dim3 grid((unsigned)(g.ng * g.nc + nk));
+        nv = g.ng * g.nc;
+#define MD_ENERGY(M_, I_)                                                                                          \
+    hipLaunchKernelGGL((k_energy_pairs<M_, I_>), grid, dim3(kEnergyBlock), 0, c->stream, q, p, n, len, g.ng, g.nc, \
+                       g.jlen, nk, c->eps, redV, redK)
+        if (c->model == MD_GRAV2D) {
+            if (g.ipl == 4) MD_ENERGY(MD_GRAV2D, 4);
+            else MD_ENERGY(MD_GRAV2D, 1);
+        } else {
+            if (g.ipl == 4) MD_ENERGY(MD_RING, 4);
+            else MD_ENERGY(MD_RING, 1);
+        }
+#undef MD_ENERGY
     }
-    hipLaunchKernelGGL(k_sumsq, dim3(kKinGrid), dim3(256), 0, c->stream, p, (int64_t)d * n, redK);
-    hipLaunchKernelGGL(k_energy_finalize, dim3(1), dim3(256), 0, c->stream, redV, nv, redK, kKinGrid, c->model,
-                       n, out3);
+    hipLaunchKernelGGL(k_energy_finalize, dim3(1), dim3(kFinThreads), 0, c->stream, redV, nv, redK, nk, c->model, n,
+                       out3, finite_flag(c));
     return hipGetLastError();
 }
 

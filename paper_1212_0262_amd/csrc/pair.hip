@@ -558,14 +558,6 @@ __global__ __launch_bounds__(64) void k_update_vec(const SlotT *__restrict__ par
 
 // ------------------------------------------------------------- fused stage --
 
-// Makes a wavefront's LDS writes visible to all its lanes' later reads.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Small N: one launch per force evaluation.  A block owns an i tile and all of
 // its j ranges: S wavefronts, each split into L lane groups of 64 / L lanes; lane
 // (group g, slot il) of wavefront w holds the IPL particles i0 + il + k 64/L and
