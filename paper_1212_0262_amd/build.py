@@ -25,7 +25,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmd.so")
-SOURCES = ["api.hip", "pair.hip", "hmf.hip", "energy.hip", "batch.hip", "adjoint.hip"]
+SOURCES = ["api.hip", "pair.hip", "hmf.hip", "hmf_small.hip", "energy.hip", "batch.hip", "adjoint.hip"]
 ARCH = "gfx950"
 RESOURCES = os.path.join(BUILD_DIR, "kernel_resources.json")
 

@@ -313,6 +313,10 @@ int reverse_hmf(md_ctx *c, const double *q0, const double *P, size_t slot, doubl
 {
     double B0, B1, D0, D1;
     yoshida(&B0, &B1, &D0, &D1);
+    if (hmf_small(c)) {
+        MD_TRY(launch_hmf_small_vjp(c, B0 * dt, B1 * dt, D0 * dt, D1 * dt, nsteps, q0, P, slot, lq, lp), "vjp: sweep");
+        return MD_OK;
+    }
     auto pos = [&](int64_t m) -> const double * { return m == 0 ? q0 : P + (size_t)(m - 1) * slot; };
     MD_TRY(launch_hmf_hvp_sums(c, pos(3 * nsteps), lp), "vjp: sums");
     int kick = ADJ_KICK;
@@ -332,6 +336,16 @@ int reverse_hmf(md_ctx *c, const double *q0, const double *P, size_t slot, doubl
     return MD_OK;
 }
 
+// f = force(q), HMF.
+hipError_t hmf_force(md_ctx *c, double *q, double *f)
+{
+    if (hmf_small(c)) return launch_hmf_small_eval(c, q, nullptr, nullptr, f, nullptr, nullptr);
+    hipError_t e = launch_hmf_begin(c);
+    if (e == hipSuccess) e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, q, nullptr, nullptr, nullptr, false);
+    if (e == hipSuccess) e = launch_hmf_pass(c, 1, HMF_STORE_F, 0.0, 0.0, 0.0, q, nullptr, nullptr, f, false);
+    return e;
+}
+
 // snap (FP64 state only): the angles after every drift are also written to
 // consecutive slots of snap, snap_stride doubles apart.
 int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nsteps, double *snap = nullptr,
@@ -339,6 +353,11 @@ int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nste
 {
     double B0, B1, D0, D1;
     yoshida(&B0, &B1, &D0, &D1);
+    if (hmf_small(c)) {
+        MD_TRY(launch_hmf_small_steps(c, B0 * dt, B1 * dt, D0 * dt, D1 * dt, nsteps, q, p, f, snap, snap_stride),
+               "step: stages");
+        return MD_OK;
+    }
     const bool f32 = c->prec == MD_MIXED_F32STATE;
     const int stage = HMF_KICK_M | HMF_DRIFT | HMF_WRITE | HMF_REDUCE;
     int64_t slot = 0;
@@ -378,10 +397,7 @@ int step_vjp(md_ctx *c, const double *q0, const double *p0, double dt, int64_t n
     MD_TRY(hipMemcpyAsync(pw, p0, len * sizeof(double), hipMemcpyDeviceToDevice, c->stream), "vjp: copy p");
     int st;
     if (c->model == MD_HMF) {
-        MD_TRY(launch_hmf_begin(c), "vjp: magnetization sums");
-        MD_TRY(launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, qw, nullptr, nullptr, nullptr, false),
-               "vjp: reduce");
-        MD_TRY(launch_hmf_pass(c, 1, HMF_STORE_F, 0.0, 0.0, 0.0, qw, nullptr, nullptr, fw, false), "vjp: force");
+        MD_TRY(hmf_force(c, qw, fw), "vjp: force");
         st = step_hmf(c, qw, pw, fw, dt, nsteps, P, slot);
         if (st != MD_OK) return st;
         return reverse_hmf(c, q0, P, slot, dt, nsteps, lq, lp);
@@ -984,10 +1000,7 @@ int md_force(md_ctx *c, const double *q, double *f)
     if (g.err != hipSuccess) return dev_fail(c, g.err, "md_force: set device");
     double *qm = const_cast<double *>(q);
     if (c->model == MD_HMF) {
-        MD_TRY(launch_hmf_begin(c), "force: magnetization sums");
-        MD_TRY(launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, qm, nullptr, nullptr, nullptr, false),
-               "force: reduce");
-        MD_TRY(launch_hmf_pass(c, 1, HMF_STORE_F, 0.0, 0.0, 0.0, qm, nullptr, nullptr, f, false), "force: store");
+        MD_TRY(hmf_force(c, qm, f), "force");
         c->forced = true;
         return MD_OK;
     }
@@ -1038,6 +1051,10 @@ int md_magnetization(md_ctx *c, const double *q, double *out_dev2)
     DeviceGuard g(c->dev);
     if (g.err != hipSuccess) return dev_fail(c, g.err, "md_magnetization: set device");
     MD_TRY(launch_magnetization(c, q, out_dev2), "magnetization");
+    if (hmf_small(c)) {  // the one launch recorded it
+        c->checkable = true;
+        return MD_OK;
+    }
     // M is finite exactly when the pass's FP64 block partials are: the fixed-point
     // sums of small grids turn a NaN partial into some finite integer, so the
     // partials, not the output, decide
@@ -1073,6 +1090,10 @@ int md_hvp(md_ctx *c, const double *q, const double *w, double *out)
     DeviceGuard g(c->dev);
     if (g.err != hipSuccess) return dev_fail(c, g.err, "md_hvp: set device");
     double *wm = const_cast<double *>(w);
+    if (c->model == MD_HMF && hmf_small(c)) {
+        MD_TRY(launch_hmf_small_hvp(c, q, w, out), "hvp");
+        return MD_OK;
+    }
     if (c->model == MD_HMF) {
         MD_TRY(launch_hmf_hvp_sums(c, q, w), "hvp: sums");
         MD_TRY(launch_hmf_adj_update(c, q, ADJ_OUT, 0.0, 0.0, 0.0, nullptr, wm, out), "hvp: product");
@@ -1275,10 +1296,7 @@ int md_force_noalloc(int model, int prec, int64_t n, double eps, void *hip_strea
     double *qm = const_cast<double *>(q);
     hipError_t e = hipSuccess;
     if (model == MD_HMF) {
-        // launch_hmf_begin zeroes the fixed-point sums the previous call left
-        e = launch_hmf_begin(&c);
-        if (e == hipSuccess) e = launch_hmf_pass(&c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, qm, nullptr, nullptr, nullptr, false);
-        if (e == hipSuccess) e = launch_hmf_pass(&c, 1, HMF_STORE_F, 0.0, 0.0, 0.0, qm, nullptr, nullptr, f, false);
+        e = hmf_force(&c, qm, f);  // zeroes the fixed-point sums the previous call left
     } else {
         // every slot the combine reads is written by the pair kernel first
         e = launch_update(&c, UPD_PREP, 0.0, 0.0, 0.0, qm, nullptr, nullptr);

@@ -164,6 +164,8 @@ EnergyGrid energy_grid(int64_t n)
 // [kRedSlots/2, kRedSlots/2 + kKinGrid) kinetic partials.
 hipError_t launch_energy(md_ctx *c, const double *q, const double *p, double *out3)
 {
+    if (c->model == MD_HMF && hmf_small(c))
+        return launch_hmf_small_eval(c, q, p, nullptr, nullptr, out3, finite_flag(c));
     const int n = (int)c->n;
     const int64_t len = (int64_t)dims(c->model) * n;
     double *redV = c->red;
@@ -203,6 +205,7 @@ hipError_t launch_energy(md_ctx *c, const double *q, const double *p, double *ou
 
 hipError_t launch_magnetization(md_ctx *c, const double *q, double *out2)
 {
+    if (hmf_small(c)) return launch_hmf_small_eval(c, q, nullptr, out2, nullptr, nullptr, finite_flag(c));
     hipError_t e = launch_hmf_begin(c);
     if (e == hipSuccess)
         e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, const_cast<double *>(q), nullptr, nullptr, nullptr,

@@ -1,0 +1,395 @@
+// hmf_small.hip -- the HMF model (Sec. 3.1) for systems one workgroup can hold in
+// registers: a whole md_step call, or a whole reverse sweep, in one launch.
+//
+// The magnetization joins every particle at each stage.  Across blocks that takes a
+// kernel boundary a stage (hmf.hip), 6.5 to 7.3 us however few the particles: the
+// launch, a memory round trip for (t, p), the sums' way through memory.  Here one block
+// of up to 512 threads keeps t, p and the sincos of t of P particles a thread in
+// registers for all stages of the call, so a stage is one sincos per particle (the
+// kick reuses the sincos the previous stage summed), a register reduction and one
+// barrier.  Bound by FP64 issue on one CU (36 instructions of sincos a particle) above
+// about 1000 particles and by the chain sincos - reduction - barrier below.
+// Measured (MI355X), us per step before and after, FP64 / FP32 state: n = 100 15.6 / 17.9
+// -> 1.5 / 1.5; 2001 22.0 / 19.4 -> 3.7 / 3.9; 4096 20.5 / 18.3 -> 5.8 / 4.5; 8192 20.8 /
+// 18.6 -> 12.2 / 11.6.  Four steps' md_step_vjp at n = 2001: 235 -> 51 us.
+//
+// Sums: each thread's particles t, t + threads, ... in order, then small_means.  md_force, md_magnetization, md_energy and
+// the reverse sweep of these systems take the same sums, so they agree bit for bit.
+#include "device.h"
+#include "hmf_terms.h"
+#include "md_internal.h"
+
+namespace md {
+namespace {
+
+// Most threads of a block whose threads hold P particles: their t, p, sin and cos take 8 P
+// registers, of 256 a thread in blocks of 512 and 512 in blocks of 256 (16 in blocks of
+// 512 and 11 in blocks of 768 spill to memory).
+constexpr int small_threads(int P) { return P > 8 ? 256 : 512; }
+constexpr int kSmallWaves = 16;  // the wavefronts' sums: one row of lanes
+static_assert(small_threads(1) <= kSmallWaves * kWave, "a lane per wavefront");
+
+// The totals of K = 2 or 4 values over the block, divided by n, in every thread.  The
+// first lane exchanges put the K values in different rows of lanes, so that one chain
+// of moves and adds serves them all; the wavefronts' sums meet in lds (this stage's
+// buffer: two alternate, as a wavefront may be a stage ahead), one row of lanes per
+// value.  Every wavefront does this, so a block takes as few of them as fill its SIMDs.
+template <int K>
+__device__ __forceinline__ void small_means(double (&v)[K], double (&lds)[K][kSmallWaves], double n)
+{
+    static_assert(K == 2 || K == 4, "");
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    double t;
+    if constexpr (K == 2) {
+        t = swap32_sum(v[0], v[1]);  // halves: v0 | v1
+        t = swap16_sum(t, t);
+    } else {
+        t = swap16_sum(swap32_sum(v[0], v[2]), swap32_sum(v[1], v[3]));  // rows: v0 | v1 | v2 | v3
+    }
+    t = row_sum(t);
+    constexpr int kLanes = kWave / K;  // lanes of each value
+    if (lane % kLanes == 0) lds[lane / kLanes][wave] = t;
+    __syncthreads();
+    const int w = lane & (kSmallWaves - 1);
+    t = row_sum(w < nw ? lds[lane / kLanes][w] : 0.0);
+    t /= n;
+    v[0] = lane_value<0>(t);
+    v[1] = lane_value<kLanes>(t);
+    if constexpr (K == 4) {
+        v[2] = lane_value<2 * kLanes>(t);
+        v[3] = lane_value<3 * kLanes>(t);
+    }
+}
+
+// sum cos, sum sin of the thread's particles below n.
+template <typename T, int P>
+__device__ __forceinline__ void small_sums(const T (&s)[P], const T (&c)[P], int n, double (&v)[2])
+{
+    v[0] = v[1] = 0.0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        if ((int)(threadIdx.x + k * blockDim.x) < n) {
+            v[0] += (double)c[k];
+            v[1] += (double)s[k];
+        }
+    }
+}
+
+// eq. 6
+__device__ __forceinline__ double small_force(double s, double c, double mx, double my)
+{
+    return __builtin_fma(c, my, -(s * mx));
+}
+__device__ __forceinline__ float small_force(float s, float c, float mx, float my)
+{
+    return __builtin_fmaf(c, my, -(s * mx));
+}
+
+// Kicks b0, b1 and drifts d0, d1 (eq. 4) times dt.
+struct StepCoef {
+    double b0, b1, d0, d1;
+};
+
+// nsteps >= 1 Yoshida steps.  snap (nullable): the angles after each drift, stride apart.
+template <typename T, int P>
+__global__ __launch_bounds__(small_threads(P)) void k_hmf_small_step(double *__restrict__ q, double *__restrict__ p,
+                                                                  double *__restrict__ f, int n, StepCoef a,
+                                                                  int nsteps, double *__restrict__ snap, size_t stride)
+{
+    __shared__ double lds[2][2][kSmallWaves];
+    const T b0 = (T)a.b0, b1 = (T)a.b1, d0 = (T)a.d0, d1 = (T)a.d1;
+    T th[P], pp[P], s[P], c[P];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        const double qi = i < n ? q[i] : 0.0, pi = i < n ? p[i] : 0.0, fi = i < n ? f[i] : 0.0;
+        th[k] = (T)qi;
+        if constexpr (sizeof(T) == 4) th[k] = wrap_pi(th[k]);
+        pp[k] = (T)pi;
+        pp[k] += b0 * (T)fi;
+    }
+    const int last = 3 * nsteps - 1;
+    T dr = d0;
+    for (int m = 0, r = 0;; ++m, r = r == 2 ? 0 : r + 1) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            th[k] += dr * pp[k];
+            if constexpr (sizeof(T) == 4) th[k] = wrap_pi(th[k]);
+        }
+        if (snap) {
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const int i = threadIdx.x + k * blockDim.x;
+                if (i < n) snap[(size_t)m * stride + i] = (double)th[k];
+            }
+        }
+        sincos_n(th, s, c);
+        double v[2];
+        small_sums(s, c, n, v);
+        small_means(v, lds[m & 1], n);
+        const T mx = (T)v[0], my = (T)v[1];
+        const T k1 = r == 2 ? b0 : b1;
+        T(&fm)[P] = s;  // the force, in the place of the sines
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            fm[k] = small_force(s[k], c[k], mx, my);
+            pp[k] += k1 * fm[k];
+        }
+        if (m == last) {
+#pragma unroll
+            for (int k = 0; k < P; ++k) {
+                const int i = threadIdx.x + k * blockDim.x;
+                if (i < n) {
+                    q[i] = (double)th[k];
+                    p[i] = (double)pp[k];
+                    f[i] = (double)fm[k];
+                }
+            }
+            return;
+        }
+        if (r == 2) {  // the end kick of a step, then the start kick of the next
+#pragma unroll
+            for (int k = 0; k < P; ++k) pp[k] += b0 * fm[k];
+        }
+        dr = r == 0 ? d1 : d0;
+    }
+}
+
+// What one evaluation of the magnetization of q gives (each output nullable): M (the
+// context's and out2), the force f, the energies of (q, p), and whether M or the
+// energies are finite.
+template <int P>
+__global__ __launch_bounds__(small_threads(P)) void k_hmf_small_eval(const double *__restrict__ q,
+                                                                  const double *__restrict__ p, int n,
+                                                                  double *__restrict__ M, double *__restrict__ out2,
+                                                                  double *__restrict__ f, double *__restrict__ out3,
+                                                                  unsigned *__restrict__ flag)
+{
+    __shared__ double lds[2][2][kSmallWaves];
+    double th[P], pp[P], s[P], c[P], k2[2] = {0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        th[k] = i < n ? q[i] : 0.0;
+        pp[k] = out3 && i < n ? p[i] : 0.0;
+        k2[0] += pp[k] * pp[k];
+    }
+    sincos_n(th, s, c);
+    double v[2];
+    small_sums(s, c, n, v);
+    small_means(v, lds[0], n);
+    if (f) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            const int i = threadIdx.x + k * blockDim.x;
+            if (i < n) f[i] = small_force(s[k], c[k], v[0], v[1]);
+        }
+    }
+    if (out3) small_means(k2, lds[1], 1.0);
+    if (threadIdx.x != 0) return;
+    if (M) {
+        M[0] = v[0];
+        M[1] = v[1];
+    }
+    bool fine = isfinite(v[0]) && isfinite(v[1]);
+    if (out2) {
+        out2[0] = v[0];
+        out2[1] = v[1];
+    }
+    if (out3) {
+        const double kin = 0.5 * k2[0];
+        const double pot = 0.5 * (double)n * (1.0 - v[0] * v[0] - v[1] * v[1]);  // eq. 5
+        out3[0] = kin;
+        out3[1] = pot;
+        out3[2] = kin + pot;
+        fine = isfinite(kin) && isfinite(pot) && isfinite(kin + pot);
+    }
+    if (flag) *flag = fine ? 0u : 1u;
+}
+
+// The four means (Mx, My, Cw, Sw) of the product H(t) w (hmf.hip).
+template <int P>
+__device__ __forceinline__ void small_hvp_means(const double (&s)[P], const double (&c)[P], const double (&w)[P],
+                                                int n, double (&lds)[4][kSmallWaves], double (&v)[4])
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = 0.0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        if ((int)(threadIdx.x + k * blockDim.x) < n) {
+            v[0] += c[k];
+            v[1] += s[k];
+            v[2] += c[k] * w[k];
+            v[3] += s[k] * w[k];
+        }
+    }
+    small_means(v, lds, n);
+}
+
+__device__ __forceinline__ double small_hw(double s, double c, double w, const double (&v)[4])
+{
+    return w * (c * v[0] + s * v[1]) - (c * v[2] + s * v[3]);
+}
+
+// out = H(q) w.
+template <int P>
+__global__ __launch_bounds__(small_threads(P)) void k_hmf_small_hvp(const double *__restrict__ q,
+                                                                 const double *__restrict__ w, int n,
+                                                                 double *__restrict__ out)
+{
+    __shared__ double lds[4][kSmallWaves];
+    double th[P], wk[P], s[P], c[P], v[4];
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        th[k] = i < n ? q[i] : 0.0;
+        wk[k] = i < n ? w[i] : 0.0;
+    }
+    sincos_n(th, s, c);
+    small_hvp_means(s, c, wk, n, lds, v);
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        if (i < n) out[i] = small_hw(s[k], c[k], wk[k], v);
+    }
+}
+
+// The reverse sweep over nsteps recorded steps (reverse_hmf in api.hip): products at
+// P_3n, .., P_1, then at q0 (the position before the first drift), each followed by its
+// kick(s) and, but for the last, the drift before it.  pos: P_1 .. P_3n, stride apart.
+template <int P>
+__global__ __launch_bounds__(small_threads(P)) void k_hmf_small_vjp(const double *__restrict__ q0,
+                                                                 const double *__restrict__ pos, size_t stride, int n,
+                                                                 StepCoef a, int64_t nsteps, double *__restrict__ lq,
+                                                                 double *__restrict__ lp)
+{
+    __shared__ double lds[2][4][kSmallWaves];
+    double x[P], w[P], th[P], s[P], c[P], v[4];
+    auto load = [&](int64_t m) {  // positions m (0 = q0), for the next product
+        const double *__restrict__ src = m > 0 ? pos + (size_t)(m - 1) * stride : q0;
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            const int i = threadIdx.x + k * blockDim.x;
+            th[k] = i < n ? src[i] : 0.0;
+        }
+    };
+    load(3 * nsteps);
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        x[k] = i < n ? lq[i] : 0.0;
+        w[k] = i < n ? lp[i] : 0.0;
+    }
+    int r = 0;  // m mod 3
+    for (int64_t m = 3 * nsteps; m >= 0; --m, r = r == 0 ? 2 : r - 1) {
+        sincos_n(th, s, c);
+        if (m > 0) load(m - 1);  // in flight under the sums
+        small_hvp_means(s, c, w, n, lds[m & 1], v);
+        const double kick = r == 0 ? a.b0 : a.b1;
+        const bool two = r == 0 && m > 0 && m < 3 * nsteps;  // the kicks of two steps at one position
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+            const double hw = small_hw(s[k], c[k], w[k], v);
+            x[k] -= kick * hw;
+            if (two) x[k] -= kick * hw;
+        }
+        if (m > 0) {
+            const double dr = r == 2 ? a.d1 : a.d0;  // the drift that led to P_m
+#pragma unroll
+            for (int k = 0; k < P; ++k) w[k] += dr * x[k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int i = threadIdx.x + k * blockDim.x;
+        if (i < n) {
+            lq[i] = x[k];
+            lp[i] = w[k];
+        }
+    }
+}
+
+// Particles a thread: four wavefronts, one a SIMD, with 1, 2, 4, then 8 particles each,
+// up to eight wavefronts of 8, then four of 32: each wavefront repeats the reduction, so
+// fewer, fuller ones are faster while the registers last.  Measured, us per FP64 step:
+// n = 1000 2.55 (4 wavefronts of 4 a lane; 16 of 1 4.39, with the reduction of each sum by
+// itself); n = 4096 5.81 (8 of 8; 4 of 16 6.62); n = 8192 12.2 (4 of 32).
+int small_per_thread(int64_t n)
+{
+    if (n > 8 * small_threads(8)) return 32;
+    int p = 1;
+    while (p < 8 && n > (int64_t)4 * kWave * p) p *= 2;
+    return p;
+}
+static_assert(kHmfSmallN <= 32 * small_threads(32), "every particle has a thread");
+
+#define MD_SMALL(K_, ...)                                                                          \
+    do {                                                                                           \
+        const int per = small_per_thread(c->n);                                                    \
+        const int64_t waves = (c->n + (int64_t)kWave * per - 1) / ((int64_t)kWave * per);          \
+        const dim3 block((unsigned)(waves * kWave));                                               \
+        switch (per) {                                                                             \
+        case 1: hipLaunchKernelGGL((K_(1)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
+        case 2: hipLaunchKernelGGL((K_(2)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
+        case 4: hipLaunchKernelGGL((K_(4)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
+        case 8: hipLaunchKernelGGL((K_(8)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
+        default: hipLaunchKernelGGL((K_(32)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;   \
+        }                                                                                          \
+    } while (0)
+
+}  // namespace
+
+hipError_t launch_hmf_small_steps(md_ctx *c, double b0, double b1, double d0, double d1, int64_t nsteps, double *q,
+                                  double *p, double *f, double *snap, size_t snap_stride)
+{
+    const StepCoef a{b0, b1, d0, d1};
+    const int n = (int)c->n;
+    hipError_t err = hipSuccess;
+    for (int64_t done = 0; done < nsteps && err == hipSuccess;) {
+        const int k = (int)(nsteps - done < kHmfSmallSteps ? nsteps - done : kHmfSmallSteps);
+        double *sn = snap ? snap + (size_t)(3 * done) * snap_stride : nullptr;
+        const int ts = timed_begin(c, "k_hmf_small_step");
+#define K64(P_) k_hmf_small_step<double, P_>
+#define K32(P_) k_hmf_small_step<float, P_>
+        if (c->prec == MD_FP64) MD_SMALL(K64, q, p, f, n, a, k, sn, snap_stride);
+        else MD_SMALL(K32, q, p, f, n, a, k, sn, snap_stride);
+#undef K64
+#undef K32
+        err = hipGetLastError();
+        timed_end(c, ts);
+        done += k;
+    }
+    return err;
+}
+
+hipError_t launch_hmf_small_eval(md_ctx *c, const double *q, const double *p, double *out2, double *f, double *out3,
+                                 unsigned *flag)
+{
+    const int n = (int)c->n;
+#define K(P_) k_hmf_small_eval<P_>
+    MD_SMALL(K, q, p, n, c->scal, out2, f, out3, flag);
+#undef K
+    return hipGetLastError();
+}
+
+hipError_t launch_hmf_small_hvp(md_ctx *c, const double *q, const double *w, double *out)
+{
+    const int n = (int)c->n;
+#define K(P_) k_hmf_small_hvp<P_>
+    MD_SMALL(K, q, w, n, out);
+#undef K
+    return hipGetLastError();
+}
+
+hipError_t launch_hmf_small_vjp(md_ctx *c, double b0, double b1, double d0, double d1, int64_t nsteps,
+                                const double *q0, const double *pos, size_t stride, double *lq, double *lp)
+{
+    const StepCoef a{b0, b1, d0, d1};
+    const int n = (int)c->n;
+#define K(P_) k_hmf_small_vjp<P_>
+    MD_SMALL(K, q0, pos, stride, n, a, nsteps, lq, lp);
+#undef K
+    return hipGetLastError();
+}
+
+}  // namespace md

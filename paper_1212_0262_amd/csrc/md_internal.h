@@ -47,6 +47,8 @@ constexpr int kMSlots = 64;
 constexpr int kMLimbs = 4;  // sum cos: 2^-32 and 2^-64 limbs; sum sin: the same
 constexpr int kMWords = 3 * kMSlots * kMLimbs;
 constexpr int kHmfInPassM = 1024;  // grids of at most this many blocks use the fixed-point sums
+constexpr int64_t kHmfSmallN = 8192;      // HMF systems one workgroup takes whole (hmf_small.hip)
+constexpr int64_t kHmfSmallSteps = 4096;  // most steps of one of its launches (some 15 ms)
 constexpr int kEnergyBlock = 256;
 constexpr int64_t kFusedMaxN = 65536;   // contexts up to this n carry the fused stage's operand buffers
 constexpr int kFusedMaxWaves = 16;      // wavefronts per fused block
@@ -211,6 +213,17 @@ hipError_t launch_hmf_adj_update(md_ctx *c, const double *th, int flags, double 
 hipError_t launch_hmf_magnetization(md_ctx *c, double *out2);
 const double *hmf_partials(const md_ctx *c);  // block partials of the latest reducing pass
 hipError_t launch_hmf_convert(md_ctx *c, double *th, double *p, bool to_f32);
+// hmf_small.hip (n <= kHmfSmallN): whole calls in one launch.  b0 .. d1: the kicks and
+// drifts of eq. 4 times dt.  Outputs of eval (nullable): M, the force, the energies of
+// (q, p) and their (or M's) finiteness.
+inline bool hmf_small(const md_ctx *c) { return c->n <= kHmfSmallN; }
+hipError_t launch_hmf_small_steps(md_ctx *c, double b0, double b1, double d0, double d1, int64_t nsteps, double *q,
+                                  double *p, double *f, double *snap, size_t snap_stride);
+hipError_t launch_hmf_small_eval(md_ctx *c, const double *q, const double *p, double *out2, double *f, double *out3,
+                                 unsigned *flag);
+hipError_t launch_hmf_small_hvp(md_ctx *c, const double *q, const double *w, double *out);
+hipError_t launch_hmf_small_vjp(md_ctx *c, double b0, double b1, double d0, double d1, int64_t nsteps,
+                                const double *q0, const double *pos, size_t stride, double *lq, double *lp);
 // batch.hip
 hipError_t batch_pair(md_ctx *c, const double *q);
 hipError_t batch_update(md_ctx *c, int flags, double kick1, double kick2, double drift, double *q, double *p,
