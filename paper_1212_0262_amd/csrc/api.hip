@@ -362,10 +362,9 @@ int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nste
     const int stage = HMF_KICK_M | HMF_DRIFT | HMF_WRITE | HMF_REDUCE;
     int64_t slot = 0;
     auto next = [&]() { return snap ? snap + (size_t)(slot++) * snap_stride : nullptr; };
-    if (f32) MD_TRY(launch_hmf_convert(c, q, p, true), "step: convert in");
     int k = 0;  // pass index: pass k reads the magnetization sums of pass k - 1
     MD_TRY(launch_hmf_begin(c), "step: magnetization sums");
-    MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_F | HMF_DRIFT | HMF_WRITE | HMF_REDUCE, B0 * dt, 0.0, D0 * dt, q, p, f,
+    MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_F | HMF_DRIFT | HMF_WRITE | HMF_REDUCE | HMF_IN64, B0 * dt, 0.0, D0 * dt, q, p, f,
                            nullptr, f32, next()),
            "step: first pass");
     for (int64_t s = 0; s < nsteps; ++s) {
@@ -378,11 +377,10 @@ int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nste
                                    f32, next()),
                    "step: pass");
         else
-            MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_M | HMF_STORE_F | HMF_WRITE, B0 * dt, 0.0, 0.0, q, p, nullptr,
+            MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_M | HMF_STORE_F | HMF_WRITE | HMF_OUT64, B0 * dt, 0.0, 0.0, q, p, nullptr,
                                    f, f32),
                    "step: last pass");
     }
-    if (f32) MD_TRY(launch_hmf_convert(c, q, p, false), "step: convert out");
     return MD_OK;
 }
 

@@ -133,20 +133,24 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
+// Lane exchanges of 64-bit values (double, long long) between registers; the shuffles of
+// wave_sum go through LDS.
+
 // The value of the lane that DPP control CTRL selects within a row of 16 lanes.
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v)
+template <int CTRL, typename V>
+__device__ __forceinline__ V dpp_move(V v)
 {
+    static_assert(sizeof(V) == 8, "");
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
     const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
     const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
-    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+    return __builtin_bit_cast(V, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
 }
 
-// Sum over each row of 16 lanes, in every lane of the row: lane exchanges xor 1, xor 2,
-// then the mirrors of 8 and of 16 lanes (whose quads, then halves, hold one value by
-// then).  Register moves only: wave_sum's shuffles go through LDS.
-__device__ __forceinline__ double row_sum(double v)
+// Sum over each row of 16 lanes, in every lane of the row: exchanges xor 1, xor 2, then
+// the mirrors of 8 and of 16 lanes (whose quads, then halves, hold one value by then).
+template <typename V>
+__device__ __forceinline__ V row_sum(V v)
 {
     v += dpp_move<0xB1>(v);   // quad_perm 1,0,3,2
     v += dpp_move<0x4E>(v);   // quad_perm 2,3,0,1
@@ -158,31 +162,47 @@ __device__ __forceinline__ double row_sum(double v)
 // x, y -> sums over the pairs of rows (of halves) they exchange: the result holds x's
 // sum of rows 0 + 1 and 2 + 3 in rows 0 and 2 and y's in rows 1 and 3 (x's sum of
 // halves in the lower half, y's in the upper one).  gfx950's permlane swaps.
-__device__ __forceinline__ double swap16_sum(double x, double y)
+template <typename V>
+__device__ __forceinline__ V swap16_sum(V x, V y)
 {
     const uint64_t u = __builtin_bit_cast(uint64_t, x), v = __builtin_bit_cast(uint64_t, y);
     const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)v, false, false);
     const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(v >> 32), false, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
-           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+    return __builtin_bit_cast(V, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(V, ((uint64_t)hi[1] << 32) | lo[1]);
 }
-__device__ __forceinline__ double swap32_sum(double x, double y)
+template <typename V>
+__device__ __forceinline__ V swap32_sum(V x, V y)
 {
     const uint64_t u = __builtin_bit_cast(uint64_t, x), v = __builtin_bit_cast(uint64_t, y);
     const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)v, false, false);
     const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(v >> 32), false, false);
-    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
-           __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+    return __builtin_bit_cast(V, ((uint64_t)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(V, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+
+// Sums of x and y over the wavefront: x's in the lower 32 lanes, y's in the upper ones.
+template <typename V>
+__device__ __forceinline__ V wave_sum2(V x, V y)
+{
+    const V t = swap32_sum(x, y);
+    return row_sum(swap16_sum(t, t));
+}
+// Sums of four values over the wavefront, one per row of 16 lanes.
+template <typename V>
+__device__ __forceinline__ V wave_sum4(V x, V y, V z, V w)
+{
+    return row_sum(swap16_sum(swap32_sum(x, z), swap32_sum(y, w)));
 }
 
 // The value of lane L in every lane (a scalar).
-template <int L>
-__device__ __forceinline__ double lane_value(double v)
+template <int L, typename V>
+__device__ __forceinline__ V lane_value(V v)
 {
     const uint64_t u = __builtin_bit_cast(uint64_t, v);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, L);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), L);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    return __builtin_bit_cast(V, ((uint64_t)hi << 32) | lo);
 }
 
 // Sum over a block of up to 1024 threads (blockDim.x a multiple of 64).  `lds` must

@@ -26,8 +26,9 @@
 //
 // Memory access: each lane moves W consecutive elements (16-byte vector loads and
 // stores: W = 2 in FP64, 4 in FP32), U vectors per grid-stride iteration, over a
-// grid of one block per 2048 particles (at most 32768 blocks).  Pointers that are
-// not 16-byte aligned take W = 1.
+// grid of one block per 256 to 2048 particles (hmf_block; at most 32768 blocks).
+// Pointers that are not 16-byte aligned take W = 1.  The FP32 state is made from the
+// FP64 arrays by a call's first pass and written back by its last.
 //
 // Also here: the O(N) Hessian-vector product of the HMF potential (the mean-field
 // form of eqs. 6-7) and the elementwise stage of its reverse sweep.
@@ -38,7 +39,7 @@
 namespace md {
 namespace {
 
-constexpr int kUnroll = 2;  // vectors per thread per grid-stride iteration
+constexpr int kUnroll = 2;  // most vectors per thread per grid-stride iteration
 
 // W consecutive values, aligned to their size (one vector load/store when W > 1).
 template <typename T, int W>
@@ -101,8 +102,8 @@ __device__ __forceinline__ void stage_n(T (&t)[E], T (&p)[E], const double (&fin
     }
 }
 
-static_assert(kMSlots * kMLimbs == 256, "the 256 limb words: one per thread of a pass block");
-static_assert(kMSlots == kWave, "one slot per lane of the wavefront that converts the sums");
+static_assert(kMSlots * kMLimbs == 256, "the 256 limb words: one per thread of the block that zeroes them");
+static_assert(kMSlots == kWave && kMLimbs == 4, "one slot per lane of the wavefront that converts the sums");
 
 // x = (hi + lo 2^-32) 2^-32, hi = floor(x 2^32), 0 <= lo <= 2^32: exact for |x| < 2^20
 // down to 2^-64 (the bits below are rounded).
@@ -114,62 +115,45 @@ __device__ __forceinline__ void to_limbs(double x, long long &hi, long long &lo)
     lo = (long long)rint((y - h) * 0x1p32);
 }
 
-// M = (the total of the limb sums) / n, by a wavefront whose lane l holds the limbs
-// of slot l: a butterfly adds the slots in 64-bit integers (exact, so every lane
-// ends with the same total, in any order).
-__device__ __forceinline__ void limbs_sum(long long (&v)[kMLimbs], int n, double &mx, double &my)
+// M = (the total of the limb sums) / n in every lane, by one wavefront whose lane l loads
+// the limbs of slot l: the slots are added in 64-bit integers (exact, so in any order the
+// same total) by lane exchanges, one chain for the four limbs, no LDS and no barrier.
+__device__ __forceinline__ void limbs_mean(const long long *__restrict__ acc, int n, double &mx, double &my)
 {
-#pragma unroll
-    for (int m = kWave / 2; m >= 1; m >>= 1)
-#pragma unroll
-        for (int l = 0; l < kMLimbs; ++l) v[l] += __shfl_xor(v[l], m);
-    mx = ((double)v[0] * 0x1p-32 + (double)v[1] * 0x1p-64) / (double)n;
-    my = ((double)v[2] * 0x1p-32 + (double)v[3] * 0x1p-64) / (double)n;
-}
-
-// The same total by the 256 threads of a block: one word each, then four threads
-// add the 64 slots of one limb (a barrier before and after).
-__device__ __forceinline__ void limbs_sum_block(const long long *__restrict__ acc, int n, long long *lds, double &mx,
-                                                double &my)
-{
-    const int t = threadIdx.x;
-    lds[t] = acc[t];
-    __syncthreads();
-    if (t < kMLimbs) {
-        long long v = 0;
-        for (int k = 0; k < kMSlots; ++k) v += lds[k * kMLimbs + t];
-        lds[kMSlots * kMLimbs + t] = v;
-    }
-    __syncthreads();
-    const long long *L = lds + kMSlots * kMLimbs;
-    mx = ((double)L[0] * 0x1p-32 + (double)L[1] * 0x1p-64) / (double)n;
-    my = ((double)L[2] * 0x1p-32 + (double)L[3] * 0x1p-64) / (double)n;
+    const long long *__restrict__ a = acc + (threadIdx.x & (kWave - 1)) * kMLimbs;
+    const long long t = wave_sum4(a[0], a[1], a[2], a[3]);
+    mx = ((double)lane_value<0>(t) * 0x1p-32 + (double)lane_value<16>(t) * 0x1p-64) / (double)n;
+    my = ((double)lane_value<32>(t) * 0x1p-32 + (double)lane_value<48>(t) * 0x1p-64) / (double)n;
 }
 
 // One kick/drift/reduce pass over all particles (grid-stride over a grid fixed
 // per n, so every partial sum is reproducible).  T: state type; W: elements per
-// vector access.  HMF_REDUCE writes the block partials (sum cos, sum sin) to
-// red[2b], red[2b+1].  LIMBS (small grids): HMF_KICK_M / HMF_STORE_F take the
-// magnetization from the limb sums mrd (block 0 also stores it to M), HMF_REDUCE
-// adds the partials' limbs to mwr, and block 0 zeroes mzero for a later pass.
+// vector access; U: vectors per thread and iteration.  HMF_REDUCE writes the block
+// partials (sum cos, sum sin) to red[2b], red[2b+1].  LIMBS (in-pass sums):
+// HMF_KICK_M / HMF_STORE_F take the magnetization from the limb sums mrd, each
+// wavefront by itself (block 0 also stores it to M), HMF_REDUCE adds the partials'
+// limbs to mwr, and block 0 zeroes mzero for a later pass.
 // Without LIMBS the kernel reads M[0..1] and leaves the partials to the one-block
 // kernel (no code of the limbs).  Launched with 256 threads.
-template <typename T, int W, bool LIMBS>
+// FP32 state: HMF_IN64 takes the state from th64, p64 instead (angles wrapped),
+// HMF_OUT64 writes it there.
+template <typename T, int W, int U, bool LIMBS>
 __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restrict__ p,
                                                   const double *__restrict__ f_in, double *__restrict__ f_out,
                                                   const long long *__restrict__ mrd, long long *__restrict__ mwr,
                                                   long long *__restrict__ mzero, double *__restrict__ M,
-                                                  PassArgs a, int n, double *__restrict__ red, T *__restrict__ snap)
+                                                  PassArgs a, int n, double *__restrict__ red, T *__restrict__ snap,
+                                                  double *__restrict__ th64, double *__restrict__ p64)
 {
     __shared__ double lds[2][4];
-    __shared__ long long mlds[LIMBS ? kMSlots * kMLimbs + kMLimbs : 1];
     const int flags = a.flags;
     const T k1 = (T)a.kick1, k2 = (T)a.kick2, dr = (T)a.drift;
+    const bool in64 = sizeof(T) == 4 && (flags & HMF_IN64), out64 = sizeof(T) == 4 && (flags & HMF_OUT64);
     T mx = 0, my = 0;
     if (flags & (HMF_KICK_M | HMF_STORE_F)) {
         if constexpr (LIMBS) {
             double dmx, dmy;
-            limbs_sum_block(mrd, n, mlds, dmx, dmy);
+            limbs_mean(mrd, n, dmx, dmy);
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 M[0] = dmx;
                 M[1] = dmy;
@@ -189,20 +173,28 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
     const int stride = gridDim.x * blockDim.x;
     using VT = Vec<T, W>;
     using VD = Vec<double, W>;
-    constexpr int E = kUnroll * W;  // particles per thread and iteration: e = u W + w
-    for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < nvec; base += stride * kUnroll) {
-        VT t[kUnroll], q[kUnroll];
-        VD fi[kUnroll];
+    constexpr int E = U * W;  // particles per thread and iteration: e = u W + w
+    for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < nvec; base += stride * U) {
+        VT t[U], q[U];
+        VD fi[U];
         bool ok[E];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int v = base + u * stride;
             t[u] = VT{};
             q[u] = VT{};
             fi[u] = VD{};
             if (v < nvec) {
-                t[u] = reinterpret_cast<const VT *>(th)[v];
-                if (need_p) q[u] = reinterpret_cast<const VT *>(p)[v];
+                if (in64) {  // the call's first pass: element loads, any alignment
+#pragma unroll
+                    for (int w = 0; w < W; ++w) {
+                        if constexpr (sizeof(T) == 4) t[u].x[w] = wrap_pi((float)th64[v * W + w]);
+                        q[u].x[w] = (T)p64[v * W + w];
+                    }
+                } else {
+                    t[u] = reinterpret_cast<const VT *>(th)[v];
+                    if (need_p) q[u] = reinterpret_cast<const VT *>(p)[v];
+                }
                 if (flags & HMF_KICK_F) fi[u] = reinterpret_cast<const VD *>(f_in)[v];
             }
 #pragma unroll
@@ -219,7 +211,7 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
         }
         stage_n(te, pe, fe, fo, ok, mx, my, k1, k2, dr, flags, sc, ss);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int v = base + u * stride;
             if (v >= nvec) continue;
             VT to, po;
@@ -231,7 +223,13 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
                 ff.x[w] = fo[u * W + w];
             }
             if (flags & HMF_STORE_F) reinterpret_cast<VD *>(f_out)[v] = ff;
-            if (write) {
+            if (write && out64) {
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    th64[v * W + w] = (double)to.x[w];
+                    p64[v * W + w] = (double)po.x[w];
+                }
+            } else if (write) {
                 reinterpret_cast<VT *>(th)[v] = to;
                 if (need_p) reinterpret_cast<VT *>(p)[v] = po;
             }
@@ -244,35 +242,46 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
     // the n mod W particles past the last full vector: block 0
     if (W > 1 && blockIdx.x == 0 && (int)threadIdx.x < n - nvec * W) {
         const int i = nvec * W + threadIdx.x;
-        T t1[1] = {th[i]};
-        T p1[1] = {need_p ? p[i] : T(0)};
+        T t1[1], p1[1] = {T(0)};
+        if (in64) {
+            if constexpr (sizeof(T) == 4) t1[0] = wrap_pi((float)th64[i]);
+            p1[0] = (T)p64[i];
+        } else {
+            t1[0] = th[i];
+            if (need_p) p1[0] = p[i];
+        }
         const double f1[1] = {(flags & HMF_KICK_F) ? f_in[i] : 0.0};
         double fo1[1] = {0.0};
         const bool ok1[1] = {true};
         stage_n(t1, p1, f1, fo1, ok1, mx, my, k1, k2, dr, flags, sc, ss);
         if (flags & HMF_STORE_F) f_out[i] = fo1[0];
-        if (write) {
+        if (write && out64) {
+            th64[i] = (double)t1[0];
+            p64[i] = (double)p1[0];
+        } else if (write) {
             th[i] = t1[0];
             if (need_p) p[i] = p1[0];
         }
         if (snap && (flags & HMF_DRIFT)) snap[i] = t1[0];
     }
     if (flags & HMF_REDUCE) {
-        const double bc = block_sum(sc, lds[0]);
-        const double bs = block_sum(ss, lds[1]);
-        if (threadIdx.x == 0) {
-            red[2 * blockIdx.x] = bc;
-            red[2 * blockIdx.x + 1] = bs;
-        }
-        if (LIMBS && threadIdx.x == 0) {
-            unsigned long long *w = reinterpret_cast<unsigned long long *>(mwr + (blockIdx.x % kMSlots) * kMLimbs);
-            long long hi, lo;
-            to_limbs(bc, hi, lo);
-            atomicAdd(w, (unsigned long long)hi);  // two's complement: the signed sum, exactly
-            atomicAdd(w + 1, (unsigned long long)lo);
-            to_limbs(bs, hi, lo);
-            atomicAdd(w + 2, (unsigned long long)hi);
-            atomicAdd(w + 3, (unsigned long long)lo);
+        // lane 0 of a wavefront has its sum cos, lane 32 its sum sin; the first
+        // wavefront's then add the block's in order and their limbs
+        const int lane = threadIdx.x & (kWave - 1), k = lane / 32;
+        const double t = wave_sum2(sc, ss);
+        if (lane % 32 == 0) lds[k][threadIdx.x / kWave] = t;
+        __syncthreads();
+        if (threadIdx.x < kWave && lane % 32 == 0) {
+            const double b = ((lds[k][0] + lds[k][1]) + lds[k][2]) + lds[k][3];
+            red[2 * blockIdx.x + k] = b;
+            if constexpr (LIMBS) {
+                unsigned long long *w =
+                    reinterpret_cast<unsigned long long *>(mwr + (blockIdx.x % kMSlots) * kMLimbs + 2 * k);
+                long long hi, lo;
+                to_limbs(b, hi, lo);
+                atomicAdd(w, (unsigned long long)hi);  // two's complement: the signed sum, exactly
+                atomicAdd(w + 1, (unsigned long long)lo);
+            }
         }
     }
 }
@@ -286,10 +295,7 @@ __global__ __launch_bounds__(64) void k_hmf_limbs_to_m(const long long *__restri
                                                        double *__restrict__ out, double *__restrict__ M)
 {
     double mx, my;
-    long long v[kMLimbs];
-#pragma unroll
-    for (int l = 0; l < kMLimbs; ++l) v[l] = acc[threadIdx.x * kMLimbs + l];
-    limbs_sum(v, n, mx, my);
+    limbs_mean(acc, n, mx, my);
     if (threadIdx.x == 0) {
         if (out) {
             out[0] = mx;
@@ -330,22 +336,6 @@ __global__ __launch_bounds__(1024) void k_hmf_finalize(const double *__restrict_
     if (threadIdx.x == 0) {
         M[0] = c / (double)n;
         M[1] = s / (double)n;
-    }
-}
-
-// FP64 state <-> FP32 state (angles wrapped to [-pi, pi) on the way in).
-__global__ __launch_bounds__(256) void k_hmf_convert(double *__restrict__ th, double *__restrict__ p,
-                                                     float *__restrict__ th32, float *__restrict__ p32,
-                                                     int n, int to_f32)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (to_f32) {
-        th32[i] = wrap_pi((float)th[i]);
-        p32[i] = (float)p[i];
-    } else {
-        th[i] = (double)th32[i];
-        p[i] = (double)p32[i];
     }
 }
 
@@ -426,14 +416,26 @@ static int vec_width(bool f32, const void *a, const void *b, const void *c, cons
     return f32 ? 4 : 2;
 }
 
-// Blocks of an HMF pass: 2048 particles per block (two grid-stride iterations of
-// W = 2 at kUnroll = 2); measured at N = 1e7 against 1024 (7% slower: each block's
-// closing reduction is amortised over fewer particles) and 4096 (2% slower).  At
-// most kHmfGrid blocks (N = 6.7e7); above that the grid strides.  Capping at 16384
-// instead made N = 5e7 8% slower.
+// Particles of a pass block: 2048 (two grid-stride iterations of W = 2 at U = 2) at large
+// n; measured at N = 1e7 against 1024 (7% slower: each block's closing reduction is
+// amortised over fewer particles) and 4096 (2% slower).  Below, as few as keep the
+// grid within kHmfInPassM blocks, 256 at least: a thread's particles are a serial
+// chain, and 2048 a block leaves most CUs idle (49 blocks at N = 1e5).
+// Measured, us per step before (2048 a block, M by a barrier and LDS in every block) and
+// after, FP64 / FP32 state: N = 16,384 21.5 / 19.4 -> 12.0 / 11.4; 100,003 22.6 / 20.0 ->
+// 13.6 / 12.4; 400,000 24.5 / 21.0 -> 19.1 / 16.0; 1e6 33.0 / 26.3 -> 27.7 / 19.8.
+static int64_t hmf_block(int64_t n)
+{
+    int64_t per = 256;
+    while (per < 256 * kUnroll * 2 * 2 && n > per * kHmfInPassM) per *= 2;
+    return per;
+}
+
+// Blocks of an HMF pass.  At most kHmfGrid (N = 6.7e7); above that the grid strides.
+// Capping at 16384 instead made N = 5e7 8% slower.
 int hmf_grid(int64_t n)
 {
-    const int64_t per_block = 256 * kUnroll * 2 * 2;
+    const int64_t per_block = hmf_block(n);
     const int64_t b = (n + per_block - 1) / per_block;
     return (int)(b < kHmfGrid ? (b < 1 ? 1 : b) : kHmfGrid);
 }
@@ -442,7 +444,7 @@ const double *hmf_partials(const md_ctx *c) { return c->red; }
 
 // The passes of this context sum M in fixed point (small grids) rather than
 // through the one-block kernel over the FP64 partials.
-static bool hmf_in_pass(const md_ctx *c) { return hmf_grid(c->n) <= kHmfInPassM; }
+static bool hmf_in_pass(const md_ctx *c) { return hmf_grid(c->n) <= kHmfInPassM; }  // n <= 2,097,152
 
 hipError_t launch_hmf_begin(md_ctx *c)
 {
@@ -454,6 +456,7 @@ hipError_t launch_hmf_begin(md_ctx *c)
 hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kick2, double drift, double *th,
                            double *p, const double *f_in, double *f_out, bool f32state, double *snap)
 {
+    if (!f32state) flags &= ~(HMF_IN64 | HMF_OUT64);
     const int n = (int)c->n;
     const int g = hmf_grid(c->n);
     const PassArgs a{kick1, kick2, drift, flags};
@@ -466,23 +469,25 @@ hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kic
     long long *mwr = in_pass ? c->macc + (size_t)(k % 3) * B : nullptr;
     long long *mzero = in_pass ? c->macc + (size_t)((k + 1) % 3) * B : nullptr;
     const int ts = timed_begin(c, "k_hmf_pass");
-#define MD_HMF_PASS(T_, W_, TH_, P_, SNAP_)                                                                          \
-    do {                                                                                                         \
-        if (in_pass)                                                                                             \
-            hipLaunchKernelGGL((k_hmf_pass<T_, W_, true>), dim3(g), dim3(256), 0, c->stream, TH_, P_, f_in, f_out, \
-                               mrd, mwr, mzero, c->scal, a, n, c->red, SNAP_);                                   \
-        else                                                                                                     \
-            hipLaunchKernelGGL((k_hmf_pass<T_, W_, false>), dim3(g), dim3(256), 0, c->stream, TH_, P_, f_in,      \
-                               f_out, mrd, mwr, mzero, c->scal, a, n, c->red, SNAP_);                            \
+    // the vector and unroll that give a thread hmf_block / 256 particles (two iterations
+    // of kUnroll 16-byte vectors at most); W = 1 where a pointer is not 16-byte aligned
+    const int per = (int)(hmf_block(c->n) / 256);
+#define MD_HMF_PASS(T_, W_, U_, L_, TH_, P_, SNAP_)                                                                \
+    hipLaunchKernelGGL((k_hmf_pass<T_, W_, U_, L_>), dim3(g), dim3(256), 0, c->stream, TH_, P_, f_in, f_out, mrd, \
+                       mwr, mzero, c->scal, a, n, c->red, SNAP_, th, p)
+#define MD_HMF_FORM(T_, V_, TH_, P_, SNAP_)                                                    \
+    do {                                                                                       \
+        const bool vec = vec_width(sizeof(T_) == 4, TH_, P_, f_in, f_out) > 1;                 \
+        if (!in_pass && vec) MD_HMF_PASS(T_, V_, kUnroll, false, TH_, P_, SNAP_);              \
+        else if (!in_pass) MD_HMF_PASS(T_, 1, kUnroll, false, TH_, P_, SNAP_);                 \
+        else if (vec && per >= V_ * kUnroll) MD_HMF_PASS(T_, V_, kUnroll, true, TH_, P_, SNAP_); \
+        else if (vec && per >= V_) MD_HMF_PASS(T_, V_, 1, true, TH_, P_, SNAP_);               \
+        else if (per >= kUnroll) MD_HMF_PASS(T_, 1, kUnroll, true, TH_, P_, SNAP_);            \
+        else MD_HMF_PASS(T_, 1, 1, true, TH_, P_, SNAP_);                                      \
     } while (0)
-    if (f32state) {
-        if (vec_width(true, c->th32, c->p32, f_in, f_out) == 4) MD_HMF_PASS(float, 4, c->th32, c->p32, (float *)nullptr);
-        else MD_HMF_PASS(float, 1, c->th32, c->p32, (float *)nullptr);
-    } else {
-        // snap: element stores, any alignment
-        if (vec_width(false, th, p, f_in, f_out) == 2) MD_HMF_PASS(double, 2, th, p, snap);
-        else MD_HMF_PASS(double, 1, th, p, snap);
-    }
+    if (f32state) MD_HMF_FORM(float, 4, c->th32, c->p32, (float *)nullptr);
+    else MD_HMF_FORM(double, 2, th, p, snap);  // snap: element stores, any alignment
+#undef MD_HMF_FORM
 #undef MD_HMF_PASS
     hipError_t e = hipGetLastError();
     timed_end(c, ts);
@@ -498,14 +503,6 @@ hipError_t launch_hmf_magnetization(md_ctx *c, double *out2)
     if (!hmf_in_pass(c))  // the reducing pass's one-block kernel left M in c->scal
         return hipMemcpyAsync(out2, c->scal, 2 * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
     hipLaunchKernelGGL(k_hmf_limbs_to_m, dim3(1), dim3(kWave), 0, c->stream, c->macc, (int)c->n, out2, c->scal);
-    return hipGetLastError();
-}
-
-hipError_t launch_hmf_convert(md_ctx *c, double *th, double *p, bool to_f32)
-{
-    const int n = (int)c->n;
-    hipLaunchKernelGGL(k_hmf_convert, dim3((n + 255) / 256), dim3(256), 0, c->stream, th, p, c->th32, c->p32,
-                       n, to_f32 ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -40,13 +40,8 @@ __device__ __forceinline__ void small_means(double (&v)[K], double (&lds)[K][kSm
     static_assert(K == 2 || K == 4, "");
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
     double t;
-    if constexpr (K == 2) {
-        t = swap32_sum(v[0], v[1]);  // halves: v0 | v1
-        t = swap16_sum(t, t);
-    } else {
-        t = swap16_sum(swap32_sum(v[0], v[2]), swap32_sum(v[1], v[3]));  // rows: v0 | v1 | v2 | v3
-    }
-    t = row_sum(t);
+    if constexpr (K == 2) t = wave_sum2(v[0], v[1]);
+    else t = wave_sum4(v[0], v[1], v[2], v[3]);
     constexpr int kLanes = kWave / K;  // lanes of each value
     if (lane % kLanes == 0) lds[lane / kLanes][wave] = t;
     __syncthreads();

@@ -32,6 +32,8 @@ enum : int {
     HMF_REDUCE = 1 << 4,    // block partials of sum cos(t'), sum sin(t')
     HMF_STORE_F = 1 << 5,   // f_out = cos(t) My - sin(t) Mx  (no drift in the same pass)
     HMF_WRITE = 1 << 6,     // write t, p back
+    HMF_IN64 = 1 << 7,      // FP32 state: read t, p from the FP64 arrays (the first pass of a call)
+    HMF_OUT64 = 1 << 8,     // FP32 state: write t, p to the FP64 arrays (the last pass)
 };
 
 constexpr int kWave = 64;           // lanes per wavefront (CDNA)
@@ -212,7 +214,6 @@ hipError_t launch_hmf_adj_update(md_ctx *c, const double *th, int flags, double 
 // M from the limb sums of a call's pass 0, to out2[0..1] and the context scalars.
 hipError_t launch_hmf_magnetization(md_ctx *c, double *out2);
 const double *hmf_partials(const md_ctx *c);  // block partials of the latest reducing pass
-hipError_t launch_hmf_convert(md_ctx *c, double *th, double *p, bool to_f32);
 // hmf_small.hip (n <= kHmfSmallN): whole calls in one launch.  b0 .. d1: the kicks and
 // drifts of eq. 4 times dt.  Outputs of eval (nullable): M, the force, the energies of
 // (q, p) and their (or M's) finiteness.
