@@ -305,9 +305,8 @@ int reverse_pairs(md_ctx *c, const double *q0, const double *P, size_t slot, dou
     return MD_OK;
 }
 
-// HMF reverse sweep: as reverse_pairs, with the O(N) product -- per kick one pass
-// of sums over (P_m, lambda_p) and one elementwise pass that applies the kick and
-// the preceding drift.
+// HMF reverse sweep: as reverse_pairs, with the O(N) product -- per kick one pass that
+// applies it and the preceding drift and takes the sums of the next product.
 int reverse_hmf(md_ctx *c, const double *q0, const double *P, size_t slot, double dt, int64_t nsteps, double *lq,
                 double *lp)
 {
@@ -318,21 +317,20 @@ int reverse_hmf(md_ctx *c, const double *q0, const double *P, size_t slot, doubl
         return MD_OK;
     }
     auto pos = [&](int64_t m) -> const double * { return m == 0 ? q0 : P + (size_t)(m - 1) * slot; };
-    MD_TRY(launch_hmf_hvp_sums(c, pos(3 * nsteps), lp), "vjp: sums");
+    int k = 0;
+    auto pass = [&](int64_t m, int flags, double h, double h2, double a, int64_t next) {
+        return launch_hmf_adj_pass(c, k++, m >= 0 ? pos(m) : nullptr, flags, h, h2, a, lq, lp, nullptr,
+                                   next >= 0 ? pos(next) : nullptr);
+    };
+    MD_TRY(pass(-1, 0, 0.0, 0.0, 0.0, 3 * nsteps), "vjp: sums");
     int kick = ADJ_KICK;
     for (int64_t s = nsteps - 1; s >= 0; --s) {
-        MD_TRY(launch_hmf_adj_update(c, pos(3 * s + 3), kick | ADJ_DRIFT, B0 * dt, B0 * dt, D0 * dt, lq, lp, nullptr),
-               "vjp: update");
-        MD_TRY(launch_hmf_hvp_sums(c, pos(3 * s + 2), lp), "vjp: sums");
-        MD_TRY(launch_hmf_adj_update(c, pos(3 * s + 2), ADJ_KICK | ADJ_DRIFT, B1 * dt, 0.0, D1 * dt, lq, lp, nullptr),
-               "vjp: update");
-        MD_TRY(launch_hmf_hvp_sums(c, pos(3 * s + 1), lp), "vjp: sums");
-        MD_TRY(launch_hmf_adj_update(c, pos(3 * s + 1), ADJ_KICK | ADJ_DRIFT, B1 * dt, 0.0, D0 * dt, lq, lp, nullptr),
-               "vjp: update");
-        MD_TRY(launch_hmf_hvp_sums(c, pos(3 * s), lp), "vjp: sums");
+        MD_TRY(pass(3 * s + 3, kick | ADJ_DRIFT, B0 * dt, B0 * dt, D0 * dt, 3 * s + 2), "vjp: pass");
+        MD_TRY(pass(3 * s + 2, ADJ_KICK | ADJ_DRIFT, B1 * dt, 0.0, D1 * dt, 3 * s + 1), "vjp: pass");
+        MD_TRY(pass(3 * s + 1, ADJ_KICK | ADJ_DRIFT, B1 * dt, 0.0, D0 * dt, 3 * s), "vjp: pass");
         kick = s > 0 ? (ADJ_KICK | ADJ_KICK2) : ADJ_KICK;
     }
-    MD_TRY(launch_hmf_adj_update(c, q0, kick, B0 * dt, B0 * dt, 0.0, lq, lp, nullptr), "vjp: last kick");
+    MD_TRY(pass(0, kick, B0 * dt, B0 * dt, 0.0, -1), "vjp: last kick");
     return MD_OK;
 }
 
@@ -1093,8 +1091,8 @@ int md_hvp(md_ctx *c, const double *q, const double *w, double *out)
         return MD_OK;
     }
     if (c->model == MD_HMF) {
-        MD_TRY(launch_hmf_hvp_sums(c, q, w), "hvp: sums");
-        MD_TRY(launch_hmf_adj_update(c, q, ADJ_OUT, 0.0, 0.0, 0.0, nullptr, wm, out), "hvp: product");
+        MD_TRY(launch_hmf_adj_pass(c, 0, nullptr, 0, 0.0, 0.0, 0.0, nullptr, wm, nullptr, q), "hvp: sums");
+        MD_TRY(launch_hmf_adj_pass(c, 1, q, ADJ_OUT, 0.0, 0.0, 0.0, nullptr, wm, out, nullptr), "hvp: product");
         return MD_OK;
     }
     MD_TRY(launch_adj_update(c, ADJ_PREPQ | ADJ_PREPW, 0.0, 0.0, 0.0, nullptr, wm, nullptr, q), "hvp: operands");

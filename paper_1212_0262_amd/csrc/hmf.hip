@@ -31,7 +31,7 @@
 // FP64 arrays by a call's first pass and written back by its last.
 //
 // Also here: the O(N) Hessian-vector product of the HMF potential (the mean-field
-// form of eqs. 6-7) and the elementwise stage of its reverse sweep.
+// form of eqs. 6-7) and the passes of its reverse sweep.
 #include "device.h"
 #include "hmf_terms.h"
 #include "md_internal.h"
@@ -344,66 +344,183 @@ __global__ __launch_bounds__(1024) void k_hmf_finalize(const double *__restrict_
 //   (H w)_i = w_i (c_i Mx + s_i My) - (c_i Cw + s_i Sw),
 // Mx, My the magnetization (eq. 7), Cw = (1/N) sum c_j w_j, Sw = (1/N) sum s_j w_j.
 
-// Block partials of sum c, sum s, sum c w, sum s w (grid-stride, fixed grid).
-__global__ __launch_bounds__(256) void k_hmf_hvp_sums(const double *__restrict__ th, const double *__restrict__ w,
-                                                      int n, double *__restrict__ red)
+//
+// A pass applies one product and takes the sums of the next (k_hmf_adj_pass): per
+// product t of both positions, lq and lp read and lq, lp written once, 48 B a particle.
+// Measured, md_step_vjp of four steps, us, before (a pass for the sums, a one-block kernel
+// over up to 4096 partials, an elementwise kernel: 56 B a particle and three launches)
+// and after: N = 16,384 235 -> 106; 100,003 256 -> 129; 1e6 533 -> 266; 4e6 1282 -> 913.
+
+// sums[0..3] = (Mx, My, Cw, Sw) from the g block partials of each, by a block: thread t
+// adds quadruples t, t + T, ..., kAdjBatch loads at a time, then wave_sum4 and the
+// wavefronts in order.  In every thread (a barrier).  The passes of at most kAdjInPass
+// blocks take it at their start; on larger grids it costs every block more than the
+// one-block kernel.
+constexpr int kAdjBatch = 2;
+constexpr int kAdjInPass = 512;
+
+template <int T>
+__device__ __forceinline__ void adj_means(const double *__restrict__ part, int g, int n, double (&lds)[4][T / kWave],
+                                          double (&v)[4])
 {
-    __shared__ double lds[4][4];
     double a[4] = {0.0, 0.0, 0.0, 0.0};
-    const int stride = gridDim.x * blockDim.x;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        double s, c;
-        sincos64(th[i], &s, &c);
-        const double wi = w[i];
-        a[0] += c;
-        a[1] += s;
-        a[2] += c * wi;
-        a[3] += s * wi;
-    }
+    for (int b0 = 0; b0 < g; b0 += T * kAdjBatch) {
+        double x[kAdjBatch][4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double b = block_sum(a[k], lds[k]);
-        if (threadIdx.x == 0) red[4 * blockIdx.x + k] = b;
+        for (int k = 0; k < kAdjBatch; ++k) {
+            const int b = b0 + (int)threadIdx.x + T * k;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[k][j] = b < g ? part[4 * b + j] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < kAdjBatch; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[j] += x[k][j];
+    }
+    const int lane = threadIdx.x & (kWave - 1);
+    const double t = wave_sum4(a[0], a[1], a[2], a[3]);
+    if (lane % 16 == 0) lds[lane / 16][threadIdx.x / kWave] = t;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < T / kWave; ++w) s += lds[j][w];
+        v[j] = s / (double)n;
     }
 }
 
-// sums[0..3] = (Mx, My, Cw, Sw): the g partial quadruples added in a fixed order.
-__global__ __launch_bounds__(256) void k_hmf_hvp_finalize(const double *__restrict__ red, int g, int n,
-                                                          double *__restrict__ sums)
+__global__ __launch_bounds__(1024) void k_hmf_adj_finalize(const double *__restrict__ red, int g, int n,
+                                                           double *__restrict__ sums)
 {
-    __shared__ double lds[4][4];
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < g; b += blockDim.x)
-        for (int k = 0; k < 4; ++k) a[k] += red[4 * b + k];
+    __shared__ double lds[4][1024 / kWave];
+    double v[4];
+    adj_means<1024>(red, g, n, lds, v);
+    if (threadIdx.x == 0) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double t = block_sum(a[k], lds[k]);
-        if (threadIdx.x == 0) sums[k] = t / (double)n;
+        for (int j = 0; j < 4; ++j) sums[j] = v[j];
     }
 }
 
-// Elementwise, with the sums of H(th) lp: hw = (H lp)_i; out = hw; lq -= h hw
-// [; lq -= h2 hw]; lp += a lq.  Flags as the pair-model adjoint update.
-__global__ __launch_bounds__(256) void k_hmf_adj_update(const double *__restrict__ th, const double *__restrict__ sums,
-                                                        int flags, double h, double h2, double a, int n,
-                                                        double *__restrict__ lq, double *__restrict__ lp,
-                                                        double *__restrict__ out)
+// Elementwise, with the product hw = H(th) lp from its sums (part_in, g blocks of them,
+// or sums): out = hw (ADJ_OUT); lq -= h hw (ADJ_KICK), lq -= h2 hw (ADJ_KICK2);
+// lp += a lq (ADJ_DRIFT).  Then, if th_next is given, the block partials of the sums of
+// H(th_next) lp to part_out.  Grid-stride over a grid fixed per n.  W: elements per
+// vector access; U: vectors per thread and iteration; IN: sums from part_in.
+template <int W, int U, bool IN>
+__global__ __launch_bounds__(256) void k_hmf_adj_pass(const double *__restrict__ th, const double *__restrict__ part_in,
+                                                      int g, const double *__restrict__ sums, int flags, double h,
+                                                      double h2, double a, int n, double *__restrict__ lq,
+                                                      double *__restrict__ lp, double *__restrict__ out,
+                                                      const double *__restrict__ th_next,
+                                                      double *__restrict__ part_out)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (flags & (ADJ_OUT | ADJ_KICK)) {
-        double s, c;
-        sincos64(th[i], &s, &c);
-        const double w = lp[i];
-        const double hw = w * (c * sums[0] + s * sums[1]) - (c * sums[2] + s * sums[3]);
-        if (flags & ADJ_OUT) out[i] = hw;
-        if (flags & ADJ_KICK) {
-            double l = lq[i] - h * hw;
-            if (flags & ADJ_KICK2) l -= h2 * hw;
-            lq[i] = l;
+    __shared__ double lds[2][4][4];
+    using VD = Vec<double, W>;
+    constexpr int E = U * W;
+    const bool product = flags & (ADJ_OUT | ADJ_KICK);
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (product) {
+        if constexpr (IN) {
+            adj_means<256>(part_in, g, n, lds[0], v);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = sums[j];
         }
     }
-    if (flags & ADJ_DRIFT) lp[i] += a * lq[i];
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    // E particles: t of this product and of the next, lq, lp, hw; ok[e]: they exist
+    auto stage = [&](auto &t, auto &tn, auto &x, auto &w, auto &hw, const auto &ok) {
+        constexpr int N = sizeof(ok) / sizeof(ok[0]);
+        double s[N], c[N];
+        if (product) {
+            sincos_n(t, s, c);
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                hw[e] = w[e] * (c[e] * v[0] + s[e] * v[1]) - (c[e] * v[2] + s[e] * v[3]);
+                if (flags & ADJ_KICK) x[e] -= h * hw[e];
+                if (flags & ADJ_KICK2) x[e] -= h2 * hw[e];
+            }
+        }
+        if (flags & ADJ_DRIFT) {
+#pragma unroll
+            for (int e = 0; e < N; ++e) w[e] += a * x[e];
+        }
+        if (th_next) {
+            sincos_n(tn, s, c);
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                if (ok[e]) {
+                    sum[0] += c[e];
+                    sum[1] += s[e];
+                    sum[2] += c[e] * w[e];
+                    sum[3] += s[e] * w[e];
+                }
+            }
+        }
+    };
+    const bool need_x = flags & (ADJ_KICK | ADJ_DRIFT);
+    const int nvec = n / W, stride = gridDim.x * blockDim.x;
+    for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < nvec; base += stride * U) {
+        double t[E], tn[E], x[E], w[E], hw[E];
+        bool ok[E];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = base + u * stride;
+            const bool in = k < nvec;
+            VD vt{}, vn{}, vx{}, vw{};
+            if (in) {
+                if (product) vt = reinterpret_cast<const VD *>(th)[k];
+                if (th_next) vn = reinterpret_cast<const VD *>(th_next)[k];
+                if (need_x) vx = reinterpret_cast<const VD *>(lq)[k];
+                vw = reinterpret_cast<const VD *>(lp)[k];
+            }
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+                t[u * W + e] = vt.x[e];
+                tn[u * W + e] = vn.x[e];
+                x[u * W + e] = vx.x[e];
+                w[u * W + e] = vw.x[e];
+                hw[u * W + e] = 0.0;
+                ok[u * W + e] = in;
+            }
+        }
+        stage(t, tn, x, w, hw, ok);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = base + u * stride;
+            if (k >= nvec) continue;
+            VD vx, vw, vo;
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+                vx.x[e] = x[u * W + e];
+                vw.x[e] = w[u * W + e];
+                vo.x[e] = hw[u * W + e];
+            }
+            if (flags & ADJ_OUT) reinterpret_cast<VD *>(out)[k] = vo;
+            if (flags & ADJ_KICK) reinterpret_cast<VD *>(lq)[k] = vx;
+            if (flags & ADJ_DRIFT) reinterpret_cast<VD *>(lp)[k] = vw;
+        }
+    }
+    // the n mod W particles past the last full vector: block 0
+    if (W > 1 && blockIdx.x == 0 && (int)threadIdx.x < n - nvec * W) {
+        const int i = nvec * W + threadIdx.x;
+        double t[1] = {product ? th[i] : 0.0}, tn[1] = {th_next ? th_next[i] : 0.0}, x[1] = {need_x ? lq[i] : 0.0},
+               w[1] = {lp[i]}, hw[1] = {0.0};
+        const bool ok[1] = {true};
+        stage(t, tn, x, w, hw, ok);
+        if (flags & ADJ_OUT) out[i] = hw[0];
+        if (flags & ADJ_KICK) lq[i] = x[0];
+        if (flags & ADJ_DRIFT) lp[i] = w[0];
+    }
+    if (th_next) {
+        const int lane = threadIdx.x & (kWave - 1), j = lane / 16;
+        const double t = wave_sum4(sum[0], sum[1], sum[2], sum[3]);
+        if (lane % 16 == 0) lds[1][j][threadIdx.x / kWave] = t;
+        __syncthreads();
+        if (threadIdx.x < kWave && lane % 16 == 0)
+            part_out[4 * blockIdx.x + j] = ((lds[1][j][0] + lds[1][j][1]) + lds[1][j][2]) + lds[1][j][3];
+    }
 }
 
 }  // namespace
@@ -506,26 +623,44 @@ hipError_t launch_hmf_magnetization(md_ctx *c, double *out2)
     return hipGetLastError();
 }
 
-// Sums (Mx, My, Cw, Sw) of H(th) w into the context scalars c->scal[4..7].
-hipError_t launch_hmf_hvp_sums(md_ctx *c, const double *th, const double *w)
+// One pass of the product (k_hmf_adj_pass), the k-th of a call: its sums come from pass
+// k - 1, the next product's (th_next, nullable) go to pass k + 1.  The block partials
+// alternate between two halves of the scratch; with more than kAdjInPass blocks a
+// one-block kernel turns them into the context scalars c->scal[4..7].
+hipError_t launch_hmf_adj_pass(md_ctx *c, int k, const double *th, int flags, double h, double h2, double a,
+                               double *lq, double *lp, double *out, const double *th_next)
 {
     const int n = (int)c->n;
-    int g = (int)((c->n + 255) / 256);
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL(k_hmf_hvp_sums, dim3(g), dim3(256), 0, c->stream, th, w, n, c->red);
+    // 256 to 2048 particles a block (1, 2, 4 or 8 a thread), as few as keep the grid
+    // within kAdjInPass; above, 2048 and a grid-stride loop
+    int64_t per = 256;
+    while (per < 2048 && c->n > per * kAdjInPass) per *= 2;
+    int64_t blocks = (c->n + per - 1) / per;
+    if (blocks > kHmfGrid) blocks = kHmfGrid;
+    const bool in = blocks <= kAdjInPass;
+    static_assert(4 * kHmfGrid <= kRedSlots && 8 * kAdjInPass <= kRedSlots, "the partials fit the scratch");
+    double *part[2] = {c->red, in ? c->red + 4 * kAdjInPass : c->red};
+    const double *pin = part[(k + 1) & 1];
+    double *pout = part[k & 1];
+    const bool vec = vec_width(false, th, lq, lp, out) > 1 && ((uintptr_t)th_next & 15u) == 0 && per >= 512;
+    const dim3 grid((unsigned)blocks), block(256);
+#define MD_ADJ_PASS(W_, U_, IN_)                                                                                  \
+    hipLaunchKernelGGL((k_hmf_adj_pass<W_, U_, IN_>), grid, block, 0, c->stream, th, pin, (int)blocks, c->scal + 4, \
+                       flags, h, h2, a, n, lq, lp, out, th_next, pout)
+    if (!in) {
+        if (vec) MD_ADJ_PASS(2, 2, false);
+        else MD_ADJ_PASS(1, 2, false);
+    } else if (per == 256) MD_ADJ_PASS(1, 1, true);
+    else if (vec && per == 512) MD_ADJ_PASS(2, 1, true);
+    else if (vec) MD_ADJ_PASS(2, 2, true);
+    else MD_ADJ_PASS(1, 2, true);
+#undef MD_ADJ_PASS
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_hmf_hvp_finalize, dim3(1), dim3(256), 0, c->stream, c->red, g, n, c->scal + 4);
-    return hipGetLastError();
-}
-
-hipError_t launch_hmf_adj_update(md_ctx *c, const double *th, int flags, double h, double h2, double a, double *lq,
-                                 double *lp, double *out)
-{
-    const int n = (int)c->n;
-    hipLaunchKernelGGL(k_hmf_adj_update, dim3((n + 255) / 256), dim3(256), 0, c->stream, th, c->scal + 4, flags, h, h2,
-                       a, n, lq, lp, out);
-    return hipGetLastError();
+    if (e == hipSuccess && th_next && !in) {
+        hipLaunchKernelGGL(k_hmf_adj_finalize, dim3(1), dim3(1024), 0, c->stream, pout, (int)blocks, n, c->scal + 4);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 }  // namespace md

@@ -208,9 +208,8 @@ hipError_t launch_hmf_begin(md_ctx *c);
 hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kick2, double drift,
                            double *th, double *p, const double *f_in, double *f_out,
                            bool f32state, double *snap = nullptr);
-hipError_t launch_hmf_hvp_sums(md_ctx *c, const double *th, const double *w);
-hipError_t launch_hmf_adj_update(md_ctx *c, const double *th, int flags, double h, double h2, double a,
-                                 double *lq, double *lp, double *out);
+hipError_t launch_hmf_adj_pass(md_ctx *c, int k, const double *th, int flags, double h, double h2, double a,
+                               double *lq, double *lp, double *out, const double *th_next);
 // M from the limb sums of a call's pass 0, to out2[0..1] and the context scalars.
 hipError_t launch_hmf_magnetization(md_ctx *c, double *out2);
 const double *hmf_partials(const md_ctx *c);  // block partials of the latest reducing pass
