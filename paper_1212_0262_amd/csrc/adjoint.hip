@@ -104,11 +104,12 @@ __device__ __forceinline__ void hvp_ring(T ci, T si, T wi, T cj, T sj, T wj, T e
 template <typename T, typename A, int IPL>
 __global__ __launch_bounds__(256) void k_hvp_2d(const T *__restrict__ xs, const T *__restrict__ ys,
                                                 const T *__restrict__ wxs, const T *__restrict__ wys, int n,
-                                                int npad, int jlen, int jtile, T eps, double *__restrict__ part)
+                                                int npad, int jlen, int jtile, int waves, T eps,
+                                                double *__restrict__ part)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int ibase = (blockIdx.x * (blockDim.x / kWave) + wave) * (kWave * IPL) + lane;
+    const int ibase = (blockIdx.x * waves + wave) * (kWave * IPL) + lane;
     const int s = blockIdx.y;
     const int j0 = s * jlen;
     const int j1 = min(n, j0 + jlen);
@@ -170,12 +171,12 @@ __global__ __launch_bounds__(256) void k_hvp_2d(const T *__restrict__ xs, const 
 
 template <typename T, typename A, int IPL>
 __global__ __launch_bounds__(256) void k_hvp_ring(const T *__restrict__ cs, const T *__restrict__ ws, int n,
-                                                  int npad, int jlen, int jtile, T one_eps,
+                                                  int npad, int jlen, int jtile, int waves, T one_eps,
                                                   double *__restrict__ part)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int ibase = (blockIdx.x * (blockDim.x / kWave) + wave) * (kWave * IPL) + lane;
+    const int ibase = (blockIdx.x * waves + wave) * (kWave * IPL) + lane;
     const int s = blockIdx.y;
     const int j0 = s * jlen;
     const int j1 = min(n, j0 + jlen);
@@ -385,7 +386,7 @@ __global__ __launch_bounds__(256) void k_adj_update(const double *__restrict__ p
                                                     double *__restrict__ out, const double *__restrict__ pos,
                                                     void *__restrict__ ops, void *__restrict__ wops)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) {
         if constexpr (PREP == PREP_COPY64) {
             if (i < npad) {
@@ -451,7 +452,7 @@ int prep_kind(const md_ctx *c)
 template <typename T, typename A>
 hipError_t hvp_launch(md_ctx *c, const void *qsrc, const void *wsrc, dim3 grid, dim3 block, int jlen)
 {
-    const int n = (int)c->n, npad = (int)c->npad, jt = c->tiles.jtile;
+    const int n = (int)c->n, npad = (int)c->npad, jt = c->tiles.jtile, waves = c->tiles.waves;
     const bool fp64 = c->prec == MD_FP64;
     const int ts = timed_begin(c, c->model == MD_GRAV2D ? "k_hvp_2d" : "k_hvp_ring");
     if (c->model == MD_GRAV2D) {
@@ -461,18 +462,18 @@ hipError_t hvp_launch(md_ctx *c, const void *qsrc, const void *wsrc, dim3 grid, 
         const T *wy = wx + (fp64 ? n : npad);
         const T eps = (T)c->eps;
         switch (c->tiles.ipl) {
-        case 1: hipLaunchKernelGGL((k_hvp_2d<T, A, 1>), grid, block, 0, c->stream, x, y, wx, wy, n, npad, jlen, jt, eps, c->part); break;
-        case 2: hipLaunchKernelGGL((k_hvp_2d<T, A, 2>), grid, block, 0, c->stream, x, y, wx, wy, n, npad, jlen, jt, eps, c->part); break;
-        default: hipLaunchKernelGGL((k_hvp_2d<T, A, 4>), grid, block, 0, c->stream, x, y, wx, wy, n, npad, jlen, jt, eps, c->part); break;
+        case 1: hipLaunchKernelGGL((k_hvp_2d<T, A, 1>), grid, block, 0, c->stream, x, y, wx, wy, n, npad, jlen, jt, waves, eps, c->part); break;
+        case 2: hipLaunchKernelGGL((k_hvp_2d<T, A, 2>), grid, block, 0, c->stream, x, y, wx, wy, n, npad, jlen, jt, waves, eps, c->part); break;
+        default: hipLaunchKernelGGL((k_hvp_2d<T, A, 4>), grid, block, 0, c->stream, x, y, wx, wy, n, npad, jlen, jt, waves, eps, c->part); break;
         }
     } else {
         const T *cs = static_cast<const T *>(qsrc);
         const T *w = static_cast<const T *>(wsrc);
         const T one_eps = sizeof(T) == 8 ? (T)(1.0 + c->eps) : (T)(2.0 * c->eps);  // FP32 half-angle form: 2 eps
         switch (c->tiles.ipl) {
-        case 1: hipLaunchKernelGGL((k_hvp_ring<T, A, 1>), grid, block, 0, c->stream, cs, w, n, npad, jlen, jt, one_eps, c->part); break;
-        case 2: hipLaunchKernelGGL((k_hvp_ring<T, A, 2>), grid, block, 0, c->stream, cs, w, n, npad, jlen, jt, one_eps, c->part); break;
-        default: hipLaunchKernelGGL((k_hvp_ring<T, A, 4>), grid, block, 0, c->stream, cs, w, n, npad, jlen, jt, one_eps, c->part); break;
+        case 1: hipLaunchKernelGGL((k_hvp_ring<T, A, 1>), grid, block, 0, c->stream, cs, w, n, npad, jlen, jt, waves, one_eps, c->part); break;
+        case 2: hipLaunchKernelGGL((k_hvp_ring<T, A, 2>), grid, block, 0, c->stream, cs, w, n, npad, jlen, jt, waves, one_eps, c->part); break;
+        default: hipLaunchKernelGGL((k_hvp_ring<T, A, 4>), grid, block, 0, c->stream, cs, w, n, npad, jlen, jt, waves, one_eps, c->part); break;
         }
     }
     const hipError_t err = hipGetLastError();

@@ -339,8 +339,8 @@ hipError_t hmf_force(md_ctx *c, double *q, double *f)
 {
     if (hmf_small(c)) return launch_hmf_small_eval(c, q, nullptr, nullptr, f, nullptr, nullptr);
     hipError_t e = launch_hmf_begin(c);
-    if (e == hipSuccess) e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, q, nullptr, nullptr, nullptr, false);
-    if (e == hipSuccess) e = launch_hmf_pass(c, 1, HMF_STORE_F, 0.0, 0.0, 0.0, q, nullptr, nullptr, f, false);
+    if (e == hipSuccess) e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, q, nullptr, nullptr, false);
+    if (e == hipSuccess) e = launch_hmf_pass(c, 1, HMF_STORE_F, 0.0, 0.0, 0.0, q, nullptr, f, false);
     return e;
 }
 
@@ -363,20 +363,20 @@ int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nste
     int k = 0;  // pass index: pass k reads the magnetization sums of pass k - 1
     MD_TRY(launch_hmf_begin(c), "step: magnetization sums");
     MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_F | HMF_DRIFT | HMF_WRITE | HMF_REDUCE | HMF_IN64, B0 * dt, 0.0, D0 * dt, q, p, f,
-                           nullptr, f32, next()),
+                           f32, next()),
            "step: first pass");
     for (int64_t s = 0; s < nsteps; ++s) {
-        MD_TRY(launch_hmf_pass(c, k++, stage, B1 * dt, 0.0, D1 * dt, q, p, nullptr, nullptr, f32, next()),
+        MD_TRY(launch_hmf_pass(c, k++, stage, B1 * dt, 0.0, D1 * dt, q, p, nullptr, f32, next()),
                "step: pass");
-        MD_TRY(launch_hmf_pass(c, k++, stage, B1 * dt, 0.0, D0 * dt, q, p, nullptr, nullptr, f32, next()),
+        MD_TRY(launch_hmf_pass(c, k++, stage, B1 * dt, 0.0, D0 * dt, q, p, nullptr, f32, next()),
                "step: pass");
         if (s + 1 < nsteps)
-            MD_TRY(launch_hmf_pass(c, k++, stage | HMF_KICK2, B0 * dt, B0 * dt, D0 * dt, q, p, nullptr, nullptr,
+            MD_TRY(launch_hmf_pass(c, k++, stage | HMF_KICK2, B0 * dt, B0 * dt, D0 * dt, q, p, nullptr,
                                    f32, next()),
                    "step: pass");
         else
-            MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_M | HMF_STORE_F | HMF_WRITE | HMF_OUT64, B0 * dt, 0.0, 0.0, q, p, nullptr,
-                                   f, f32),
+            MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_M | HMF_STORE_F | HMF_WRITE | HMF_OUT64, B0 * dt, 0.0, 0.0, q, p, f,
+                                   f32),
                    "step: last pass");
     }
     return MD_OK;

@@ -219,8 +219,8 @@ __global__ __launch_bounds__(256) void k_batch_energy_finalize(const double *__r
     __shared__ double lds[2][4];
     const int b = blockIdx.x;
     double v = 0.0, k2 = 0.0;
-    for (int e = eoff[b] + (int)threadIdx.x; e < eoff[b + 1]; e += blockDim.x) v += ered[e];
-    for (int r = roff[b] + (int)threadIdx.x; r < roff[b + 1]; r += blockDim.x) k2 += kred[r];
+    for (int e = eoff[b] + (int)threadIdx.x; e < eoff[b + 1]; e += 256) v += ered[e];
+    for (int r = roff[b] + (int)threadIdx.x; r < roff[b + 1]; r += 256) k2 += kred[r];
     v = block_sum(v, lds[0]);
     k2 = block_sum(k2, lds[1]);
     if (threadIdx.x == 0) {
@@ -241,7 +241,7 @@ template <typename T, typename A, int IPL>
 __global__ __launch_bounds__(256) void k_batch_pair_ring_win(const PairItem *__restrict__ items,
                                                              const T *__restrict__ cs,
                                                              const double *__restrict__ beps, int npad, int jtile,
-                                                             double *__restrict__ part)
+                                                             int waves, double *__restrict__ part)
 {
     __shared__ T win[2][kWinJ];
     const PairItem it = items[blockIdx.x];
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void k_batch_pair_ring_win(const PairItem *__r
         si[k] = ss[i];
     }
     window_stream<kWinJ>(
-        cc, ss, it.j0, it.j1, jtile, win,
+        cc, ss, it.j0, it.j1, jtile, win, waves * kWave,
         [&](T cj, T sj) {
 #pragma unroll
             for (int k = 0; k < IPL; ++k) ring_term(ci[k], si[k], cj, sj, e, a[k]);
@@ -405,9 +405,9 @@ hipError_t pair_launch(md_ctx *c, const void *src)
     } else if constexpr (sizeof(T) == 4) {
         const T *cs = static_cast<const T *>(src);
         switch (c->tiles.ipl) {
-        case 1: hipLaunchKernelGGL((k_batch_pair_ring_win<T, A, 1>), grid, block, 0, c->stream, items, cs, B.d_eps, npad, jt, c->part); break;
-        case 2: hipLaunchKernelGGL((k_batch_pair_ring_win<T, A, 2>), grid, block, 0, c->stream, items, cs, B.d_eps, npad, jt, c->part); break;
-        default: hipLaunchKernelGGL((k_batch_pair_ring_win<T, A, 4>), grid, block, 0, c->stream, items, cs, B.d_eps, npad, jt, c->part); break;
+        case 1: hipLaunchKernelGGL((k_batch_pair_ring_win<T, A, 1>), grid, block, 0, c->stream, items, cs, B.d_eps, npad, jt, c->tiles.waves, c->part); break;
+        case 2: hipLaunchKernelGGL((k_batch_pair_ring_win<T, A, 2>), grid, block, 0, c->stream, items, cs, B.d_eps, npad, jt, c->tiles.waves, c->part); break;
+        default: hipLaunchKernelGGL((k_batch_pair_ring_win<T, A, 4>), grid, block, 0, c->stream, items, cs, B.d_eps, npad, jt, c->tiles.waves, c->part); break;
         }
     } else {
         const T *cs = static_cast<const T *>(src);

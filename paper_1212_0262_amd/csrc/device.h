@@ -205,9 +205,15 @@ __device__ __forceinline__ V lane_value(V v)
     return __builtin_bit_cast(V, ((uint64_t)hi << 32) | lo);
 }
 
-// Sum over a block of up to 1024 threads (blockDim.x a multiple of 64).  `lds` must
-// hold blockDim.x/64 doubles.  The result is valid in thread 0 only.  Contains a
-// __syncthreads(): every thread of the block must call it.
+// The kernels take their block and grid sizes as arguments or constants, never from
+// blockDim or gridDim: those are hidden arguments, 256 bytes more for the host to write
+// for each launch.  Measured host time of a launch (MI355X, arguments written to device
+// memory): 2.7 us with 12 to 104 bytes of arguments, 3.4 us with the hidden ones or with
+// 136 bytes and more; small systems' stages are bound by it.
+
+// Sum over a block of T threads.  `lds` must hold T/64 doubles.  The result is valid in
+// thread 0 only.  Contains a __syncthreads(): every thread of the block must call it.
+template <int T = 256>
 __device__ __forceinline__ double block_sum(double v, double *lds)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -217,8 +223,8 @@ __device__ __forceinline__ double block_sum(double v, double *lds)
     __syncthreads();
     double t = 0.0;
     if (threadIdx.x == 0) {
-        const int nw = blockDim.x / kWave;
-        for (int w = 0; w < nw; ++w) t += lds[w];
+#pragma unroll
+        for (int w = 0; w < T / kWave; ++w) t += lds[w];
     }
     return t;
 }

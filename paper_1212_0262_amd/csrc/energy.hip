@@ -58,11 +58,11 @@ __global__ __launch_bounds__(kEnergyBlock) void k_energy_pairs(const double *__r
 }
 
 // Block partials of sum p^2 over len values (HMF).
-__global__ __launch_bounds__(256) void k_sumsq(const double *__restrict__ p, int64_t len,
+__global__ __launch_bounds__(256) void k_sumsq(const double *__restrict__ p, int64_t len, int blocks,
                                                double *__restrict__ red)
 {
     __shared__ double lds[4];
-    const double b = block_sum(sumsq_part(p, len, (int)blockIdx.x, (int)gridDim.x), lds);
+    const double b = block_sum(sumsq_part(p, len, (int)blockIdx.x, blocks), lds);
     if (threadIdx.x == 0) red[blockIdx.x] = b;
 }
 
@@ -97,9 +97,9 @@ __global__ __launch_bounds__(kFinThreads) void k_energy_finalize(const double *_
     const double pk = ordered_part(redK, nk, 1);
     const double pv = ordered_part(redV, nv, model == MD_HMF ? 2 : 1);
     const double ps = model == MD_HMF ? ordered_part(redV + 1, nv, 2) : 0.0;
-    const double k2 = block_sum(pk, lds[0]);
-    const double sv = block_sum(pv, lds[1]);
-    const double ss = block_sum(ps, lds[2]);
+    const double k2 = block_sum<kFinThreads>(pk, lds[0]);
+    const double sv = block_sum<kFinThreads>(pv, lds[1]);
+    const double ss = block_sum<kFinThreads>(ps, lds[2]);
     if (threadIdx.x != 0) return;
     double v;
     if (model == MD_HMF) {
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void k_finite_flag(const double *__restrict__ 
                                                      unsigned *__restrict__ flag)
 {
     int bad = 0;
-    for (int k = threadIdx.x; k < count; k += blockDim.x) bad |= !isfinite(v[k]);
+    for (int k = threadIdx.x; k < count; k += 256) bad |= !isfinite(v[k]);
     bad = __syncthreads_or(bad);
     if (threadIdx.x == 0) *flag = bad ? 1u : 0u;
 }
@@ -176,12 +176,11 @@ hipError_t launch_energy(md_ctx *c, const double *q, const double *p, double *ou
     if (c->model == MD_HMF) {
         // block partials of sum cos, sum sin of q (added here in FP64, in a fixed order; the pass's
         // fixed-point sums are not read)
-        hipError_t e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, const_cast<double *>(q), nullptr, nullptr,
-                                       nullptr, false);
+        hipError_t e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, const_cast<double *>(q), nullptr, nullptr, false);
         if (e != hipSuccess) return e;
         nv = hmf_grid(c->n);
         redV = const_cast<double *>(hmf_partials(c));
-        hipLaunchKernelGGL(k_sumsq, dim3((unsigned)nk), dim3(256), 0, c->stream, p, len, redK);
+        hipLaunchKernelGGL(k_sumsq, dim3((unsigned)nk), dim3(256), 0, c->stream, p, len, nk, redK);
     } else {
         const EnergyGrid g = energy_grid(c->n);
         const dim3 grid((unsigned)(g.ng * g.nc + nk));
@@ -208,8 +207,7 @@ hipError_t launch_magnetization(md_ctx *c, const double *q, double *out2)
     if (hmf_small(c)) return launch_hmf_small_eval(c, q, nullptr, out2, nullptr, nullptr, finite_flag(c));
     hipError_t e = launch_hmf_begin(c);
     if (e == hipSuccess)
-        e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, const_cast<double *>(q), nullptr, nullptr, nullptr,
-                            false);
+        e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, const_cast<double *>(q), nullptr, nullptr, false);
     if (e != hipSuccess) return e;
     return launch_hmf_magnetization(c, out2);
 }

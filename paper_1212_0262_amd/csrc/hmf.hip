@@ -47,11 +47,6 @@ struct alignas(sizeof(T) * W) Vec {
     T x[W];
 };
 
-struct PassArgs {
-    double kick1, kick2, drift;
-    int flags;
-};
-
 // The work of one stage on E particles: kick (with f from f_in or from M), drift,
 // and the sincos of the new angle into the partial sums (of the particles with
 // ok[e]; in the order of e).  Each step runs over all E particles before the next,
@@ -132,23 +127,30 @@ __device__ __forceinline__ void limbs_mean(const long long *__restrict__ acc, in
 // partials (sum cos, sum sin) to red[2b], red[2b+1].  LIMBS (in-pass sums):
 // HMF_KICK_M / HMF_STORE_F take the magnetization from the limb sums mrd, each
 // wavefront by itself (block 0 also stores it to M), HMF_REDUCE adds the partials'
-// limbs to mwr, and block 0 zeroes mzero for a later pass.
+// limbs to mwr, and block 0 zeroes mzero for the next pass.
 // Without LIMBS the kernel reads M[0..1] and leaves the partials to the one-block
 // kernel (no code of the limbs).  Launched with 256 threads.
+// f: read by HMF_KICK_F, written by HMF_STORE_F.  macc: the limb sums, three buffers
+// [kMSlots][kMLimbs] in turn: buf is read, the next added to, the one after it zeroed.
 // FP32 state: HMF_IN64 takes the state from th64, p64 instead (angles wrapped),
-// HMF_OUT64 writes it there.
+// HMF_OUT64 writes it there.  FP64 state: the drifted angles also go to snap (both x64).
 template <typename T, int W, int U, bool LIMBS>
 __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restrict__ p,
-                                                  const double *__restrict__ f_in, double *__restrict__ f_out,
-                                                  const long long *__restrict__ mrd, long long *__restrict__ mwr,
-                                                  long long *__restrict__ mzero, double *__restrict__ M,
-                                                  PassArgs a, int n, double *__restrict__ red, T *__restrict__ snap,
-                                                  double *__restrict__ th64, double *__restrict__ p64)
+                                                  long long *__restrict__ macc, double *__restrict__ M, int n,
+                                                  int grid, int flags, int buf, double *__restrict__ f,
+                                                  double *__restrict__ red, double kick1, double kick2, double drift,
+                                                  double *__restrict__ x64, double *__restrict__ p64)
 {
     __shared__ double lds[2][4];
-    const int flags = a.flags;
-    const T k1 = (T)a.kick1, k2 = (T)a.kick2, dr = (T)a.drift;
+    double *__restrict__ th64 = x64;  // FP32 state
+    double *__restrict__ snap = x64;  // FP64 state
+    constexpr int B = kMSlots * kMLimbs;  // words per limb buffer; the three in turn: read, add, zero
+    const long long *__restrict__ mrd = macc + buf * B;
+    long long *__restrict__ mwr = macc + (buf == 2 ? 0 : buf + 1) * B;
+    long long *__restrict__ mzero = macc + (buf == 0 ? 2 : buf - 1) * B;
+    const T k1 = (T)kick1, k2 = (T)kick2, dr = (T)drift;
     const bool in64 = sizeof(T) == 4 && (flags & HMF_IN64), out64 = sizeof(T) == 4 && (flags & HMF_OUT64);
+    const bool take_snap = sizeof(T) == 8 && snap && (flags & HMF_DRIFT);
     T mx = 0, my = 0;
     if (flags & (HMF_KICK_M | HMF_STORE_F)) {
         if constexpr (LIMBS) {
@@ -170,11 +172,11 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
     const bool write = flags & HMF_WRITE;
     double sc = 0.0, ss = 0.0;
     const int nvec = n / W;
-    const int stride = gridDim.x * blockDim.x;
+    const int stride = grid * 256;
     using VT = Vec<T, W>;
     using VD = Vec<double, W>;
     constexpr int E = U * W;  // particles per thread and iteration: e = u W + w
-    for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < nvec; base += stride * U) {
+    for (int base = blockIdx.x * 256 + threadIdx.x; base < nvec; base += stride * U) {
         VT t[U], q[U];
         VD fi[U];
         bool ok[E];
@@ -195,7 +197,7 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
                     t[u] = reinterpret_cast<const VT *>(th)[v];
                     if (need_p) q[u] = reinterpret_cast<const VT *>(p)[v];
                 }
-                if (flags & HMF_KICK_F) fi[u] = reinterpret_cast<const VD *>(f_in)[v];
+                if (flags & HMF_KICK_F) fi[u] = reinterpret_cast<const VD *>(f)[v];
             }
 #pragma unroll
             for (int w = 0; w < W; ++w) ok[u * W + w] = v < nvec;
@@ -222,7 +224,7 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
                 po.x[w] = pe[u * W + w];
                 ff.x[w] = fo[u * W + w];
             }
-            if (flags & HMF_STORE_F) reinterpret_cast<VD *>(f_out)[v] = ff;
+            if (flags & HMF_STORE_F) reinterpret_cast<VD *>(f)[v] = ff;
             if (write && out64) {
 #pragma unroll
                 for (int w = 0; w < W; ++w) {
@@ -233,7 +235,7 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
                 reinterpret_cast<VT *>(th)[v] = to;
                 if (need_p) reinterpret_cast<VT *>(p)[v] = po;
             }
-            if (snap && (flags & HMF_DRIFT)) {
+            if (take_snap) {
 #pragma unroll
                 for (int w = 0; w < W; ++w) snap[v * W + w] = to.x[w];
             }
@@ -250,11 +252,11 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
             t1[0] = th[i];
             if (need_p) p1[0] = p[i];
         }
-        const double f1[1] = {(flags & HMF_KICK_F) ? f_in[i] : 0.0};
+        const double f1[1] = {(flags & HMF_KICK_F) ? f[i] : 0.0};
         double fo1[1] = {0.0};
         const bool ok1[1] = {true};
         stage_n(t1, p1, f1, fo1, ok1, mx, my, k1, k2, dr, flags, sc, ss);
-        if (flags & HMF_STORE_F) f_out[i] = fo1[0];
+        if (flags & HMF_STORE_F) f[i] = fo1[0];
         if (write && out64) {
             th64[i] = (double)t1[0];
             p64[i] = (double)p1[0];
@@ -262,7 +264,7 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
             th[i] = t1[0];
             if (need_p) p[i] = p1[0];
         }
-        if (snap && (flags & HMF_DRIFT)) snap[i] = t1[0];
+        if (take_snap) snap[i] = t1[0];
     }
     if (flags & HMF_REDUCE) {
         // lane 0 of a wavefront has its sum cos, lane 32 its sum sin; the first
@@ -331,8 +333,8 @@ __global__ __launch_bounds__(1024) void k_hmf_finalize(const double *__restrict_
             s += vs[k];
         }
     }
-    c = block_sum(c, lds[0]);
-    s = block_sum(s, lds[1]);
+    c = block_sum<1024>(c, lds[0]);
+    s = block_sum<1024>(s, lds[1]);
     if (threadIdx.x == 0) {
         M[0] = c / (double)n;
         M[1] = s / (double)n;
@@ -402,15 +404,15 @@ __global__ __launch_bounds__(1024) void k_hmf_adj_finalize(const double *__restr
     }
 }
 
-// Elementwise, with the product hw = H(th) lp from its sums (part_in, g blocks of them,
-// or sums): out = hw (ADJ_OUT); lq -= h hw (ADJ_KICK), lq -= h2 hw (ADJ_KICK2);
+// Elementwise (g blocks of 256 threads), with the product hw = H(th) lp from its sums
+// (part_in, g blocks of them, or sums): out = hw (ADJ_OUT); lq -= h hw (ADJ_KICK), lq -= h2 hw (ADJ_KICK2);
 // lp += a lq (ADJ_DRIFT).  Then, if th_next is given, the block partials of the sums of
 // H(th_next) lp to part_out.  Grid-stride over a grid fixed per n.  W: elements per
 // vector access; U: vectors per thread and iteration; IN: sums from part_in.
 template <int W, int U, bool IN>
 __global__ __launch_bounds__(256) void k_hmf_adj_pass(const double *__restrict__ th, const double *__restrict__ part_in,
-                                                      int g, const double *__restrict__ sums, int flags, double h,
-                                                      double h2, double a, int n, double *__restrict__ lq,
+                                                      const double *__restrict__ sums, int g, int flags, int n,
+                                                      double h, double h2, double a, double *__restrict__ lq,
                                                       double *__restrict__ lp, double *__restrict__ out,
                                                       const double *__restrict__ th_next,
                                                       double *__restrict__ part_out)
@@ -460,8 +462,8 @@ __global__ __launch_bounds__(256) void k_hmf_adj_pass(const double *__restrict__
         }
     };
     const bool need_x = flags & (ADJ_KICK | ADJ_DRIFT);
-    const int nvec = n / W, stride = gridDim.x * blockDim.x;
-    for (int base = blockIdx.x * blockDim.x + threadIdx.x; base < nvec; base += stride * U) {
+    const int nvec = n / W, stride = g * 256;
+    for (int base = blockIdx.x * 256 + threadIdx.x; base < nvec; base += stride * U) {
         double t[E], tn[E], x[E], w[E], hw[E];
         bool ok[E];
 #pragma unroll
@@ -526,7 +528,7 @@ __global__ __launch_bounds__(256) void k_hmf_adj_pass(const double *__restrict__
 }  // namespace
 
 // Vector width of the accesses for this context (1 when a pointer is not 16-byte aligned).
-static int vec_width(bool f32, const void *a, const void *b, const void *c, const void *d)
+static int vec_width(bool f32, const void *a, const void *b, const void *c, const void *d = nullptr)
 {
     const uintptr_t m = (uintptr_t)a | (uintptr_t)b | (uintptr_t)c | (uintptr_t)d;
     if (m & 15u) return 1;
@@ -540,7 +542,8 @@ static int vec_width(bool f32, const void *a, const void *b, const void *c, cons
 // chain, and 2048 a block leaves most CUs idle (49 blocks at N = 1e5).
 // Measured, us per step before (2048 a block, M by a barrier and LDS in every block) and
 // after, FP64 / FP32 state: N = 16,384 21.5 / 19.4 -> 12.0 / 11.4; 100,003 22.6 / 20.0 ->
-// 13.6 / 12.4; 400,000 24.5 / 21.0 -> 19.1 / 16.0; 1e6 33.0 / 26.3 -> 27.7 / 19.8.
+// 13.6 / 12.4; 400,000 24.5 / 21.0 -> 19.1 / 16.0; 1e6 33.0 / 26.3 -> 27.7 / 19.8 (and with
+// the cheaper launches of device.h 9.9 / 9.2, 11.3 / 10.6, 17.4 / 15.2, 26.2 / 19.1).
 static int64_t hmf_block(int64_t n)
 {
     int64_t per = 256;
@@ -571,38 +574,34 @@ hipError_t launch_hmf_begin(md_ctx *c)
 }
 
 hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kick2, double drift, double *th,
-                           double *p, const double *f_in, double *f_out, bool f32state, double *snap)
+                           double *p, double *f, bool f32state, double *snap)
 {
     if (!f32state) flags &= ~(HMF_IN64 | HMF_OUT64);
     const int n = (int)c->n;
     const int g = hmf_grid(c->n);
-    const PassArgs a{kick1, kick2, drift, flags};
-    constexpr int B = kMSlots * kMLimbs;  // words per limb buffer
     // Small grids: M from the limb sums inside the pass, no other launch.  Large
     // ones: the one-block kernel over the FP64 partials after a reducing pass, and
     // M read from c->scal.
     const bool in_pass = hmf_in_pass(c);
-    const long long *mrd = in_pass ? c->macc + (size_t)((k + 2) % 3) * B : nullptr;
-    long long *mwr = in_pass ? c->macc + (size_t)(k % 3) * B : nullptr;
-    long long *mzero = in_pass ? c->macc + (size_t)((k + 1) % 3) * B : nullptr;
-    const int ts = timed_begin(c, "k_hmf_pass");
+    const int buf = (k + 2) % 3;
+    const bool vec = (f32state ? vec_width(true, c->th32, c->p32, f) : vec_width(false, th, p, f)) > 1;
     // the vector and unroll that give a thread hmf_block / 256 particles (two iterations
     // of kUnroll 16-byte vectors at most); W = 1 where a pointer is not 16-byte aligned
     const int per = (int)(hmf_block(c->n) / 256);
-#define MD_HMF_PASS(T_, W_, U_, L_, TH_, P_, SNAP_)                                                                \
-    hipLaunchKernelGGL((k_hmf_pass<T_, W_, U_, L_>), dim3(g), dim3(256), 0, c->stream, TH_, P_, f_in, f_out, mrd, \
-                       mwr, mzero, c->scal, a, n, c->red, SNAP_, th, p)
-#define MD_HMF_FORM(T_, V_, TH_, P_, SNAP_)                                                    \
-    do {                                                                                       \
-        const bool vec = vec_width(sizeof(T_) == 4, TH_, P_, f_in, f_out) > 1;                 \
-        if (!in_pass && vec) MD_HMF_PASS(T_, V_, kUnroll, false, TH_, P_, SNAP_);              \
-        else if (!in_pass) MD_HMF_PASS(T_, 1, kUnroll, false, TH_, P_, SNAP_);                 \
-        else if (vec && per >= V_ * kUnroll) MD_HMF_PASS(T_, V_, kUnroll, true, TH_, P_, SNAP_); \
-        else if (vec && per >= V_) MD_HMF_PASS(T_, V_, 1, true, TH_, P_, SNAP_);               \
-        else if (per >= kUnroll) MD_HMF_PASS(T_, 1, kUnroll, true, TH_, P_, SNAP_);            \
-        else MD_HMF_PASS(T_, 1, 1, true, TH_, P_, SNAP_);                                      \
+    const int ts = timed_begin(c, "k_hmf_pass");
+#define MD_HMF_PASS(T_, W_, U_, L_, TH_, P_, X_)                                                                 \
+    hipLaunchKernelGGL((k_hmf_pass<T_, W_, U_, L_>), dim3(g), dim3(256), 0, c->stream, TH_, P_, c->macc, c->scal, n, \
+                       g, flags, buf, f, c->red, kick1, kick2, drift, X_, p)
+#define MD_HMF_FORM(T_, V_, TH_, P_, X_)                                                     \
+    do {                                                                                     \
+        if (!in_pass && vec) MD_HMF_PASS(T_, V_, kUnroll, false, TH_, P_, X_);               \
+        else if (!in_pass) MD_HMF_PASS(T_, 1, kUnroll, false, TH_, P_, X_);                  \
+        else if (vec && per >= V_ * kUnroll) MD_HMF_PASS(T_, V_, kUnroll, true, TH_, P_, X_); \
+        else if (vec && per >= V_) MD_HMF_PASS(T_, V_, 1, true, TH_, P_, X_);                \
+        else if (per >= kUnroll) MD_HMF_PASS(T_, 1, kUnroll, true, TH_, P_, X_);             \
+        else MD_HMF_PASS(T_, 1, 1, true, TH_, P_, X_);                                       \
     } while (0)
-    if (f32state) MD_HMF_FORM(float, 4, c->th32, c->p32, (float *)nullptr);
+    if (f32state) MD_HMF_FORM(float, 4, c->th32, c->p32, th);
     else MD_HMF_FORM(double, 2, th, p, snap);  // snap: element stores, any alignment
 #undef MD_HMF_FORM
 #undef MD_HMF_PASS
@@ -645,8 +644,8 @@ hipError_t launch_hmf_adj_pass(md_ctx *c, int k, const double *th, int flags, do
     const bool vec = vec_width(false, th, lq, lp, out) > 1 && ((uintptr_t)th_next & 15u) == 0 && per >= 512;
     const dim3 grid((unsigned)blocks), block(256);
 #define MD_ADJ_PASS(W_, U_, IN_)                                                                                  \
-    hipLaunchKernelGGL((k_hmf_adj_pass<W_, U_, IN_>), grid, block, 0, c->stream, th, pin, (int)blocks, c->scal + 4, \
-                       flags, h, h2, a, n, lq, lp, out, th_next, pout)
+    hipLaunchKernelGGL((k_hmf_adj_pass<W_, U_, IN_>), grid, block, 0, c->stream, th, pin, c->scal + 4, (int)blocks, \
+                       flags, n, h, h2, a, lq, lp, out, th_next, pout)
     if (!in) {
         if (vec) MD_ADJ_PASS(2, 2, false);
         else MD_ADJ_PASS(1, 2, false);

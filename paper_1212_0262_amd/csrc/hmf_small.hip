@@ -29,16 +29,16 @@ constexpr int small_threads(int P) { return P > 8 ? 256 : 512; }
 constexpr int kSmallWaves = 16;  // the wavefronts' sums: one row of lanes
 static_assert(small_threads(1) <= kSmallWaves * kWave, "a lane per wavefront");
 
-// The totals of K = 2 or 4 values over the block, divided by n, in every thread.  The
+// The totals of K = 2 or 4 values over the block of B threads, divided by n, in every thread.  The
 // first lane exchanges put the K values in different rows of lanes, so that one chain
 // of moves and adds serves them all; the wavefronts' sums meet in lds (this stage's
 // buffer: two alternate, as a wavefront may be a stage ahead), one row of lanes per
 // value.  Every wavefront does this, so a block takes as few of them as fill its SIMDs.
 template <int K>
-__device__ __forceinline__ void small_means(double (&v)[K], double (&lds)[K][kSmallWaves], double n)
+__device__ __forceinline__ void small_means(double (&v)[K], double (&lds)[K][kSmallWaves], int B, double n)
 {
     static_assert(K == 2 || K == 4, "");
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = blockDim.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, nw = B / kWave;
     double t;
     if constexpr (K == 2) t = wave_sum2(v[0], v[1]);
     else t = wave_sum4(v[0], v[1], v[2], v[3]);
@@ -58,16 +58,23 @@ __device__ __forceinline__ void small_means(double (&v)[K], double (&lds)[K][kSm
 
 // sum cos, sum sin of the thread's particles below n.
 template <typename T, int P>
-__device__ __forceinline__ void small_sums(const T (&s)[P], const T (&c)[P], int n, double (&v)[2])
+__device__ __forceinline__ void small_sums(const T (&s)[P], const T (&c)[P], int n, int B, double (&v)[2])
 {
     v[0] = v[1] = 0.0;
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        if ((int)(threadIdx.x + k * blockDim.x) < n) {
+        if ((int)(threadIdx.x + k * B) < n) {
             v[0] += (double)c[k];
             v[1] += (double)s[k];
         }
     }
+}
+
+// The block's threads: a constant where the registers are short.
+template <int P>
+__device__ __forceinline__ int small_block(int threads)
+{
+    return P > 8 ? small_threads(P) : threads;
 }
 
 // eq. 6
@@ -88,15 +95,16 @@ struct StepCoef {
 // nsteps >= 1 Yoshida steps.  snap (nullable): the angles after each drift, stride apart.
 template <typename T, int P>
 __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_step(double *__restrict__ q, double *__restrict__ p,
-                                                                  double *__restrict__ f, int n, StepCoef a,
+                                                                  double *__restrict__ f, int n, int threads, StepCoef a,
                                                                   int nsteps, double *__restrict__ snap, size_t stride)
 {
+    const int B = small_block<P>(threads);
     __shared__ double lds[2][2][kSmallWaves];
     const T b0 = (T)a.b0, b1 = (T)a.b1, d0 = (T)a.d0, d1 = (T)a.d1;
     T th[P], pp[P], s[P], c[P];
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        const int i = threadIdx.x + k * blockDim.x;
+        const int i = threadIdx.x + k * B;
         const double qi = i < n ? q[i] : 0.0, pi = i < n ? p[i] : 0.0, fi = i < n ? f[i] : 0.0;
         th[k] = (T)qi;
         if constexpr (sizeof(T) == 4) th[k] = wrap_pi(th[k]);
@@ -114,14 +122,14 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_step(double *__r
         if (snap) {
 #pragma unroll
             for (int k = 0; k < P; ++k) {
-                const int i = threadIdx.x + k * blockDim.x;
+                const int i = threadIdx.x + k * B;
                 if (i < n) snap[(size_t)m * stride + i] = (double)th[k];
             }
         }
         sincos_n(th, s, c);
         double v[2];
-        small_sums(s, c, n, v);
-        small_means(v, lds[m & 1], n);
+        small_sums(s, c, n, B, v);
+        small_means(v, lds[m & 1], B, n);
         const T mx = (T)v[0], my = (T)v[1];
         const T k1 = r == 2 ? b0 : b1;
         T(&fm)[P] = s;  // the force, in the place of the sines
@@ -133,7 +141,7 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_step(double *__r
         if (m == last) {
 #pragma unroll
             for (int k = 0; k < P; ++k) {
-                const int i = threadIdx.x + k * blockDim.x;
+                const int i = threadIdx.x + k * B;
                 if (i < n) {
                     q[i] = (double)th[k];
                     p[i] = (double)pp[k];
@@ -155,32 +163,33 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_step(double *__r
 // energies are finite.
 template <int P>
 __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_eval(const double *__restrict__ q,
-                                                                  const double *__restrict__ p, int n,
+                                                                  const double *__restrict__ p, int n, int threads,
                                                                   double *__restrict__ M, double *__restrict__ out2,
                                                                   double *__restrict__ f, double *__restrict__ out3,
                                                                   unsigned *__restrict__ flag)
 {
+    const int B = small_block<P>(threads);
     __shared__ double lds[2][2][kSmallWaves];
     double th[P], pp[P], s[P], c[P], k2[2] = {0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        const int i = threadIdx.x + k * blockDim.x;
+        const int i = threadIdx.x + k * B;
         th[k] = i < n ? q[i] : 0.0;
         pp[k] = out3 && i < n ? p[i] : 0.0;
         k2[0] += pp[k] * pp[k];
     }
     sincos_n(th, s, c);
     double v[2];
-    small_sums(s, c, n, v);
-    small_means(v, lds[0], n);
+    small_sums(s, c, n, B, v);
+    small_means(v, lds[0], B, n);
     if (f) {
 #pragma unroll
         for (int k = 0; k < P; ++k) {
-            const int i = threadIdx.x + k * blockDim.x;
+            const int i = threadIdx.x + k * B;
             if (i < n) f[i] = small_force(s[k], c[k], v[0], v[1]);
         }
     }
-    if (out3) small_means(k2, lds[1], 1.0);
+    if (out3) small_means(k2, lds[1], B, 1.0);
     if (threadIdx.x != 0) return;
     if (M) {
         M[0] = v[0];
@@ -205,20 +214,20 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_eval(const doubl
 // The four means (Mx, My, Cw, Sw) of the product H(t) w (hmf.hip).
 template <int P>
 __device__ __forceinline__ void small_hvp_means(const double (&s)[P], const double (&c)[P], const double (&w)[P],
-                                                int n, double (&lds)[4][kSmallWaves], double (&v)[4])
+                                                int n, int B, double (&lds)[4][kSmallWaves], double (&v)[4])
 {
 #pragma unroll
     for (int k = 0; k < 4; ++k) v[k] = 0.0;
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        if ((int)(threadIdx.x + k * blockDim.x) < n) {
+        if ((int)(threadIdx.x + k * B) < n) {
             v[0] += c[k];
             v[1] += s[k];
             v[2] += c[k] * w[k];
             v[3] += s[k] * w[k];
         }
     }
-    small_means(v, lds, n);
+    small_means(v, lds, B, n);
 }
 
 __device__ __forceinline__ double small_hw(double s, double c, double w, const double (&v)[4])
@@ -229,22 +238,23 @@ __device__ __forceinline__ double small_hw(double s, double c, double w, const d
 // out = H(q) w.
 template <int P>
 __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_hvp(const double *__restrict__ q,
-                                                                 const double *__restrict__ w, int n,
+                                                                 const double *__restrict__ w, int n, int threads,
                                                                  double *__restrict__ out)
 {
+    const int B = small_block<P>(threads);
     __shared__ double lds[4][kSmallWaves];
     double th[P], wk[P], s[P], c[P], v[4];
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        const int i = threadIdx.x + k * blockDim.x;
+        const int i = threadIdx.x + k * B;
         th[k] = i < n ? q[i] : 0.0;
         wk[k] = i < n ? w[i] : 0.0;
     }
     sincos_n(th, s, c);
-    small_hvp_means(s, c, wk, n, lds, v);
+    small_hvp_means(s, c, wk, n, B, lds, v);
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        const int i = threadIdx.x + k * blockDim.x;
+        const int i = threadIdx.x + k * B;
         if (i < n) out[i] = small_hw(s[k], c[k], wk[k], v);
     }
 }
@@ -255,23 +265,24 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_hvp(const double
 template <int P>
 __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_vjp(const double *__restrict__ q0,
                                                                  const double *__restrict__ pos, size_t stride, int n,
-                                                                 StepCoef a, int64_t nsteps, double *__restrict__ lq,
+                                                                 int threads, StepCoef a, int64_t nsteps, double *__restrict__ lq,
                                                                  double *__restrict__ lp)
 {
+    const int B = small_block<P>(threads);
     __shared__ double lds[2][4][kSmallWaves];
     double x[P], w[P], th[P], s[P], c[P], v[4];
     auto load = [&](int64_t m) {  // positions m (0 = q0), for the next product
         const double *__restrict__ src = m > 0 ? pos + (size_t)(m - 1) * stride : q0;
 #pragma unroll
         for (int k = 0; k < P; ++k) {
-            const int i = threadIdx.x + k * blockDim.x;
+            const int i = threadIdx.x + k * B;
             th[k] = i < n ? src[i] : 0.0;
         }
     };
     load(3 * nsteps);
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        const int i = threadIdx.x + k * blockDim.x;
+        const int i = threadIdx.x + k * B;
         x[k] = i < n ? lq[i] : 0.0;
         w[k] = i < n ? lp[i] : 0.0;
     }
@@ -279,7 +290,7 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_vjp(const double
     for (int64_t m = 3 * nsteps; m >= 0; --m, r = r == 0 ? 2 : r - 1) {
         sincos_n(th, s, c);
         if (m > 0) load(m - 1);  // in flight under the sums
-        small_hvp_means(s, c, w, n, lds[m & 1], v);
+        small_hvp_means(s, c, w, n, B, lds[m & 1], v);
         const double kick = r == 0 ? a.b0 : a.b1;
         const bool two = r == 0 && m > 0 && m < 3 * nsteps;  // the kicks of two steps at one position
 #pragma unroll
@@ -296,7 +307,7 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_vjp(const double
     }
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-        const int i = threadIdx.x + k * blockDim.x;
+        const int i = threadIdx.x + k * B;
         if (i < n) {
             lq[i] = x[k];
             lp[i] = w[k];
@@ -322,7 +333,8 @@ static_assert(kHmfSmallN <= 32 * small_threads(32), "every particle has a thread
     do {                                                                                           \
         const int per = small_per_thread(c->n);                                                    \
         const int64_t waves = (c->n + (int64_t)kWave * per - 1) / ((int64_t)kWave * per);          \
-        const dim3 block((unsigned)(waves * kWave));                                               \
+        const int B = per > 8 ? small_threads(per) : (int)(waves * kWave);                         \
+        const dim3 block((unsigned)B);                                                             \
         switch (per) {                                                                             \
         case 1: hipLaunchKernelGGL((K_(1)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
         case 2: hipLaunchKernelGGL((K_(2)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
@@ -346,8 +358,8 @@ hipError_t launch_hmf_small_steps(md_ctx *c, double b0, double b1, double d0, do
         const int ts = timed_begin(c, "k_hmf_small_step");
 #define K64(P_) k_hmf_small_step<double, P_>
 #define K32(P_) k_hmf_small_step<float, P_>
-        if (c->prec == MD_FP64) MD_SMALL(K64, q, p, f, n, a, k, sn, snap_stride);
-        else MD_SMALL(K32, q, p, f, n, a, k, sn, snap_stride);
+        if (c->prec == MD_FP64) MD_SMALL(K64, q, p, f, n, B, a, k, sn, snap_stride);
+        else MD_SMALL(K32, q, p, f, n, B, a, k, sn, snap_stride);
 #undef K64
 #undef K32
         err = hipGetLastError();
@@ -362,7 +374,7 @@ hipError_t launch_hmf_small_eval(md_ctx *c, const double *q, const double *p, do
 {
     const int n = (int)c->n;
 #define K(P_) k_hmf_small_eval<P_>
-    MD_SMALL(K, q, p, n, c->scal, out2, f, out3, flag);
+    MD_SMALL(K, q, p, n, B, c->scal, out2, f, out3, flag);
 #undef K
     return hipGetLastError();
 }
@@ -371,7 +383,7 @@ hipError_t launch_hmf_small_hvp(md_ctx *c, const double *q, const double *w, dou
 {
     const int n = (int)c->n;
 #define K(P_) k_hmf_small_hvp<P_>
-    MD_SMALL(K, q, w, n, out);
+    MD_SMALL(K, q, w, n, B, out);
 #undef K
     return hipGetLastError();
 }
@@ -382,7 +394,7 @@ hipError_t launch_hmf_small_vjp(md_ctx *c, double b0, double b1, double d0, doub
     const StepCoef a{b0, b1, d0, d1};
     const int n = (int)c->n;
 #define K(P_) k_hmf_small_vjp<P_>
-    MD_SMALL(K, q0, pos, stride, n, a, nsteps, lq, lp);
+    MD_SMALL(K, q0, pos, stride, n, B, a, nsteps, lq, lp);
 #undef K
     return hipGetLastError();
 }

@@ -203,11 +203,11 @@ hipError_t launch_fused(md_ctx *c, int flags, double kick1, double kick2, double
 // sums pass k - 1 added, adds its own to buffer k mod 3 and zeroes buffer
 // (k + 1) mod 3.  launch_hmf_begin zeroes buffer 0 before the first pass of a call
 // whose passes read M.
+// f: read by HMF_KICK_F or written by HMF_STORE_F.
 // snap (nullable, FP64 state only): with HMF_DRIFT, the drifted angles are also written there.
 hipError_t launch_hmf_begin(md_ctx *c);
-hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kick2, double drift,
-                           double *th, double *p, const double *f_in, double *f_out,
-                           bool f32state, double *snap = nullptr);
+hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kick2, double drift, double *th, double *p,
+                           double *f, bool f32state, double *snap = nullptr);
 hipError_t launch_hmf_adj_pass(md_ctx *c, int k, const double *th, int flags, double h, double h2, double a,
                                double *lq, double *lp, double *out, const double *th_next);
 // M from the limb sums of a call's pass 0, to out2[0..1] and the context scalars.

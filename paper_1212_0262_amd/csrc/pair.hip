@@ -37,12 +37,12 @@ using namespace pairs;
 // part[(s*2 + c)*npad + i] = sum over j in the s-th j range of the 2D pair term.
 template <typename T, typename A, int IPL>
 __global__ __launch_bounds__(256) void k_pair_2d(const T *__restrict__ xs, const T *__restrict__ ys,
-                                                 int n, int npad, int jlen, int jtile, T eps,
+                                                 int n, int npad, int jlen, int jtile, int waves, T eps,
                                                  double *__restrict__ part)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int ibase = (blockIdx.x * (blockDim.x / kWave) + wave) * (kWave * IPL) + lane;
+    const int ibase = (blockIdx.x * waves + wave) * (kWave * IPL) + lane;
     const int s = blockIdx.y;
     const int j0 = s * jlen;
     const int j1 = min(n, j0 + jlen);
@@ -101,11 +101,11 @@ __device__ __forceinline__ void ring_range(const T *__restrict__ cc, const T *__
 // cs = two rows of npad: [cos t | sin t] (FP64) or sqrt2 [cos(t/2) | sin(t/2)] (FP32).
 template <typename T, typename A, int IPL>
 __global__ __launch_bounds__(256) void k_pair_ring(const T *__restrict__ cs, int n, int npad, int jlen,
-                                                   int jtile, T one_eps, double *__restrict__ part)
+                                                   int jtile, int waves, T one_eps, double *__restrict__ part)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int ibase = (blockIdx.x * (blockDim.x / kWave) + wave) * (kWave * IPL) + lane;
+    const int ibase = (blockIdx.x * waves + wave) * (kWave * IPL) + lane;
     const int s = blockIdx.y;
     const int j0 = s * jlen;
     const int j1 = min(n, j0 + jlen);
@@ -144,12 +144,13 @@ constexpr int kWinJ = 512;  // j per window
 
 template <int MODEL, typename T, typename A, int IPL>
 __global__ __launch_bounds__(256) void k_pair_win(const T *__restrict__ r0, const T *__restrict__ r1, int n,
-                                                  int npad, int jlen, int jtile, T e, double *__restrict__ part)
+                                                  int npad, int jlen, int jtile, int waves, T e,
+                                                  double *__restrict__ part)
 {
     __shared__ T win[2][kWinJ];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    const int ibase = (blockIdx.x * (blockDim.x / kWave) + wave) * (kWave * IPL) + lane;
+    const int ibase = (blockIdx.x * waves + wave) * (kWave * IPL) + lane;
     const int s = blockIdx.y;
     const int j0 = s * jlen;
     const int j1 = min(n, j0 + jlen);
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(256) void k_pair_win(const T *__restrict__ r0, cons
             else ring_term(a0[k], a1[k], x, y, e, acc0[k]);
         }
     };
-    window_stream<kWinJ>(r0, r1, j0, j1, jtile, win, term, [&]() {
+    window_stream<kWinJ>(r0, r1, j0, j1, jtile, win, waves * kWave, term, [&]() {
 #pragma unroll
         for (int k = 0; k < IPL; ++k) {
             acc0[k].fold();
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(256) void k_update(const SlotT *__restrict__ part, 
                                                 void *__restrict__ ops, double kick1, double kick2,
                                                 double drift, int flags, double *__restrict__ snap)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) {  // with UPD_PREP the grid covers the pads too
         if ((flags & UPD_PREP) && i < npad) stage_pad<PREP>(i, npad, ops);
         return;
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(64) void k_update_vec(const SlotT *__restrict__ par
 {
     using V = typename SlotVec<SlotT, VW>::T;
     constexpr int U = kSlotBlock;
-    const int i0 = VW * (blockIdx.x * blockDim.x + threadIdx.x);
+    const int i0 = VW * (blockIdx.x * kWave + threadIdx.x);
     if (i0 >= npad) return;
     double fs[VW][D];
 #pragma unroll
@@ -572,18 +573,16 @@ __global__ __launch_bounds__(64) void k_update_vec(const SlotT *__restrict__ par
 // update launches.  The j operands come from `in`; the refreshed ones go to
 // `out` (another buffer: other blocks still read `in`), so the two alternate.
 template <int MODEL, typename T, typename A, int IPL, int PREP, int L>
-__global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, void *__restrict__ out, int n, int npad,
-                                                int jlen, int jtile, T e, double pref, double *__restrict__ f,
-                                                double *__restrict__ p, double *__restrict__ q, double kick1,
-                                                double kick2, double drift, int flags, double *__restrict__ snap)
+__global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double *__restrict__ q,
+                                                double *__restrict__ p, int n, int npad, int jlen, int S,
+                                                int slice_bytes, int CHL, int flags, int jtile, T e,
+                                                void *__restrict__ out, double pref, double *__restrict__ f,
+                                                double kick1, double kick2, double drift, double *__restrict__ snap)
 {
     constexpr int D = MODEL == MD_GRAV2D ? 2 : 1;
     constexpr int IL = kWave / L;          // i slots per lane group
     constexpr int PAD = L > 1 ? 1 : 0;     // group windows one element apart: no LDS bank conflicts
     extern __shared__ double lds[];
-    const int S = blockDim.x / kWave;
-    const int slice_bytes = kFusedLdsBytes / S;
-    const int CHL = ((slice_bytes / (2 * (int)sizeof(T) * L)) - PAD) / 16 * 16;  // j per group per window
     const int WS = CHL + PAD;              // window row stride per group
     const int lane = threadIdx.x & (kWave - 1);
     const int w = threadIdx.x / kWave;
@@ -606,7 +605,7 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, void *
     }
     // The stage's own q, p, fetched now so that their latency hides under the pair
     // loop (the block owns these particles: nothing else writes them meanwhile).
-    const bool one_pass = IPL * D * IL <= (int)blockDim.x;
+    const bool one_pass = IPL * D * IL <= S * kWave;
     double q_pre = 0.0, p_pre = 0.0;
     if (one_pass && (int)threadIdx.x < IPL * D * IL) {
         const int it = threadIdx.x, s2 = it % IL, kd = it / IL;
@@ -636,8 +635,10 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, void *
 #pragma unroll
         for (int k = 0; k < IPL; ++k) pair_2d_two(a0[k], a1[k], xa, ya, xb, yb, e, acc0[k], acc1[k]);
     };
+    // off: t modulo the window, run: t modulo jtile, counted (an integer division is tens
+    // of instructions, and at small N a wavefront has few j to spread them over)
+    int off = 0, run = 0;
     for (int t = 0; t < wlen; t += 16) {
-        const int off = t % CHL;
         if (off == 0) {
             wave_sync();  // the previous window's reads are done
             // The window's cnt j per group (none past the wavefront's longest range):
@@ -705,13 +706,17 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, void *
             }
             for (; u < len - t; ++u) term(w0[u], w1[u]);
         }
-        if (t < len && ((t + 16) % jtile == 0 || t + 16 >= len)) {
+        run += 16;
+        if (t < len && (run == jtile || t + 16 >= len)) {
 #pragma unroll
             for (int k = 0; k < IPL; ++k) {
                 acc0[k].fold();
                 if constexpr (MODEL == MD_GRAV2D) acc1[k].fold();
             }
         }
+        if (run == jtile) run = 0;
+        off += 16;
+        if (off == CHL) off = 0;
     }
     wave_sync();  // window reads done before the slice takes the partials
     double *part = reinterpret_cast<double *>(slice);  // [L][IPL * D][IL]
@@ -745,7 +750,7 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, void *
         }
         __syncthreads();
     }
-    for (int it = threadIdx.x; it < IPL * D * IL; it += blockDim.x) {
+    for (int it = threadIdx.x; it < IPL * D * IL; it += S * kWave) {
         const int s2 = it % IL, kd = it / IL;
         const int k = kd / D, d = kd % D;
         const int i = i0 + IL * k + s2;
@@ -846,11 +851,13 @@ hipError_t fused_ipl(md_ctx *c, int flags, double kick1, double kick2, double dr
     const int itile = kWave / L * t.ipl;
     const dim3 block((unsigned)(kWave * S));
     const dim3 grid((unsigned)((n + itile - 1) / itile));
-    const size_t lds = (size_t)(kFusedLdsBytes / S) * S;
+    const int slice = kFusedLdsBytes / S;  // bytes of a wavefront's window, then of its partials
+    const size_t lds = (size_t)slice * S;
     const T *src = static_cast<const T *>(in);
 #define MD_FUSED(I_, L_)                                                                                              \
-    hipLaunchKernelGGL((k_fused<MODEL, T, A, I_, PREP, L_>), grid, block, lds, c->stream, src, out, n, npad, jlen, \
-                       t.jtile, e, pref, f, p, q, kick1, kick2, drift, flags, snap)
+    hipLaunchKernelGGL((k_fused<MODEL, T, A, I_, PREP, L_>), grid, block, lds, c->stream, src, q, p, n, npad, jlen, \
+                       S, slice, (slice / (2 * (int)sizeof(T) * L_) - (L_ > 1 ? 1 : 0)) / 16 * 16, flags, t.jtile, e, \
+                       out, pref, f, kick1, kick2, drift, snap)
 #define MD_FUSED_L(I_)                          \
     switch (L) {                                \
     case 1: MD_FUSED(I_, 1); break;             \
@@ -874,16 +881,16 @@ hipError_t fused_ipl(md_ctx *c, int flags, double kick1, double kick2, double dr
 template <typename T, typename A>
 hipError_t pair_ipl(md_ctx *c, const void *src, dim3 grid, dim3 block, int jlen)
 {
-    const int n = (int)c->n, npad = (int)c->npad, jt = c->tiles.jtile;
+    const int n = (int)c->n, npad = (int)c->npad, jt = c->tiles.jtile, waves = c->tiles.waves;
     const int ts = timed_begin(c, c->model == MD_GRAV2D ? "k_pair_2d" : sizeof(T) == 4 ? "k_pair_win" : "k_pair_ring");
     if (c->model == MD_GRAV2D) {
         const T *x = static_cast<const T *>(src);
         const T *y = x + (src == c->ops ? npad : n);
         const T eps = (T)c->eps;
         switch (c->tiles.ipl) {
-        case 1: hipLaunchKernelGGL((k_pair_2d<T, A, 1>), grid, block, 0, c->stream, x, y, n, npad, jlen, jt, eps, c->part); break;
-        case 2: hipLaunchKernelGGL((k_pair_2d<T, A, 2>), grid, block, 0, c->stream, x, y, n, npad, jlen, jt, eps, c->part); break;
-        default: hipLaunchKernelGGL((k_pair_2d<T, A, 4>), grid, block, 0, c->stream, x, y, n, npad, jlen, jt, eps, c->part); break;
+        case 1: hipLaunchKernelGGL((k_pair_2d<T, A, 1>), grid, block, 0, c->stream, x, y, n, npad, jlen, jt, waves, eps, c->part); break;
+        case 2: hipLaunchKernelGGL((k_pair_2d<T, A, 2>), grid, block, 0, c->stream, x, y, n, npad, jlen, jt, waves, eps, c->part); break;
+        default: hipLaunchKernelGGL((k_pair_2d<T, A, 4>), grid, block, 0, c->stream, x, y, n, npad, jlen, jt, waves, eps, c->part); break;
         }
     } else if constexpr (sizeof(T) == 4) {
         // Ring FP32 forms: the LDS-window kernel
@@ -891,7 +898,7 @@ hipError_t pair_ipl(md_ctx *c, const void *src, dim3 grid, dim3 block, int jlen)
         const T e = (T)(2.0 * c->eps);  // half-angle form: 2 eps
 #define MD_WIN(I_)                                                                                                 \
     hipLaunchKernelGGL((k_pair_win<MD_RING, T, A, I_>), grid, block, 0, c->stream, r0, r0 + npad, n, npad, jlen, jt, \
-                       e, c->part)
+                       waves, e, c->part)
         switch (c->tiles.ipl) {
         case 1: MD_WIN(1); break;
         case 2: MD_WIN(2); break;
@@ -902,9 +909,9 @@ hipError_t pair_ipl(md_ctx *c, const void *src, dim3 grid, dim3 block, int jlen)
         const T *cs = static_cast<const T *>(src);
         const T one_eps = (T)(1.0 + c->eps);
         switch (c->tiles.ipl) {
-        case 1: hipLaunchKernelGGL((k_pair_ring<T, A, 1>), grid, block, 0, c->stream, cs, n, npad, jlen, jt, one_eps, c->part); break;
-        case 2: hipLaunchKernelGGL((k_pair_ring<T, A, 2>), grid, block, 0, c->stream, cs, n, npad, jlen, jt, one_eps, c->part); break;
-        default: hipLaunchKernelGGL((k_pair_ring<T, A, 4>), grid, block, 0, c->stream, cs, n, npad, jlen, jt, one_eps, c->part); break;
+        case 1: hipLaunchKernelGGL((k_pair_ring<T, A, 1>), grid, block, 0, c->stream, cs, n, npad, jlen, jt, waves, one_eps, c->part); break;
+        case 2: hipLaunchKernelGGL((k_pair_ring<T, A, 2>), grid, block, 0, c->stream, cs, n, npad, jlen, jt, waves, one_eps, c->part); break;
+        default: hipLaunchKernelGGL((k_pair_ring<T, A, 4>), grid, block, 0, c->stream, cs, n, npad, jlen, jt, waves, one_eps, c->part); break;
         }
     }
     const hipError_t err = hipGetLastError();

@@ -298,16 +298,16 @@ __device__ __forceinline__ void ring_term(T c0, T s0, T c1, T s1, T e, A &a)
 // term(x, y) runs for every j in ascending order and fold() after every jtile j
 // counted from j0 and at j1 (jtile a multiple of 16): the order of the
 // scalar-load kernels, so the same sums bit for bit.  j0 and j1 must be uniform
-// across the block (every thread reaches the barriers).
+// across the block of `threads` (every thread reaches the barriers).
 template <int WJ, typename T, typename Term, typename Fold>
 __device__ __forceinline__ void window_stream(const T *__restrict__ r0, const T *__restrict__ r1, int j0, int j1,
-                                              int jtile, T (*win)[WJ], Term &&term, Fold &&fold)
+                                              int jtile, T (*win)[WJ], int threads, Term &&term, Fold &&fold)
 {
     for (int g = j0; g < j1; g += 16) {
         const int off = (g - j0) % WJ;
         if (off == 0) {
             __syncthreads();  // the previous window's reads are done
-            for (int m = threadIdx.x; m < WJ; m += blockDim.x) {
+            for (int m = threadIdx.x; m < WJ; m += threads) {
                 const int j = g + m;
                 if (j < j1) {
                     win[0][m] = r0[j];
