@@ -262,7 +262,7 @@ enum md_launch { MD_LAUNCH_AUTO = 0, MD_LAUNCH_STAGED = 1, MD_LAUNCH_FUSED = 2, 
 #define MD_SYMMETRIC_AUTO_N 13312
 #define MD_SYMMETRIC_AUTO_N_COMP 15360
 #define MD_SYMMETRIC_AUTO_N_RING 13312
-#define MD_SYMMETRIC_AUTO_N_RING64 10240
+#define MD_SYMMETRIC_AUTO_N_RING64 4608
 int md_set_launch(md_ctx *c, int mode);
 int md_get_launch(const md_ctx *c);
 int md_get_sym_tile(const md_ctx *c);

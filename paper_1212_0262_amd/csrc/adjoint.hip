@@ -334,7 +334,7 @@ __device__ __forceinline__ void hvp_sym_block(const double *__restrict__ q, cons
         jw[wave][0][m] = sj[0].get();
         jw[wave][1][m] = sj[1].get();
         __syncthreads();
-        for (int x = threadIdx.x; x < 2 * kWave; x += W * kWave) {  // W = 1: a thread per (d, j) in turn
+        for (int x = threadIdx.x; x < 2 * kWave; x += W * kWave) {
             const int d = x / kWave, mm = x & (kWave - 1);
             double t = 0.0;
 #pragma unroll
@@ -372,13 +372,129 @@ __global__ __launch_bounds__(W * kWave) void k_hvp_sym(const double *__restrict_
     }
 }
 
+// Tiles of 256: four wavefronts share a tile pair, as the force's (k_sym_split in
+// pair.hip): the same 256 i, a 64-j block each, the i-side sums added in order through LDS.
+// Measured, us per product with its two elementwise launches, one wavefront a pair -> this:
+// N = 13,312 118 -> 90, 20,480 222 -> 182, 32,768 475 -> 453.
+template <bool SYM>
+__device__ __forceinline__ void hvp_split_block(const double *__restrict__ q, const double *__restrict__ w, int n,
+                                                int npad, double e, double *__restrict__ part, int a, int b,
+                                                double (&lds)[4][2][kWave * kSymIpl])
+{
+    constexpr int TILE = kWave * kSymIpl;
+    static_assert(TILE == 4 * kWave, "a 64-j block for each of four wavefronts");
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int i0 = a * TILE + lane, j0 = b * TILE + wave * kWave;
+    double x[kSymIpl], y[kSymIpl], wx[kSymIpl], wy[kSymIpl];
+#pragma unroll
+    for (int k = 0; k < kSymIpl; ++k) {
+        const int i = i0 + k * kWave;
+        x[k] = q[i];
+        y[k] = q[npad + i];
+        wx[k] = w[i];
+        wy[k] = w[npad + i];
+    }
+    auto load = [&](int, double &xj, double &yj, double &wxj, double &wyj) {
+        xj = q[j0 + lane];
+        yj = q[npad + j0 + lane];
+        wxj = w[j0 + lane];
+        wyj = w[npad + j0 + lane];
+    };
+    auto jsum = [&](int, int m, AccF64 (&sj)[2]) {
+        part[(size_t)(2 * a) * npad + j0 + m] = sj[0].get();
+        part[(size_t)(2 * a + 1) * npad + j0 + m] = sj[1].get();
+    };
+    AccF64 acc[2][kSymIpl];
+    if ((b + 1) * TILE > n)  // a j tile with pads: one reciprocal a pair
+        sym_tile_hvp<kWave, SYM, false>(x, y, wx, wy, e, lane, load, jsum, acc);
+    else
+        sym_tile_hvp<kWave, SYM, true>(x, y, wx, wy, e, lane, load, jsum, acc);
+#pragma unroll
+    for (int k = 0; k < kSymIpl; ++k)
+#pragma unroll
+        for (int d = 0; d < 2; ++d) lds[wave][d][lane + k * kWave] = acc[d][k].get();
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+        const int i = threadIdx.x;
+        part[(size_t)(2 * b + d) * npad + a * TILE + i] =
+            ((lds[0][d][i] + lds[1][d][i]) + lds[2][d][i]) + lds[3][d][i];
+    }
+}
+
+__global__ __launch_bounds__(4 * kWave) void k_hvp_split(const double *__restrict__ q, const double *__restrict__ w,
+                                                         int n, int npad, int ntile, double e,
+                                                         double *__restrict__ part)
+{
+    __shared__ double lds[4][2][kWave * kSymIpl];
+    const int t = (int)blockIdx.x, noff = ntile * (ntile - 1) / 2;
+    if (t < noff) {
+        int a, b;
+        sym_tile_pair(t, ntile, a, b);
+        hvp_split_block<true>(q, w, n, npad, e, part, a, b, lds);
+    } else {
+        hvp_split_block<false>(q, w, n, npad, e, part, t - noff, t - noff, lds);
+    }
+}
+
 // PREP_COPY64: the symmetric product's padded FP64 rows (positions to ops, vector to wops).
 enum Prep { PREP_NONE = 0, PREP_CAST32 = 1, PREP_HALF32 = 2, PREP_SINCOS64 = 3, PREP_COPY64 = 4 };
 
-// Elementwise: hw = pref * (sum of the product partials, fixed order); out = hw;
-// lq -= h hw; lp += a lq; operands of the next product (positions pos, vector lp).
-// PREP_COPY64 (the symmetric product): the grid covers npad and writes the pads of
-// the operand rows too, positions at sym_pad (1e150) and the vector at 0.
+// One coordinate d of particle i: hw (the product); out = hw; lq -= h hw; lp += a lq;
+// operands of the next product (positions pos, vector lp).
+template <int PREP>
+__device__ __forceinline__ void adj_elem(int d, int i, int n, int npad, double hw, int flags, double h, double h2,
+                                         double a, double *__restrict__ lq, double *__restrict__ lp,
+                                         double *__restrict__ out, const double *__restrict__ pos,
+                                         void *__restrict__ ops, void *__restrict__ wops)
+{
+    const size_t k = (size_t)d * n + i;
+    if (flags & ADJ_OUT) out[k] = hw;
+    if (flags & ADJ_KICK) {
+        double l = lq[k] - h * hw;
+        if (flags & ADJ_KICK2) l -= h2 * hw;  // a second kick at the same positions
+        lq[k] = l;
+    }
+    if (flags & ADJ_DRIFT) lp[k] += a * lq[k];
+    if (flags & ADJ_PREPW) {
+        if (PREP == PREP_COPY64) static_cast<double *>(wops)[(size_t)d * npad + i] = lp[k];
+        else static_cast<float *>(wops)[(size_t)d * npad + i] = (float)lp[k];
+    }
+    if ((flags & ADJ_PREPQ) && PREP != PREP_NONE) {
+        const double qd = pos[k];
+        if (PREP == PREP_COPY64) {
+            static_cast<double *>(ops)[(size_t)d * npad + i] = qd;
+        } else if (PREP == PREP_CAST32) {
+            static_cast<float *>(ops)[(size_t)d * npad + i] = (float)qd;
+        } else if (PREP == PREP_HALF32) {
+            double sn, cn;
+            sincos64(0.5 * qd, &sn, &cn);
+            static_cast<float *>(ops)[i] = (float)(1.4142135623730951 * cn);
+            static_cast<float *>(ops)[npad + i] = (float)(1.4142135623730951 * sn);
+        } else {
+            double sn, cn;
+            sincos64(qd, &sn, &cn);
+            static_cast<double *>(ops)[i] = cn;
+            static_cast<double *>(ops)[npad + i] = sn;
+        }
+    }
+}
+
+// The pads of the symmetric product's operand rows (PREP_COPY64): positions at sym_pad,
+// the vector at 0.
+template <int PREP>
+__device__ __forceinline__ void adj_pad(int d, int i, int npad, int flags, void *__restrict__ ops,
+                                        void *__restrict__ wops)
+{
+    if constexpr (PREP == PREP_COPY64) {
+        if (i >= npad) return;
+        if (flags & ADJ_PREPQ) static_cast<double *>(ops)[(size_t)d * npad + i] = sym_pad<MD_GRAV2D, double>();
+        if (flags & ADJ_PREPW) static_cast<double *>(wops)[(size_t)d * npad + i] = 0.0;
+    }
+}
+
+// Elementwise, hw = pref * (sum of the product partials, fixed order).  PREP_COPY64 (the
+// symmetric product): the grid covers npad and writes the pads too.
 template <int D, int PREP>
 __global__ __launch_bounds__(256) void k_adj_update(const double *__restrict__ part, int S, int n, int npad,
                                                     double pref, int flags, double h, double h2, double a,
@@ -387,54 +503,37 @@ __global__ __launch_bounds__(256) void k_adj_update(const double *__restrict__ p
                                                     void *__restrict__ ops, void *__restrict__ wops)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) {
-        if constexpr (PREP == PREP_COPY64) {
-            if (i < npad) {
-#pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    if (flags & ADJ_PREPQ) static_cast<double *>(ops)[(size_t)d * npad + i] = sym_pad<MD_GRAV2D, double>();
-                    if (flags & ADJ_PREPW) static_cast<double *>(wops)[(size_t)d * npad + i] = 0.0;
-                }
-            }
-        }
-        return;
-    }
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        const size_t k = (size_t)d * n + i;
-        if (flags & (ADJ_OUT | ADJ_KICK)) {
-            const double hw = pref * slot_sum<D>(part, S, d, npad, i);
-            if (flags & ADJ_OUT) out[k] = hw;
-            if (flags & ADJ_KICK) {
-                double l = lq[k] - h * hw;
-                if (flags & ADJ_KICK2) l -= h2 * hw;  // a second kick at the same positions
-                lq[k] = l;
-            }
+        if (i >= n) {
+            adj_pad<PREP>(d, i, npad, flags, ops, wops);
+            continue;
         }
-        if (flags & ADJ_DRIFT) lp[k] += a * lq[k];
-        if (flags & ADJ_PREPW) {
-            if (PREP == PREP_COPY64) static_cast<double *>(wops)[(size_t)d * npad + i] = lp[k];
-            else static_cast<float *>(wops)[(size_t)d * npad + i] = (float)lp[k];
-        }
-        if ((flags & ADJ_PREPQ) && PREP != PREP_NONE) {
-            const double qd = pos[k];
-            if (PREP == PREP_COPY64) {
-                static_cast<double *>(ops)[(size_t)d * npad + i] = qd;
-            } else if (PREP == PREP_CAST32) {
-                static_cast<float *>(ops)[(size_t)d * npad + i] = (float)qd;
-            } else if (PREP == PREP_HALF32) {
-                double sn, cn;
-                sincos64(0.5 * qd, &sn, &cn);
-                static_cast<float *>(ops)[i] = (float)(1.4142135623730951 * cn);
-                static_cast<float *>(ops)[npad + i] = (float)(1.4142135623730951 * sn);
-            } else {
-                double sn, cn;
-                sincos64(qd, &sn, &cn);
-                static_cast<double *>(ops)[i] = cn;
-                static_cast<double *>(ops)[npad + i] = sn;
-            }
-        }
+        const double hw = flags & (ADJ_OUT | ADJ_KICK) ? pref * slot_sum<D>(part, S, d, npad, i) : 0.0;
+        adj_elem<PREP>(d, i, n, npad, hw, flags, h, h2, a, lq, lp, out, pos, ops, wops);
     }
+}
+
+// The same with the partials' sums split over the block's wavefronts (slot_block_sums in
+// device.h), 64 particles a block; the same sums bit for bit.
+template <int D, int PREP>
+__global__ __launch_bounds__(kSplitWaves *kWave) void k_adj_update_split(
+    const double *__restrict__ part, int S, int n, int npad, double pref, int flags, double h, double h2, double a,
+    double *__restrict__ lq, double *__restrict__ lp, double *__restrict__ out, const double *__restrict__ pos,
+    void *__restrict__ ops, void *__restrict__ wops)
+{
+    extern __shared__ double bs[];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int i = blockIdx.x * kWave + lane, ic = min(i, n - 1);
+    slot_block_sums<D, double>(part, S, npad, ic, wave, lane, bs);
+    __syncthreads();
+    if (wave >= D) return;
+    if (i >= n) {
+        adj_pad<PREP>(wave, i, npad, flags, ops, wops);
+        return;
+    }
+    const double hw = pref * slot_total<D, double>(part, S, npad, i, wave, lane, bs);
+    adj_elem<PREP>(wave, i, n, npad, hw, flags, h, h2, a, lq, lp, out, pos, ops, wops);
 }
 
 // The symmetric product (k_hvp_sym) where the force takes the symmetric form: 2D, FP64.
@@ -500,7 +599,7 @@ hipError_t launch_hvp_pair(md_ctx *c, const double *pos, const double *w)
             hipLaunchKernelGGL(k_hvp_sym<2>, dim3((unsigned)nblocks), dim3(2 * kWave), 0, c->stream, q, w, (int)c->n,
                                npad, ntile, c->eps, c->part);
         else
-            hipLaunchKernelGGL(k_hvp_sym<1>, dim3((unsigned)nblocks), dim3(kWave), 0, c->stream, q, w, (int)c->n,
+            hipLaunchKernelGGL(k_hvp_split, dim3((unsigned)nblocks), dim3(4 * kWave), 0, c->stream, q, w, (int)c->n,
                                npad, ntile, c->eps, c->part);
         const hipError_t err = hipGetLastError();
         timed_end(c, ts);
@@ -539,9 +638,17 @@ hipError_t launch_adj_update(md_ctx *c, int flags, double h, double h2, double a
     if (c->prec == MD_FP64 && !sym) flags &= ~ADJ_PREPW;
     if (pk == PREP_NONE) flags &= ~ADJ_PREPQ;
     const int npad = (int)c->npad, S = sym ? npad / sym_tile_n(c->model, c->prec, c->n) : c->tiles.jsplit;
-#define MD_ADJ(D_, P_)                                                                                          \
-    hipLaunchKernelGGL((k_adj_update<D_, P_>), grid, block, 0, c->stream, c->part, S, n, npad, pref, flags, h, h2, a, \
-                       lq, lp, out, pos, c->ops, c->wops)
+    const bool split = (flags & (ADJ_OUT | ADJ_KICK)) && slot_split(S, npad);
+    const dim3 sblock(kSplitWaves * kWave), sgrid((unsigned)((nthreads + kWave - 1) / kWave));
+#define MD_ADJ(D_, P_)                                                                                              \
+    do {                                                                                                            \
+        if (split)                                                                                                  \
+            hipLaunchKernelGGL((k_adj_update_split<D_, P_>), sgrid, sblock, slot_split_lds(S, D_), c->stream, c->part, \
+                               S, n, npad, pref, flags, h, h2, a, lq, lp, out, pos, c->ops, c->wops);               \
+        else                                                                                                        \
+            hipLaunchKernelGGL((k_adj_update<D_, P_>), grid, block, 0, c->stream, c->part, S, n, npad, pref, flags, h, \
+                               h2, a, lq, lp, out, pos, c->ops, c->wops);                                           \
+    } while (0)
     if (c->model == MD_GRAV2D) {
         if (pk == PREP_CAST32) MD_ADJ(2, PREP_CAST32);
         else if (pk == PREP_COPY64) MD_ADJ(2, PREP_COPY64);

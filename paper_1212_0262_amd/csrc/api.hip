@@ -602,9 +602,10 @@ int64_t pad_n(int64_t n) { return (n + kSymTile - 1) / kSymTile * kSymTile; }
 // Smaller tiles in the symmetric form of single systems below a size: a block's
 // tile pair is a serial unit of work (its wavefronts hold their i for the whole j
 // tile), so with few tile pairs the launch is as long as a block's round.  Tiles
-// of 256 (one wavefront a block) give 16 times the tile pairs of 1024-tiles at a
-// sixteenth of the work each, tiles of 512 (two wavefronts) four times.  Measured
-// md_step, us per step (MI355X), 256- / 512- / 1024-tiles where measured:
+// of 256 give 16 times the tile pairs of 1024-tiles at a sixteenth of the work
+// each (shared by up to four wavefronts: k_sym_split in pair.hip), tiles of 512 (two
+// wavefronts) four times.  Measured md_step, us per step (MI355X), 256- (one wavefront a
+// pair) / 512- / 1024-tiles where measured:
 //   2D mixed: N = 32,768 419 / 480 / 562; 49,152 842 / 1005 / 933; 65,536 1434 /
 //     1613 / 1509; 98,304 3195 / 3218 / 3174;
 //   2D FP64: 32,768 788 / 821 / 931; 65,536 2930 / 2943 / 2978; 98,304 6639 / 6376 /

@@ -314,4 +314,52 @@ __device__ __forceinline__ void slot_sums(const SlotT *__restrict__ part, int S,
         for (int d = 0; d < D; ++d) s[d] += (double)part[(size_t)(b * D + d) * npad + i];
 }
 
+// slot_sums in the same order by the four wavefronts of a block that takes 64 particles
+// (lane = particle): wavefront w forms the tree sums of slot blocks w, w + 4, ... into
+// bs[block][d][lane] (LDS); after a barrier slot_total adds one coordinate's in order.
+// For few particles with many slots: a thread per particle leaves most CUs idle
+// (n = 20,480: 80 blocks) while each thread waits for its loads.
+constexpr int kSplitWaves = 4;
+
+template <int D, typename SlotT>
+__device__ __forceinline__ void slot_block_sums(const SlotT *__restrict__ part, int S, int npad, int i, int wave,
+                                                int lane, double *__restrict__ bs)
+{
+    const int nblk = S / kSlotBlock;
+    for (int b = wave; b < nblk; b += 2 * kSplitWaves) {
+        SlotT v[2][D][kSlotBlock];
+        const bool two = b + kSplitWaves < nblk;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int u = 0; u < kSlotBlock; ++u)
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    const int s = (h && two ? b + kSplitWaves : b) * kSlotBlock + u;
+                    v[h][d][u] = part[(size_t)(s * D + d) * npad + i];
+                }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+                if (!h || two) bs[((b + h * kSplitWaves) * D + d) * kWave + lane] = tree8(v[h][d]);
+    }
+}
+
+template <int D, typename SlotT>
+__device__ __forceinline__ double slot_total(const SlotT *__restrict__ part, int S, int npad, int i, int d, int lane,
+                                             const double *__restrict__ bs)
+{
+    const int nblk = S / kSlotBlock;
+    double s = 0.0;
+    for (int b = 0; b < nblk; ++b) s += bs[(b * D + d) * kWave + lane];
+    for (int b = nblk * kSlotBlock; b < S; ++b) s += (double)part[(size_t)(b * D + d) * npad + i];
+    return s;
+}
+
+// Systems whose updates take the split sums: S slots of a system padded to npad.
+constexpr int64_t kSplitMaxN = 65536;
+inline bool slot_split(int S, int64_t npad) { return S >= 2 * kSlotBlock && npad <= kSplitMaxN; }
+inline size_t slot_split_lds(int S, int d) { return (size_t)(S / kSlotBlock) * d * kWave * sizeof(double); }
+
 }  // namespace md

@@ -60,10 +60,12 @@ constexpr int64_t kFusedAutoN2D = 6144; // ... and up to this n for 2D gravity
 constexpr int kSymTile = 1024;          // particles per tile of the symmetric form (4 waves x 64 x 4 i)
 constexpr int kBatchSymTile = 512;     // tiles of the ensembles' symmetric form (2 waves x 64 x 4 i)
 constexpr int kSymTileSmall = 512;      // ... for smaller n (2 waves x 64 x 4 i; sym_tile_n), and 256
-                                        // (1 wave) for smaller n still
+                                        // (shared by up to 4 waves) for smaller n still
 constexpr int64_t kSymMinN = 2048;      // the symmetric form needs two tiles at least
 constexpr int64_t kSymMaxN = 1 << 20;   // and at most 1024 tiles (its partial slots: 8 d n^2 / 1024 bytes)
-// MD_LAUNCH_AUTO takes the symmetric form from this n (measured crossovers)
+// MD_LAUNCH_AUTO takes the symmetric form from this n (measured crossovers).  Ring FP64,
+// us per force evaluation, staged / symmetric: N = 4096 16.2 / 17.4, 5120 25.0 / 18.8,
+// 7168 37.7 / 26.5, 10,240 57.6 / 40.5.
 inline int64_t sym_auto_n(int model, int prec)
 {
     if (model != MD_RING)

@@ -269,7 +269,7 @@ __device__ __forceinline__ void sym_block(const T *__restrict__ r0, const T *__r
 #pragma unroll
             for (int d = 0; d < D; ++d) jw64[wave][d][m] = sj[d].get();
             __syncthreads();
-            for (int x = threadIdx.x; x < D * kWave; x += W * kWave) {  // W = 1: a thread per (d, j) in turn
+            for (int x = threadIdx.x; x < D * kWave; x += W * kWave) {
                 const int d = x / kWave, mm = x & (kWave - 1);
                 double t = 0.0;
 #pragma unroll
@@ -328,6 +328,88 @@ __global__ __launch_bounds__(W * kWave) void k_sym(const T *__restrict__ r0, con
     }
 }
 
+// Tiles of 256 (small n, sym_tile_n in api.hip): NS wavefronts share a tile pair.  Each
+// holds the same 256 i and takes 4 / NS of the tile's 64-j blocks, so its j-side sums are
+// whole (written from registers) and its i-side sums are added over the wavefronts in
+// order through LDS.  At these n there are 2 to 32 tile pairs a SIMD, and with one
+// wavefront a pair (the first form) the last ones ran alone: N = 20,480 has 3240, 3.2 a
+// SIMD, and took the time of 5.  NS = 4 for FP64 sums; MD_MIXED NS = 2, each wavefront one
+// 128-j run of its FP32 partials, so the same sums bit for bit; MD_MIXED_KAHAN NS = 1 (a
+// compensated sum's terms are rounded against its state: split, the force moves by 1e-9).
+// Measured, us per force evaluation with its update, one wavefront a pair -> this: 2D FP64
+// N = 13,312 69 -> 54, 16,384 84 -> 72, 20,480 123 -> 105, 32,768 256 -> 248; 2D mixed
+// 16,384 51 -> 44, 20,480 73 -> 63; Ring FP64 13,312 80 -> 59, 20,480 142 -> 118, 32,768
+// 308 -> 287; Ring mixed 16,384 64 -> 52.
+template <typename A>
+constexpr int kSymSplit = std::is_same_v<A, AccKahan> ? 1 : kJW32<A> ? 2 : 4;
+
+template <int MODEL, typename T, typename A, bool SYM, int NS>
+__device__ __forceinline__ void sym_split_block(const T *__restrict__ r0, const T *__restrict__ r1, int n, int npad,
+                                                T e, sym_slot_t<A> *__restrict__ part, int a, int b,
+                                                double (&lds)[NS][MODEL == MD_GRAV2D ? 2 : 1][kWave * kSymIpl])
+{
+    constexpr int D = MODEL == MD_GRAV2D ? 2 : 1;
+    constexpr int TILE = kWave * kSymIpl, NB = TILE / kWave / NS;  // 64-j blocks a wavefront
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int i0 = a * TILE + lane, j0 = b * TILE + wave * NB * kWave;
+    T u0[kSymIpl], u1[kSymIpl];
+    A acc[D][kSymIpl];
+#pragma unroll
+    for (int k = 0; k < kSymIpl; ++k) {
+        u0[k] = r0[i0 + k * kWave];
+        u1[k] = r1[i0 + k * kWave];
+    }
+    auto load = [&](int blk, T &v0, T &v1) {
+        v0 = r0[j0 + blk * kWave + lane];
+        v1 = r1[j0 + blk * kWave + lane];
+    };
+    auto jsum = [&](int blk, int m, A (&sj)[D]) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) part[(size_t)(D * a + d) * npad + j0 + blk * kWave + m] = (sym_slot_t<A>)sj[d].get();
+    };
+    constexpr bool kShare = MODEL == MD_GRAV2D && sizeof(T) == 8;  // as sym_block
+    if (!kShare || (b + 1) * TILE > n) sym_tile<MODEL, T, A, SYM, false>(u0, u1, e, lane, NB, load, jsum, acc);
+    else sym_tile<MODEL, T, A, SYM, kShare>(u0, u1, e, lane, NB, load, jsum, acc);
+    if constexpr (NS == 1) {
+#pragma unroll
+        for (int k = 0; k < kSymIpl; ++k)
+#pragma unroll
+            for (int d = 0; d < D; ++d)
+                part[(size_t)(D * b + d) * npad + i0 + k * kWave] = (sym_slot_t<A>)acc[d][k].get();
+    } else {
+#pragma unroll
+        for (int k = 0; k < kSymIpl; ++k)
+#pragma unroll
+            for (int d = 0; d < D; ++d) lds[wave][d][lane + k * kWave] = acc[d][k].get();
+        __syncthreads();
+#pragma unroll
+        for (int x = threadIdx.x; x < D * TILE; x += NS * kWave) {
+            const int d = x / TILE, i = x % TILE;
+            double t = lds[0][d][i];
+#pragma unroll
+            for (int w = 1; w < NS; ++w) t += lds[w][d][i];
+            part[(size_t)(D * b + d) * npad + a * TILE + i] = (sym_slot_t<A>)t;
+        }
+    }
+}
+
+template <int MODEL, typename T, typename A>
+__global__ __launch_bounds__(kSymSplit<A> *kWave) void k_sym_split(const T *__restrict__ r0, const T *__restrict__ r1,
+                                                                   int n, int npad, int ntile, T e,
+                                                                   sym_slot_t<A> *__restrict__ part)
+{
+    constexpr int NS = kSymSplit<A>;
+    __shared__ double lds[NS][MODEL == MD_GRAV2D ? 2 : 1][kWave * kSymIpl];
+    const int t = (int)blockIdx.x, noff = ntile * (ntile - 1) / 2;
+    if (t < noff) {
+        int a, b;
+        sym_tile_pair(t, ntile, a, b);
+        sym_split_block<MODEL, T, A, true, NS>(r0, r1, n, npad, e, part, a, b, lds);
+    } else {
+        sym_split_block<MODEL, T, A, false, NS>(r0, r1, n, npad, e, part, t - noff, t - noff, lds);
+    }
+}
+
 // The pads (particles n .. npad - 1) hold sym_pad's operands: every operand refresh
 // (UPD_PREP in k_update) writes them, so they are in place before any pair launch
 // of the same call, also inside a captured graph.
@@ -347,8 +429,8 @@ hipError_t sym_launch(md_ctx *c)
         hipLaunchKernelGGL((k_sym<MODEL, T, A, 2>), dim3((unsigned)nblk), dim3(2 * kWave), 0, c->stream, ops,
                            ops + npad, (int)c->n, npad, ntile, e, slots);
     else
-        hipLaunchKernelGGL((k_sym<MODEL, T, A, 1>), dim3((unsigned)nblk), dim3(kWave), 0, c->stream, ops,
-                           ops + npad, (int)c->n, npad, ntile, e, slots);
+        hipLaunchKernelGGL((k_sym_split<MODEL, T, A>), dim3((unsigned)nblk), dim3(kSymSplit<A> * kWave), 0, c->stream,
+                           ops, ops + npad, (int)c->n, npad, ntile, e, slots);
     const hipError_t err = hipGetLastError();
     timed_end(c, ts);
     return err;
@@ -461,6 +543,34 @@ __global__ __launch_bounds__(256) void k_update(const SlotT *__restrict__ part, 
         }
         stage_elem<PREP>(d, i, n, npad, fd, flags, f, p, q, ops, kick1, kick2, drift, snap);
     }
+}
+
+// k_update with the slot sums split over a block's wavefronts (slot_block_sums in
+// device.h): blocks of 64 particles, wavefront d then runs the stage of coordinate d.
+// The same sums bit for bit.  Measured, a 2D FP64 update in a step at N = 20,480 (80 slots)
+// and 32,768 (128): 9.8 -> 6.8 and 14.1 -> 11.5 us.
+template <int D, int PREP, typename SlotT>
+__global__ __launch_bounds__(kSplitWaves *kWave) void k_update_split(const SlotT *__restrict__ part, int S, int n,
+                                                                     int npad, double pref, double *__restrict__ f,
+                                                                     double *__restrict__ p, double *__restrict__ q,
+                                                                     void *__restrict__ ops, double kick1,
+                                                                     double kick2, double drift, int flags,
+                                                                     double *__restrict__ snap)
+{
+    extern __shared__ double bs[];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int i = blockIdx.x * kWave + lane, ic = min(i, n - 1);
+    const size_t k = (size_t)(wave < D ? wave : 0) * n + ic;
+    const double qd = stage_reads_q(flags) ? q[k] : 0.0, pd = stage_reads_p(flags) ? p[k] : 0.0;
+    slot_block_sums<D, SlotT>(part, S, npad, ic, wave, lane, bs);
+    __syncthreads();
+    if (wave >= D) return;
+    if (i >= n) {  // with UPD_PREP the grid covers the pads too
+        if (wave == 0 && (flags & UPD_PREP) && i < npad) stage_pad<PREP>(i, npad, ops);
+        return;
+    }
+    const double fd = pref * slot_total<D, SlotT>(part, S, npad, i, wave, lane, bs);
+    stage_elem_v<PREP>(wave, i, n, npad, fd, qd, pd, flags, f, p, q, ops, kick1, kick2, drift, snap);
 }
 
 // k_update for VW consecutive particles per thread (the symmetric form's slots,
@@ -809,9 +919,18 @@ hipError_t update(md_ctx *c, int flags, double kick1, double kick2, double drift
     const int vw = slots32 ? 4 : 2;
     const bool vec = sym && (flags & UPD_F_FROM_PART) && npad / vw / kWave >= 1024;
     const dim3 vblock(kWave), vgrid((unsigned)((nthreads + vw * kWave - 1) / (vw * kWave)));
+    const bool split = (flags & UPD_F_FROM_PART) && !vec && slot_split(S, npad);
+    const dim3 sblock(kSplitWaves * kWave), sgrid((unsigned)((nthreads + kWave - 1) / kWave));
 #define MD_UPD(D_, P_)                                                                                              \
     do {                                                                                                            \
-        if (vec && slots32)                                                                                         \
+        if (split && slots32)                                                                                       \
+            hipLaunchKernelGGL((k_update_split<D_, P_, float>), sgrid, sblock, slot_split_lds(S, D_), c->stream,    \
+                               reinterpret_cast<const float *>(c->part), S, n, npad, pref, f, p, q, ops, kick1, kick2, \
+                               drift, flags, snap);                                                                 \
+        else if (split)                                                                                             \
+            hipLaunchKernelGGL((k_update_split<D_, P_, double>), sgrid, sblock, slot_split_lds(S, D_), c->stream,   \
+                               c->part, S, n, npad, pref, f, p, q, ops, kick1, kick2, drift, flags, snap);          \
+        else if (vec && slots32)                                                                                         \
             hipLaunchKernelGGL((k_update_vec<D_, P_, float, 4>), vgrid, vblock, 0, c->stream,                       \
                                reinterpret_cast<const float *>(c->part), S, n, npad, pref, f, p, q, ops, kick1, kick2, \
                                drift, flags, snap);                                                                 \

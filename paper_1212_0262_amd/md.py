@@ -28,7 +28,7 @@ LAUNCH_AUTO, LAUNCH_STAGED, LAUNCH_FUSED, LAUNCH_SYMMETRIC = 0, 1, 2, 3
 SYMMETRIC_AUTO_N = 13312  # MD_SYMMETRIC_AUTO_N: LAUNCH_AUTO takes the symmetric 2D form from this n (MIXED, FP64)
 SYMMETRIC_AUTO_N_COMP = 15360    # MD_SYMMETRIC_AUTO_N_COMP: the same for 2D with the compensated forms
 SYMMETRIC_AUTO_N_RING = 13312    # MD_SYMMETRIC_AUTO_N_RING: the same for the Ring with the FP32 forms
-SYMMETRIC_AUTO_N_RING64 = 10240  # MD_SYMMETRIC_AUTO_N_RING64: the same for the Ring with FP64
+SYMMETRIC_AUTO_N_RING64 = 4608   # MD_SYMMETRIC_AUTO_N_RING64: the same for the Ring with FP64
 # MD_EPS_*: the softening each pair model and precision accepts (md_init)
 EPS_MIN_2D_FP64, EPS_MAX_2D_FP64 = 1e-75, 1e75
 EPS_MIN_2D_FP32 = 1e-30

@@ -509,3 +509,25 @@ def test_ring_fp32_symmetric_coincident_angles():
     for prec in (md.MIXED, md.MIXED_KAHAN):
         fs = _force(q, md.LAUNCH_SYMMETRIC, prec, RING, eps)
         check(f"duplicated angles prec={prec}", rel_inf(fs[:, rows], fo), force_tol(RING, prec, n))
+
+
+# ------------------------------------------------ tiles of 256, split sums --
+
+@pytest.mark.parametrize("model,eps", [(GRAV2D, 1e-3), (RING, 1e-2)])
+@pytest.mark.parametrize("prec", [md.FP64, md.MIXED, md.MIXED_KAHAN, md.MIXED_PAIRF64])
+@pytest.mark.parametrize("n", [2048, 2305, 4863, 7168, 65_536])
+def test_split_tiles_and_sums(model, eps, prec, n):
+    """Tiles of 256 shared by the wavefronts, and the slot sums split over a block (2 to 64
+    blocks of slots, remainders, pads), on sampled rows against the oracle."""
+    q, _ = inputs.grav2d_disk(n, seed=n) if model == GRAV2D else inputs.ring_waterbag(n, seed=n)
+    rows = np.unique(np.concatenate([[0, 63, 64, 255, 256, n - 1], np.random.default_rng(n).integers(0, n, 26)]))
+    fo = oracle.force_rows(model, q, rows, eps)
+    ctx = md.md_init(model, prec, n, eps)
+    md.md_set_launch(ctx, md.LAUNCH_SYMMETRIC)
+    f, g = torch.empty_like(dev(q)), torch.empty_like(dev(q))
+    md.md_force(ctx, dev(q), f)
+    md.md_force(ctx, dev(q), g)
+    ctx.close()
+    assert torch.equal(f, g)
+    err = np.abs(host(f)[:, rows] - fo).max() / np.abs(fo).max()
+    assert err < force_tol(model, prec, n, run=256), err
