@@ -437,6 +437,143 @@ __global__ __launch_bounds__(4 * kWave) void k_hvp_split(const double *__restric
     }
 }
 
+// --------------------------------------------------------- fused small-N product --
+
+// FP64, small n (where md_step takes its fused form): a whole product, and in the reverse
+// sweep its kick and drift, in one launch.  A block takes 8 particles i and every j in 64
+// ranges: wavefront w's lane group g (8 lanes, one per i) the range b = 8 w + g of jlen j,
+// in chunks of kHvpChunk j that the wavefront loads coalesced into its own LDS window (the
+// Ring's sincos of each j as it is loaded); the ranges' sums meet by lane exchanges, then
+// over the wavefronts in LDS, and 8 d lanes apply the product to the block's particles.
+// At these n the separate launches (operands, pair kernel, elementwise kernel) and the pair
+// kernel's wave-uniform loads, a memory round trip for every few j, took most of the time.
+// Measured, us, before -> after: md_hvp 2D n = 500 12.3 -> 5.3, 2000 13.2 -> 6.6; md_step_vjp
+// of four steps (force and recomputed steps included) 2D n = 500 235 -> 117, 2000 271 -> 176,
+// Ring n = 500 194 -> 127, 2000 235 -> 192.
+//   pos:    positions, rows of n;  w_in: the vector, rows of w_stride (another block's
+//           particles too: never an array this launch writes);
+//   out:    the product (ADJ_OUT), rows of n;  lq: kicked in place (ADJ_KICK, ADJ_KICK2);
+//   w_out:  the vector after the drift (ADJ_DRIFT) or as it was, rows of o_stride.
+constexpr int kHvpChunk = 16, kHvpWaves = 8, kHvpI = 8;
+
+template <int MODEL>
+__global__ __launch_bounds__(kHvpWaves *kWave) void k_hvp_fused(const double *__restrict__ pos,
+                                                                const double *__restrict__ w_in, double *__restrict__ lq,
+                                                                int n, int w_stride, int jlen, int flags, int o_stride,
+                                                                double *__restrict__ w_out, double *__restrict__ out,
+                                                                double e, double pref, double h, double h2, double a)
+{
+    constexpr int D = MODEL == MD_GRAV2D ? 2 : 1, R = D + 2, G = kWave / kHvpI, CW = kHvpChunk + 1;
+    static_assert(G * kHvpChunk == 2 * kWave, "two j of a chunk per lane");
+    __shared__ double win[kHvpWaves][R][G * CW];  // groups one element apart: no bank conflicts
+    __shared__ double red[kHvpWaves][D][kHvpI];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int g = lane / kHvpI, il = lane % kHvpI;
+    // rows of the operands of particle j: (x, y, wx, wy) or (cos, sin, w)
+    auto load = [&](int j, double (&v)[R]) {
+        v[0] = pos[j];
+        if constexpr (D == 2) v[1] = pos[n + j];
+        v[R - D] = w_in[j];
+        if constexpr (D == 2) v[3] = w_in[w_stride + j];
+    };
+    auto operands = [&](double (&v)[R]) {
+        if constexpr (D == 1) {
+            double s, c;
+            sincos64(v[0], &s, &c);
+            v[0] = c;
+            v[1] = s;
+        }
+    };
+    const int i0 = (int)blockIdx.x * kHvpI;
+    // the particle this thread updates at the end: coordinate ud
+    const int ud = (int)threadIdx.x / kHvpI, ui = i0 + (int)threadIdx.x % kHvpI;
+    const bool owner = (int)threadIdx.x < D * kHvpI && ui < n;
+    const double x_pre = owner && (flags & ADJ_KICK) ? lq[(size_t)ud * n + ui] : 0.0;
+    const double w_pre = owner && w_out ? w_in[(size_t)ud * w_stride + ui] : 0.0;
+    double own[R];
+    load(min(i0 + il, n - 1), own);
+    const int j0 = (wave * G + g) * jlen;
+    const int len = max(0, min(n - j0, jlen));                // this lane's range
+    const int wlen = max(0, min(n - wave * G * jlen, jlen));  // the wavefront's longest
+    double v[2][R];
+    auto fetch = [&](int t) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int x = m * kWave + lane, c = x % kHvpChunk;
+            const int j = (wave * G + x / kHvpChunk) * jlen + t + c;
+            load(t + c < jlen && j < n ? j : 0, v[m]);
+        }
+    };
+    if (wlen > 0) fetch(0);
+    operands(own);
+    AccF64 ax, ay;
+    for (int t = 0; t < wlen; t += kHvpChunk) {
+        wave_sync();  // the previous chunk's reads are done
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int x = m * kWave + lane;
+            operands(v[m]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) win[wave][r][x / kHvpChunk * CW + x % kHvpChunk] = v[m][r];
+        }
+        wave_sync();
+        if (t + kHvpChunk < wlen) fetch(t + kHvpChunk);
+        const double *r0 = &win[wave][0][g * CW], *r1 = &win[wave][1][g * CW], *r2 = &win[wave][2][g * CW];
+        const double *r3 = &win[wave][R - 1][g * CW];
+        auto one = [&](int u) {
+            if constexpr (D == 2) hvp_2d(own[0], own[1], own[2], own[3], r0[u], r1[u], r2[u], r3[u], e, ax, ay);
+            else hvp_ring(own[0], own[1], own[2], r0[u], r1[u], r2[u], e, ax);
+        };
+        auto four = [&](int u) {
+            if constexpr (D == 2) {
+                const double xq[4] = {r0[u], r0[u + 1], r0[u + 2], r0[u + 3]};
+                const double yq[4] = {r1[u], r1[u + 1], r1[u + 2], r1[u + 3]};
+                const double wxq[4] = {r2[u], r2[u + 1], r2[u + 2], r2[u + 3]};
+                const double wyq[4] = {r3[u], r3[u + 1], r3[u + 2], r3[u + 3]};
+                hvp_2d_four(own[0], own[1], own[2], own[3], xq, yq, wxq, wyq, e, ax, ay);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) one(u + k);
+            }
+        };
+        if (t + kHvpChunk <= len) {
+#pragma unroll
+            for (int u = 0; u < kHvpChunk; u += 4) four(u);
+        } else {
+            int u = 0;
+            for (; u + 4 <= len - t; u += 4) four(u);
+            for (; u < len - t; ++u) one(u);
+        }
+    }
+    // over the 8 groups: lanes il + 8 g; then lanes 0 .. 7 hold x (and 32 .. 39 y)
+    double s = D == 2 ? swap32_sum(ax.get(), ay.get()) : swap32_sum(ax.get(), ax.get());
+    s = swap16_sum(s, s);
+    s += dpp_move<0x128>(s);  // row_ror:8
+    if (lane % 32 < kHvpI && lane / 32 < D) red[wave][lane / 32][il] = s;
+    __syncthreads();
+    if (!owner) return;
+    double hw = 0.0;
+#pragma unroll
+    for (int w = 0; w < kHvpWaves; ++w) hw += red[w][ud][threadIdx.x % kHvpI];
+    hw *= pref;
+    const size_t k = (size_t)ud * n + ui;
+    if (flags & ADJ_OUT) out[k] = hw;
+    double x = x_pre - h * hw;
+    if (flags & ADJ_KICK2) x -= h2 * hw;
+    if (flags & ADJ_KICK) lq[k] = x;
+    if (w_out) w_out[(size_t)ud * o_stride + ui] = flags & ADJ_DRIFT ? w_pre + a * x : w_pre;
+}
+
+// out = in for len values, twice (the state a sweep starts from: one launch).
+__global__ __launch_bounds__(256) void k_copy2(const double *__restrict__ a, double *__restrict__ a_out,
+                                               const double *__restrict__ b, double *__restrict__ b_out, int len)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= len) return;
+    a_out[i] = a[i];
+    b_out[i] = b[i];
+}
+
 // PREP_COPY64: the symmetric product's padded FP64 rows (positions to ops, vector to wops).
 enum Prep { PREP_NONE = 0, PREP_CAST32 = 1, PREP_HALF32 = 2, PREP_SINCOS64 = 3, PREP_COPY64 = 4 };
 
@@ -548,6 +685,13 @@ int prep_kind(const md_ctx *c)
     return c->prec == MD_FP64 ? PREP_SINCOS64 : PREP_HALF32;
 }
 
+// Hessian prefactors: 2/N (2D); 1/(2 sqrt2 N) (Ring, FP64 terms); 1/N (Ring, half-angle FP32 terms)
+double hvp_prefactor(const md_ctx *c)
+{
+    const double n = (double)c->n;
+    return c->model == MD_GRAV2D ? 2.0 / n : c->prec == MD_FP64 ? 1.0 / (2.0 * 1.4142135623730951 * n) : 1.0 / n;
+}
+
 template <typename T, typename A>
 hipError_t hvp_launch(md_ctx *c, const void *qsrc, const void *wsrc, dim3 grid, dim3 block, int jlen)
 {
@@ -581,6 +725,37 @@ hipError_t hvp_launch(md_ctx *c, const void *qsrc, const void *wsrc, dim3 grid, 
 }
 
 }  // namespace
+
+// The fused product applies: FP64, a single system that takes the fused form, small n.
+bool hvp_fused(const md_ctx *c)
+{
+    return c->prec == MD_FP64 && c->n <= kFusedHvpN && !c->batch && c->model != MD_HMF && launch_form(c) == MD_LAUNCH_FUSED;
+}
+
+hipError_t launch_hvp_fused(md_ctx *c, const double *pos, const double *w_in, int w_stride, int flags, double h,
+                            double h2, double a, double *lq, double *w_out, int o_stride, double *out)
+{
+    const int n = (int)c->n;
+    const int jlen = (n + kHvpWaves * 8 - 1) / (kHvpWaves * 8);
+    const dim3 grid((unsigned)((n + kHvpI - 1) / kHvpI)), block(kHvpWaves * kWave);
+    const int ts = timed_begin(c, "k_hvp_fused");
+    if (c->model == MD_GRAV2D)
+        hipLaunchKernelGGL(k_hvp_fused<MD_GRAV2D>, grid, block, 0, c->stream, pos, w_in, lq, n, w_stride, jlen, flags,
+                           o_stride, w_out, out, c->eps, hvp_prefactor(c), h, h2, a);
+    else
+        hipLaunchKernelGGL(k_hvp_fused<MD_RING>, grid, block, 0, c->stream, pos, w_in, lq, n, w_stride, jlen, flags,
+                           o_stride, w_out, out, 1.0 + c->eps, hvp_prefactor(c), h, h2, a);
+    const hipError_t err = hipGetLastError();
+    timed_end(c, ts);
+    return err;
+}
+
+hipError_t launch_copy2(md_ctx *c, const double *a, double *a_out, const double *b, double *b_out, int64_t len)
+{
+    hipLaunchKernelGGL(k_copy2, dim3((unsigned)((len + 255) / 256)), dim3(256), 0, c->stream, a, a_out, b, b_out,
+                       (int)len);
+    return hipGetLastError();
+}
 
 // Product partials of H(pos) w into c->part.  FP64 2D reads pos and w directly;
 // every other form reads the operands prepared by launch_adj_update (ADJ_PREPQ,
@@ -630,13 +805,11 @@ hipError_t launch_adj_update(md_ctx *c, int flags, double h, double h2, double a
     const bool sym = hvp_sym(c);
     const int nthreads = sym && (flags & (ADJ_PREPQ | ADJ_PREPW)) ? (int)c->npad : n;  // the pads too
     const dim3 block(256), grid((unsigned)((nthreads + 255) / 256));
-    // Hessian prefactors: 2/N (2D); 1/(2 sqrt2 N) (Ring, FP64 terms); 1/N (Ring, half-angle FP32 terms)
-    const double pref = c->model == MD_GRAV2D ? 2.0 / (double)n
-                        : c->prec == MD_FP64  ? 1.0 / (2.0 * 1.4142135623730951 * (double)n)
-                                              : 1.0 / (double)n;
+    const double pref = hvp_prefactor(c);
     const int pk = prep_kind(c);
     if (c->prec == MD_FP64 && !sym) flags &= ~ADJ_PREPW;
     if (pk == PREP_NONE) flags &= ~ADJ_PREPQ;
+    if (!flags) return hipSuccess;  // no operands to prepare
     const int npad = (int)c->npad, S = sym ? npad / sym_tile_n(c->model, c->prec, c->n) : c->tiles.jsplit;
     const bool split = (flags & (ADJ_OUT | ADJ_KICK)) && slot_split(S, npad);
     const dim3 sblock(kSplitWaves * kWave), sgrid((unsigned)((nthreads + kWave - 1) / kWave));

@@ -219,6 +219,24 @@ int form_of(const md_ctx *c)
     return MD_LAUNCH_STAGED;
 }
 
+// f = force(q), Ring and 2D, single systems and ensembles.  The fused form: the operands,
+// then pair sums and combine in one launch (the staged form's sums bit for bit).
+int force_pairs(md_ctx *c, double *q, double *f)
+{
+    if (form_of(c) == MD_LAUNCH_FUSED && c->n <= kFusedForceN) {
+        MD_TRY(launch_update_fused(c, UPD_PREP, 0.0, 0.0, 0.0, q, nullptr, nullptr, c->fops[0], nullptr),
+               "force: operands");
+        MD_TRY(launch_fused(c, UPD_F_FROM_PART | UPD_STORE_F, 0.0, 0.0, 0.0, nullptr, nullptr, f, c->fops[0],
+                            c->fops[1], nullptr),
+               "force: fused");
+        return MD_OK;
+    }
+    MD_TRY(update_(c, UPD_PREP, 0.0, 0.0, 0.0, q, nullptr, nullptr), "force: operands");
+    MD_TRY(pair_(c, q), "force: pair kernel");
+    MD_TRY(update_(c, UPD_F_FROM_PART | UPD_STORE_F, 0.0, 0.0, 0.0, q, nullptr, f), "force: combine");
+    return MD_OK;
+}
+
 int step_pairs(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nsteps, double *snap = nullptr,
                size_t snap_stride = 0)
 {
@@ -280,6 +298,20 @@ int reverse_pairs(md_ctx *c, const double *q0, const double *P, size_t slot, dou
     double B0, B1, D0, D1;
     yoshida(&B0, &B1, &D0, &D1);
     auto pos = [&](int64_t m) -> const double * { return m == 0 ? q0 : P + (size_t)(m - 1) * slot; };
+    if (hvp_fused(c)) {  // a launch per product; the vector alternates between two buffers
+        double *const buf[2] = {static_cast<double *>(c->fops[0]), static_cast<double *>(c->fops[1])};
+        const int n = (int)c->n, npad = (int)c->npad;
+        const double h[3] = {B0 * dt, B1 * dt, B1 * dt}, a[3] = {D0 * dt, D0 * dt, D1 * dt};  // by m mod 3
+        for (int64_t m = 3 * nsteps, k = 0; m >= 0; --m, ++k) {
+            const int r = (int)(m % 3);
+            const bool two = r == 0 && m > 0 && m < 3 * nsteps;  // the kicks of two steps at one position
+            const int flags = ADJ_KICK | (two ? ADJ_KICK2 : 0) | (m > 0 ? ADJ_DRIFT : 0);
+            MD_TRY(launch_hvp_fused(c, pos(m), k == 0 ? lp : buf[(k - 1) & 1], k == 0 ? n : npad, flags, h[r], h[r],
+                                    a[r], lq, m > 0 ? buf[k & 1] : lp, m > 0 ? npad : n, nullptr),
+                   "vjp: product");
+        }
+        return MD_OK;
+    }
     // pending product at P_3n, kick weight B0 dt
     const int prep = ADJ_PREPQ | ADJ_PREPW;
     MD_TRY(launch_adj_update(c, prep, 0.0, 0.0, 0.0, lq, lp, nullptr, pos(3 * nsteps)), "vjp: operands");
@@ -389,8 +421,7 @@ int step_vjp(md_ctx *c, const double *q0, const double *p0, double dt, int64_t n
 {
     const size_t len = (size_t)dims(c->model) * c->n, slot = vjp_slot(c);
     double *qw = stage, *pw = stage + slot, *fw = stage + 2 * slot, *P = stage + 3 * slot;
-    MD_TRY(hipMemcpyAsync(qw, q0, len * sizeof(double), hipMemcpyDeviceToDevice, c->stream), "vjp: copy q");
-    MD_TRY(hipMemcpyAsync(pw, p0, len * sizeof(double), hipMemcpyDeviceToDevice, c->stream), "vjp: copy p");
+    MD_TRY(launch_copy2(c, q0, qw, p0, pw, (int64_t)len), "vjp: copy q, p");
     int st;
     if (c->model == MD_HMF) {
         MD_TRY(hmf_force(c, qw, fw), "vjp: force");
@@ -398,9 +429,8 @@ int step_vjp(md_ctx *c, const double *q0, const double *p0, double dt, int64_t n
         if (st != MD_OK) return st;
         return reverse_hmf(c, q0, P, slot, dt, nsteps, lq, lp);
     }
-    MD_TRY(update_(c, UPD_PREP, 0.0, 0.0, 0.0, qw, nullptr, nullptr), "vjp: operands");
-    MD_TRY(pair_(c, qw), "vjp: pair kernel");
-    MD_TRY(update_(c, UPD_F_FROM_PART | UPD_STORE_F, 0.0, 0.0, 0.0, qw, nullptr, fw), "vjp: force");
+    st = force_pairs(c, qw, fw);
+    if (st != MD_OK) return st;
     st = step_pairs(c, qw, pw, fw, dt, nsteps, P, slot);
     if (st != MD_OK) return st;
     return reverse_pairs(c, q0, P, slot, dt, nsteps, lq, lp);
@@ -1001,11 +1031,9 @@ int md_force(md_ctx *c, const double *q, double *f)
         c->forced = true;
         return MD_OK;
     }
-    MD_TRY(update_(c, UPD_PREP, 0.0, 0.0, 0.0, qm, nullptr, nullptr), "force: operands");
-    MD_TRY(pair_(c, q), "force: pair kernel");
-    MD_TRY(update_(c, UPD_F_FROM_PART | UPD_STORE_F, 0.0, 0.0, 0.0, qm, nullptr, f), "force: combine");
-    c->forced = true;
-    return MD_OK;
+    const int st = force_pairs(c, qm, f);
+    if (st == MD_OK) c->forced = true;
+    return st;
 }
 
 int md_step(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nsteps)
@@ -1094,6 +1122,13 @@ int md_hvp(md_ctx *c, const double *q, const double *w, double *out)
     if (c->model == MD_HMF) {
         MD_TRY(launch_hmf_adj_pass(c, 0, nullptr, 0, 0.0, 0.0, 0.0, nullptr, wm, nullptr, q), "hvp: sums");
         MD_TRY(launch_hmf_adj_pass(c, 1, q, ADJ_OUT, 0.0, 0.0, 0.0, nullptr, wm, out, nullptr), "hvp: product");
+        return MD_OK;
+    }
+    // one launch, unless out overlaps an input (blocks read other blocks' particles)
+    const size_t len = (size_t)dims(c->model) * (size_t)c->n;
+    const auto apart = [&](const double *x) { return x + len <= out || out + len <= x; };
+    if (hvp_fused(c) && apart(q) && apart(w)) {
+        MD_TRY(launch_hvp_fused(c, q, w, (int)c->n, ADJ_OUT, 0.0, 0.0, 0.0, nullptr, nullptr, 0, out), "hvp: product");
         return MD_OK;
     }
     MD_TRY(launch_adj_update(c, ADJ_PREPQ | ADJ_PREPW, 0.0, 0.0, 0.0, nullptr, wm, nullptr, q), "hvp: operands");

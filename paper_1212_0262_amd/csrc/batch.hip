@@ -448,6 +448,7 @@ hipError_t batch_update(md_ctx *c, int flags, double kick1, double kick2, double
     const Batch &B = *c->batch;
     const int pk = prep_kind(c);
     if (pk == PREP_NONE) flags &= ~UPD_PREP;
+    if (!flags) return hipSuccess;  // no operands to prepare
     const dim3 grid((unsigned)B.n_rows), block(256);
     // the symmetric form's rows carry S_b = T_b tile slots
     const int4 *rows = reinterpret_cast<const int4 *>(launch_form(c) == MD_LAUNCH_SYMMETRIC ? B.d_srows : B.d_rows);

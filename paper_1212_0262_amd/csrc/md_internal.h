@@ -57,6 +57,11 @@ constexpr int kFusedMaxWaves = 16;      // wavefronts per fused block
 constexpr int kFusedLdsBytes = 49152;   // LDS per fused block (split evenly between its wavefronts)
 constexpr int64_t kFusedAutoN = 4096;   // MD_LAUNCH_AUTO takes the fused form up to this n (Ring)
 constexpr int64_t kFusedAutoN2D = 6144; // ... and up to this n for 2D gravity
+// Up to these n a fused context's md_force and FP64 products are fused launches too.
+// Measured, us, fused / staged, 2D and Ring FP64: force n = 2000 8.7 / 9.1 and 9.1 / 11.5, 3000
+// 13.6 / 9.6 and 15.0 / 13.7; product 3000 12.1 / 12.9 and 14.0 / 14.4, 4096 14.8 / 17.4 and
+// 17.6 / 18.6, 5000 25.9 / 23.4 (2D).
+constexpr int64_t kFusedForceN = 2048, kFusedHvpN = 4096;
 constexpr int kSymTile = 1024;          // particles per tile of the symmetric form (4 waves x 64 x 4 i)
 constexpr int kBatchSymTile = 512;     // tiles of the ensembles' symmetric form (2 waves x 64 x 4 i)
 constexpr int kSymTileSmall = 512;      // ... for smaller n (2 waves x 64 x 4 i; sym_tile_n), and 256
@@ -241,6 +246,12 @@ enum : int {
     ADJ_KICK2 = 1 << 5,  // then lq -= h2 * (H w): a second kick at the same positions
 };
 hipError_t launch_hvp_pair(md_ctx *c, const double *pos, const double *w);
+// Small n, FP64: a whole product (out) or a whole stage of the reverse sweep in one launch
+// (w_in must not be an array the launch writes).
+bool hvp_fused(const md_ctx *c);
+hipError_t launch_hvp_fused(md_ctx *c, const double *pos, const double *w_in, int w_stride, int flags, double h,
+                            double h2, double a, double *lq, double *w_out, int o_stride, double *out);
+hipError_t launch_copy2(md_ctx *c, const double *a, double *a_out, const double *b, double *b_out, int64_t len);
 hipError_t launch_adj_update(md_ctx *c, int flags, double h, double h2, double a, double *lq, double *lp,
                              double *out, const double *pos);
 // energy.hip

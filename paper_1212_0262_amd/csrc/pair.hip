@@ -912,6 +912,7 @@ hipError_t update(md_ctx *c, int flags, double kick1, double kick2, double drift
     const int npad = (int)c->npad;
     const int pk = prep_kind(c, fused);
     if (pk == PREP_NONE) flags &= ~UPD_PREP;
+    if (!flags) return hipSuccess;  // no operands to prepare
     const int nthreads = (flags & UPD_PREP) ? npad : n;  // an operand refresh also writes the pads
     const dim3 block(256), grid((unsigned)((nthreads + 255) / 256));
     // the symmetric form's slot sums with 16-byte loads where VW particles a thread

@@ -363,3 +363,29 @@ def test_adjoint_config_full_run():
         print(f"adjoint config run dir {k}: ad={ad:.12e} fd={fd:.12e} rel={rel:.3e}")
         assert rel < 2e-6, (ad, fd)
     ctx.close()
+
+
+@pytest.mark.parametrize("model,eps", [(GRAV2D, 1e-3), (RING, 0.01)])
+@pytest.mark.parametrize("n", [1, 2, 7, 8, 9, 64, 65, 1023, 1025, 2048, 2049, 4096, 4097])
+def test_fused_product(model, eps, n):
+    """The one-launch product of small systems at the edges of its blocks (8 i), ranges (64) and
+    chunks (16 j), against the oracle; into its own input through the other launches; and its
+    sweep over a recorded run."""
+    q, p = _state(model, n, seed=n)
+    rng = np.random.default_rng(n)
+    w, lp = rng.normal(size=q.shape), rng.normal(size=q.shape)
+    ctx = md.md_init(model, md.FP64, n, eps)
+    ho = oracle.hvp(model, q, w, eps)
+    scale = max(np.abs(ho).max(), 1e-300)
+    hw = host(md.md_hvp(ctx, dev(q), dev(w)))
+    assert np.abs(hw - ho).max() <= 1e-13 * scale
+    wd = dev(w)
+    md.md_hvp(ctx, dev(q), wd, wd)  # out = w
+    assert np.abs(host(wd) - ho).max() <= 1e-13 * scale
+    if n <= 1025:
+        want = oracle.step_vjp(model, q, p, 0.01, 2, w, lp, eps)
+        a, b = dev(w), dev(lp)
+        md.md_step_vjp(ctx, dev(q), dev(p), 0.01, 2, a, b)
+        for x, y in zip((a, b), want):
+            assert np.abs(host(x) - y).max() <= 1e-11 * np.abs(y).max()
+    ctx.close()
