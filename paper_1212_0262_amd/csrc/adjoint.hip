@@ -76,16 +76,19 @@ __device__ __forceinline__ void hvp_2d_four(T xi, T yi, T wxi, T wyi, const T *x
 //   (pair_terms.h): a = 2 sin(d/2), b = 2 cos(d/2), r' = (a^2 + 2 eps)^{-1/2}
 //   (e = 2 eps): the same quantity is r'^3 [(1 - a^2/2) - (3/4) a^2 b^2 r'^2] with
 //   pref = 1/N.
+__device__ __forceinline__ double hvp_ring_factor(double ci, double si, double cj, double sj, double e)
+{
+    const double cd = fma_(ci, cj, si * sj);
+    const double sd = fma_(si, cj, -(ci * sj));
+    const double r = rsq_(e - cd);
+    const double r2 = r * r;
+    return r2 * r * fma_(-1.5 * sd * sd, r2, cd);
+}
 template <typename T, typename A>
 __device__ __forceinline__ void hvp_ring(T ci, T si, T wi, T cj, T sj, T wj, T e, A &acc)
 {
     if constexpr (sizeof(T) == 8) {
-        const T cd = fma_(ci, cj, si * sj);
-        const T sd = fma_(si, cj, -(ci * sj));
-        const T r = rsq_(e - cd);
-        const T r2 = r * r;
-        const T h = r2 * r * fma_(T(-1.5) * sd * sd, r2, cd);
-        acc.add(h, wi - wj);
+        acc.add(hvp_ring_factor(ci, si, cj, sj, e), wi - wj);
     } else {
         T a;
         {
@@ -437,6 +440,70 @@ __global__ __launch_bounds__(4 * kWave) void k_hvp_split(const double *__restric
     }
 }
 
+// Ring, FP64, tiles of 256 (n <= 65536): the term phi''(ti - tj) (w_i - w_j) is odd
+// under i <-> j too (cos d even, sin^2 d even).  As k_hvp_split, with the operands (cos,
+// sin) from the force's padded rows (pads 0: the term is exactly 0) and w read in place (a
+// pad's w is the last particle's).  19 FP64 instructions and a seed an evaluation for both
+// particles against 18 and a seed for one.  Measured, us per product with its two elementwise
+// launches, staged -> this: N = 5120 30 -> 23,
+// 10,240 76 -> 54, 20,480 271 -> 162, 32,768 672 -> 399, 65,536 2651 -> 1543.
+template <bool SYM>
+__device__ __forceinline__ void hvp_ring_block(const double *__restrict__ cs, const double *__restrict__ w, int n,
+                                               int npad, double e, double *__restrict__ part, int a, int b,
+                                               double (&lds)[4][kWave * kSymIpl])
+{
+    constexpr int TILE = kWave * kSymIpl;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int next = ((lane + 1) & (kWave - 1)) * 4;  // ds_bpermute byte address of lane l + 1
+    const int i0 = a * TILE + lane, j0 = b * TILE + wave * kWave;
+    double ci[kSymIpl], si[kSymIpl], wi[kSymIpl];
+#pragma unroll
+    for (int k = 0; k < kSymIpl; ++k) {
+        const int i = i0 + k * kWave;
+        ci[k] = cs[i];
+        si[k] = cs[npad + i];
+        wi[k] = w[min(i, n - 1)];
+    }
+    double cj = cs[j0 + lane], sj = cs[npad + j0 + lane], wj = w[min(j0 + lane, n - 1)];
+    AccF64 acc[kSymIpl], js;
+#pragma unroll 8
+    for (int s = 0; s < kWave; ++s) {
+        if (s) {
+            cj = lane_next(next, cj);
+            sj = lane_next(next, sj);
+            wj = lane_next(next, wj);
+            if (SYM) js.rotate(next);
+        }
+#pragma unroll
+        for (int k = 0; k < kSymIpl; ++k) {
+            const double u = wi[k] - wj, h = hvp_ring_factor(ci[k], si[k], cj, sj, e);
+            acc[k].add(h, u);
+            if (SYM) js.add(-h, u);
+        }
+    }
+    if (SYM) part[(size_t)a * npad + j0 + ((lane + kWave - 1) & (kWave - 1))] = js.get();  // lane l holds j = l - 1
+#pragma unroll
+    for (int k = 0; k < kSymIpl; ++k) lds[wave][lane + k * kWave] = acc[k].get();
+    __syncthreads();
+    const int i = threadIdx.x;
+    part[(size_t)b * npad + a * TILE + i] = ((lds[0][i] + lds[1][i]) + lds[2][i]) + lds[3][i];
+}
+
+__global__ __launch_bounds__(4 * kWave) void k_hvp_ring_split(const double *__restrict__ cs,
+                                                              const double *__restrict__ w, int n, int npad, int ntile,
+                                                              double e, double *__restrict__ part)
+{
+    __shared__ double lds[4][kWave * kSymIpl];
+    const int t = (int)blockIdx.x, noff = ntile * (ntile - 1) / 2;
+    if (t < noff) {
+        int a, b;
+        sym_tile_pair(t, ntile, a, b);
+        hvp_ring_block<true>(cs, w, n, npad, e, part, a, b, lds);
+    } else {
+        hvp_ring_block<false>(cs, w, n, npad, e, part, t - noff, t - noff, lds);
+    }
+}
+
 // --------------------------------------------------------- fused small-N product --
 
 // FP64, small n (where md_step takes its fused form): a whole product, and in the reverse
@@ -617,12 +684,16 @@ __device__ __forceinline__ void adj_elem(int d, int i, int n, int npad, double h
     }
 }
 
-// The pads of the symmetric product's operand rows (PREP_COPY64): positions at sym_pad,
-// the vector at 0.
+// The pads of the symmetric product's operand rows (2D: PREP_COPY64, Ring: PREP_SINCOS64):
+// positions at sym_pad, the vector at 0.
 template <int PREP>
 __device__ __forceinline__ void adj_pad(int d, int i, int npad, int flags, void *__restrict__ ops,
                                         void *__restrict__ wops)
 {
+    if constexpr (PREP == PREP_SINCOS64) {
+        if (i < npad && (flags & ADJ_PREPQ))
+            static_cast<double *>(ops)[i] = static_cast<double *>(ops)[npad + i] = sym_pad<MD_RING, double>();
+    }
     if constexpr (PREP == PREP_COPY64) {
         if (i >= npad) return;
         if (flags & ADJ_PREPQ) static_cast<double *>(ops)[(size_t)d * npad + i] = sym_pad<MD_GRAV2D, double>();
@@ -673,10 +744,12 @@ __global__ __launch_bounds__(kSplitWaves *kWave) void k_adj_update_split(
     adj_elem<PREP>(wave, i, n, npad, hw, flags, h, h2, a, lq, lp, out, pos, ops, wops);
 }
 
-// The symmetric product (k_hvp_sym) where the force takes the symmetric form: 2D, FP64.
+// The symmetric product (k_hvp_sym, k_hvp_split, k_hvp_ring_split) where the force takes the
+// symmetric form: FP64, 2D, and the Ring in tiles of 256.
 bool hvp_sym(const md_ctx *c)
 {
-    return c->model == MD_GRAV2D && c->prec == MD_FP64 && !c->batch && launch_form(c) == MD_LAUNCH_SYMMETRIC;
+    if (c->prec != MD_FP64 || c->batch || launch_form(c) != MD_LAUNCH_SYMMETRIC) return false;
+    return c->model == MD_GRAV2D || sym_tile_n(c->model, c->prec, c->n) == kWave * kSymIpl;
 }
 
 int prep_kind(const md_ctx *c)
@@ -765,16 +838,19 @@ hipError_t launch_hvp_pair(md_ctx *c, const double *pos, const double *w)
     if (hvp_sym(c)) {
         const int npad = (int)c->npad, tile = sym_tile_n(c->model, c->prec, c->n), ntile = npad / tile;
         const int nblocks = ntile * (ntile - 1) / 2 + ntile;
-        const double *q = static_cast<const double *>(c->ops), *w = static_cast<const double *>(c->wops);
-        const int ts = timed_begin(c, "k_hvp_sym");
-        if (tile == kSymTile)
-            hipLaunchKernelGGL(k_hvp_sym<4>, dim3((unsigned)nblocks), dim3(4 * kWave), 0, c->stream, q, w, (int)c->n,
+        const double *q = static_cast<const double *>(c->ops), *wr = static_cast<const double *>(c->wops);
+        const int ts = timed_begin(c, c->model == MD_RING ? "k_hvp_ring_split" : "k_hvp_sym");
+        if (c->model == MD_RING)
+            hipLaunchKernelGGL(k_hvp_ring_split, dim3((unsigned)nblocks), dim3(4 * kWave), 0, c->stream, q, w,
+                               (int)c->n, npad, ntile, 1.0 + c->eps, c->part);
+        else if (tile == kSymTile)
+            hipLaunchKernelGGL(k_hvp_sym<4>, dim3((unsigned)nblocks), dim3(4 * kWave), 0, c->stream, q, wr, (int)c->n,
                                npad, ntile, c->eps, c->part);
         else if (tile == kSymTileSmall)
-            hipLaunchKernelGGL(k_hvp_sym<2>, dim3((unsigned)nblocks), dim3(2 * kWave), 0, c->stream, q, w, (int)c->n,
+            hipLaunchKernelGGL(k_hvp_sym<2>, dim3((unsigned)nblocks), dim3(2 * kWave), 0, c->stream, q, wr, (int)c->n,
                                npad, ntile, c->eps, c->part);
         else
-            hipLaunchKernelGGL(k_hvp_split, dim3((unsigned)nblocks), dim3(4 * kWave), 0, c->stream, q, w, (int)c->n,
+            hipLaunchKernelGGL(k_hvp_split, dim3((unsigned)nblocks), dim3(4 * kWave), 0, c->stream, q, wr, (int)c->n,
                                npad, ntile, c->eps, c->part);
         const hipError_t err = hipGetLastError();
         timed_end(c, ts);
@@ -807,7 +883,7 @@ hipError_t launch_adj_update(md_ctx *c, int flags, double h, double h2, double a
     const dim3 block(256), grid((unsigned)((nthreads + 255) / 256));
     const double pref = hvp_prefactor(c);
     const int pk = prep_kind(c);
-    if (c->prec == MD_FP64 && !sym) flags &= ~ADJ_PREPW;
+    if (c->prec == MD_FP64 && !(sym && c->model == MD_GRAV2D)) flags &= ~ADJ_PREPW;
     if (pk == PREP_NONE) flags &= ~ADJ_PREPQ;
     if (!flags) return hipSuccess;  // no operands to prepare
     const int npad = (int)c->npad, S = sym ? npad / sym_tile_n(c->model, c->prec, c->n) : c->tiles.jsplit;

@@ -389,3 +389,28 @@ def test_fused_product(model, eps, n):
         for x, y in zip((a, b), want):
             assert np.abs(host(x) - y).max() <= 1e-11 * np.abs(y).max()
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [2048, 2305, 4608, 9999])
+def test_ring_symmetric_product(n):
+    """The Ring's symmetric product (FP64, tiles of 256, ragged with pads) against the oracle and
+    the staged product, repeated angles among them; the same bits again; and through a sweep."""
+    q, p = _state(RING, n, seed=n)
+    q[0, 5] = q[0, n - 1] = q[0, 300]
+    rng = np.random.default_rng(n)
+    w, lp = rng.normal(size=q.shape), rng.normal(size=q.shape)
+    ho = oracle.hvp(RING, q, w, 0.01)
+    ctx = md.md_init(RING, md.FP64, n, 0.01)
+    md.md_set_launch(ctx, md.LAUNCH_SYMMETRIC)
+    hw = md.md_hvp(ctx, dev(q), dev(w))
+    assert np.abs(host(hw) - ho).max() <= 1e-13 * np.abs(ho).max()
+    assert torch.equal(hw, md.md_hvp(ctx, dev(q), dev(w)))
+    out = []
+    for mode in (md.LAUNCH_SYMMETRIC, md.LAUNCH_STAGED):
+        md.md_set_launch(ctx, mode)
+        a, b = dev(w), dev(lp)
+        md.md_step_vjp(ctx, dev(q), dev(p), 0.05, 2, a, b)
+        out.append((host(a), host(b)))
+    for x, y in zip(*out):
+        assert np.abs(x - y).max() <= 1e-11 * np.abs(y).max()
+    ctx.close()
