@@ -25,6 +25,7 @@
 #include "md_internal.h"
 #include "pair_terms.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace md {
@@ -682,12 +683,32 @@ __global__ __launch_bounds__(64) void k_update_vec(const SlotT *__restrict__ par
 // order and runs the stage on its own particles: bit for bit the staged pair +
 // update launches.  The j operands come from `in`; the refreshed ones go to
 // `out` (another buffer: other blocks still read `in`), so the two alternate.
-template <int MODEL, typename T, typename A, int IPL, int PREP, int L>
+// The arguments of k_fused that only its end needs: the kernel reads them from the argument
+// segment itself, once the operands' loads are out.  Left to the compiler, their load (a
+// memory round trip) is waited for before the first window's.  They lie at kLateOffset: the
+// arguments before take 24 + 32 bytes and e.
+struct FusedLate {
+    void *out;
+    double *f, *snap;
+    double pref, kick1, kick2, drift;
+};
+constexpr int kLateOffset = 64;
+
+__device__ __forceinline__ FusedLate fused_late()
+{
+    const char __attribute__((address_space(4))) *a =
+        (const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));  // an address the compiler cannot load from earlier
+    const auto *l = (const FusedLate __attribute__((address_space(4))) *)(a + kLateOffset);
+    return FusedLate{l->out, l->f, l->snap, l->pref, l->kick1, l->kick2, l->drift};
+}
+
+// E: entries a lane fetches per operand row and window.
+template <int MODEL, typename T, typename A, int IPL, int PREP, int L, int E>
 __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double *__restrict__ q,
                                                 double *__restrict__ p, int n, int npad, int jlen, int S,
                                                 int slice_bytes, int CHL, int flags, int jtile, T e,
-                                                void *__restrict__ out, double pref, double *__restrict__ f,
-                                                double kick1, double kick2, double drift, double *__restrict__ snap)
+                                                FusedLate)
 {
     constexpr int D = MODEL == MD_GRAV2D ? 2 : 1;
     constexpr int IL = kWave / L;          // i slots per lane group
@@ -706,6 +727,30 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double
     const int wlen = max(0, min(n - w * L * jlen, jlen));      // the wavefront's longest (its group 0)
     const T *__restrict__ r0 = in;
     const T *__restrict__ r1 = in + npad;
+    // The wavefront's next window: kCols j of every group (the host keeps CHL within them), E
+    // entries a lane and row, all loads out at once: one memory round trip.  Entry
+    // x = 64 m + lane is j = x mod kCols of group x / kCols, addresses clamped in bounds.  The
+    // first window's loads go out before anything else is loaded, and a later one's while the
+    // window before it is used: as a loop in which each window was loaded when it was due, the
+    // compiler waited for the i operands first.  Measured, us per evaluation, before (with 8
+    // entries whatever the ranges, the late arguments among the first and the tree sums
+    // through LDS) and after: 2D FP64 n = 301 5.19 -> 4.15, 2000 6.40 -> 5.20, 4000 12.3 ->
+    // 10.5; 2D mixed 301 4.86 -> 3.97; 2D Kahan 301 5.05 -> 4.16; Ring FP64 2048 7.02 -> 6.14,
+    // 4000 14.9 -> 13.7; Ring mixed 2048 5.93 -> 5.07.
+    constexpr int kCols = E * kWave / L;
+    T x0[E], x1[E];
+    auto fetch = [&](int t) {
+#pragma unroll
+        for (int m = 0; m < E; ++m) {
+            const int x = m * kWave + lane;
+            const int jc = min((w * L + x / kCols) * jlen + t + x % kCols, n - 1);
+            const uint32_t at = (uint32_t)jc * (uint32_t)sizeof(T);  // scalar base + 32-bit offset
+            x0[m] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(r0) + at);
+            x1[m] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(r1) + at);
+        }
+    };
+    constexpr bool kAhead = IPL == 1 || sizeof(T) == 4;  // FP64 with more i a lane: no registers to spare
+    if (kAhead && wlen > 0) fetch(0);
     T a0[IPL], a1[IPL];
 #pragma unroll
     for (int k = 0; k < IPL; ++k) {
@@ -726,6 +771,11 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double
             if (stage_reads_p(flags)) p_pre = p[kk];
         }
     }
+    const FusedLate late = fused_late();
+    void *__restrict__ out = late.out;
+    double *__restrict__ f = late.f;
+    double *__restrict__ snap = late.snap;
+    const double pref = late.pref, kick1 = late.kick1, kick2 = late.kick2, drift = late.drift;
     A acc0[IPL], acc1[IPL];
     auto term = [&](T x, T y) {
 #pragma unroll
@@ -751,41 +801,20 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double
     for (int t = 0; t < wlen; t += 16) {
         if (off == 0) {
             wave_sync();  // the previous window's reads are done
-            // The window's cnt j per group (none past the wavefront's longest range):
-            // FB 64-j columns of every group are loaded (addresses clamped in
-            // bounds) before the first LDS write, so a window of up to FB * 64 j per
-            // group costs one memory round trip.  Measured at N = 2048 (Ring), from
-            // the kernel's start to the first window in LDS, against one load and
-            // its LDS write per loop trip: 2.2 -> 1.9 us (FP64), 3.3 -> 1.6 us (FP32,
-            // whose windows are twice as long); a step 23.7 -> 22.7 us (FP64) and
-            // 24.1 -> 17.7 us (mixed).
-            constexpr int FB = 8 / L;
-            const int cnt = min(CHL, wlen - t);
-            for (int e0 = 0; e0 < cnt; e0 += FB * kWave) {
-                T x0[FB][L], x1[FB][L];
+            if (!kAhead) fetch(t);
+            const int cnt = min(CHL, wlen - t);  // none past the wavefront's longest range
 #pragma unroll
-                for (int m = 0; m < FB; ++m)
-#pragma unroll
-                    for (int gg = 0; gg < L; ++gg) {
-                        const int ee = e0 + m * kWave + lane;
-                        const int j = (w * L + gg) * jlen + t + ee;
-                        const int jc = ee < cnt && j < n ? j : 0;
-                        x0[m][gg] = r0[jc];
-                        x1[m][gg] = r1[jc];
-                    }
-#pragma unroll
-                for (int m = 0; m < FB; ++m)
-#pragma unroll
-                    for (int gg = 0; gg < L; ++gg) {
-                        const int ee = e0 + m * kWave + lane;
-                        const int j = (w * L + gg) * jlen + t + ee;
-                        if (ee < cnt && j < n) {
-                            win[gg * WS + ee] = x0[m][gg];
-                            win[(L + gg) * WS + ee] = x1[m][gg];
-                        }
-                    }
+            for (int m = 0; m < E; ++m) {
+                const int x = m * kWave + lane, gg = x / kCols, c = x % kCols;
+                const int j = (w * L + gg) * jlen + t + c;
+                const bool in = c < cnt && j < n;
+                if (L > 1 || in) {  // the rest into the pad between the groups: no branch
+                    win[gg * WS + (in ? c : CHL)] = x0[m];
+                    win[(L + gg) * WS + (in ? c : CHL)] = x1[m];
+                }
             }
             wave_sync();
+            if (kAhead && t + CHL < wlen) fetch(t + CHL);
         }
         const T *w0 = win + g * WS + off;
         const T *w1 = win + (L + g) * WS + off;
@@ -830,25 +859,43 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double
     }
     wave_sync();  // window reads done before the slice takes the partials
     double *part = reinterpret_cast<double *>(slice);  // [L][IPL * D][IL]
+    // With 8 lane groups the wavefront's ranges are one block of kSlotBlock: its tree sum
+    // (slot_sums in device.h) by lane exchanges, groups one, two, four apart, into the
+    // place of the block's first partial.
+    if constexpr (L == kSlotBlock) {
 #pragma unroll
-    for (int k = 0; k < IPL; ++k) {
-        part[(g * IPL * D + k * D) * IL + il] = acc0[k].get();
-        if constexpr (MODEL == MD_GRAV2D) part[(g * IPL * D + k * D + 1) * IL + il] = acc1[k].get();
+        for (int k = 0; k < IPL; ++k) {
+            double t = acc0[k].get(), u = MODEL == MD_GRAV2D ? acc1[k].get() : t;
+            t += dpp_move<0x128>(t);  // row_ror:8
+            t = swap16_sum(t, t);
+            if constexpr (MODEL == MD_GRAV2D) {
+                u += dpp_move<0x128>(u);
+                u = swap16_sum(u, u);
+            }
+            t = swap32_sum(t, MODEL == MD_GRAV2D ? u : t);  // x in the lower half, y in the upper one
+            const int d = lane / 32;
+            if (lane % 32 < IL && d < D) part[(k * D + d) * IL + il] = t;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) {
+            part[(g * IPL * D + k * D) * IL + il] = acc0[k].get();
+            if constexpr (MODEL == MD_GRAV2D) part[(g * IPL * D + k * D + 1) * IL + il] = acc1[k].get();
+        }
     }
     __syncthreads();
     // The partials of range bb (of S L) for coordinate kd of i slot s2 (the order of
-    // slot_sums in device.h, range 0 first).  First the blocks of kSlotBlock ranges,
-    // a thread per block: its tree sum replaces the block's first partial (each
-    // partial is read by one thread only); then a thread per particle adds them.
+    // slot_sums in device.h, range 0 first).  First (fewer lane groups) the blocks of
+    // kSlotBlock ranges, a thread per block: its tree sum replaces the block's first
+    // partial (each partial is read by one thread only); then a thread per particle
+    // adds them.
     auto fpart = [&](int bb, int kd, int s2) {
         return reinterpret_cast<double *>(reinterpret_cast<char *>(lds) + (size_t)(bb / L) * slice_bytes) +
                ((bb % L) * IPL * D + kd) * IL + s2;
     };
     const int nblk = S * L / kSlotBlock;
-    if (flags & UPD_F_FROM_PART) {
-        // wavefront k takes block k (and k + S, ...), its lanes the particles: with 8
-        // lane groups the block is one wavefront's slice, and the lanes of each LDS
-        // read take consecutive words
+    if (L != kSlotBlock && (flags & UPD_F_FROM_PART)) {
+        // wavefront k takes block k (and k + S, ...), its lanes the particles
         for (int k = w; k < nblk; k += S) {
             for (int it = lane; it < IPL * D * IL; it += kWave) {
                 const int bb = k * kSlotBlock, s2 = it % IL, kd = it / IL;
@@ -958,6 +1005,15 @@ hipError_t update(md_ctx *c, int flags, double kick1, double kick2, double drift
     return hipGetLastError();
 }
 
+// j per lane group of a fused wavefront's LDS window: what its slice holds of two rows
+// (groups one element apart), a multiple of 16, and what one fetch loads.
+template <typename T>
+int fused_window(int slice, int L, int E)
+{
+    const int chl = (slice / (2 * (int)sizeof(T) * L) - (L > 1 ? 1 : 0)) / 16 * 16;
+    return std::min(chl, E * kWave / L);
+}
+
 template <int MODEL, typename T, typename A, int PREP>
 hipError_t fused_ipl(md_ctx *c, int flags, double kick1, double kick2, double drift, double *q, double *p,
                      double *f, const void *in, void *out, double *snap, T e)
@@ -974,23 +1030,25 @@ hipError_t fused_ipl(md_ctx *c, int flags, double kick1, double kick2, double dr
     const int slice = kFusedLdsBytes / S;  // bytes of a wavefront's window, then of its partials
     const size_t lds = (size_t)slice * S;
     const T *src = static_cast<const T *>(in);
-#define MD_FUSED(I_, L_)                                                                                              \
-    hipLaunchKernelGGL((k_fused<MODEL, T, A, I_, PREP, L_>), grid, block, lds, c->stream, src, q, p, n, npad, jlen, \
-                       S, slice, (slice / (2 * (int)sizeof(T) * L_) - (L_ > 1 ? 1 : 0)) / 16 * 16, flags, t.jtile, e, \
-                       out, pref, f, kick1, kick2, drift, snap)
+    const FusedLate late{out, f, snap, pref, kick1, kick2, drift};
+#define MD_FUSED(I_, L_, E_)                                                                                              \
+    hipLaunchKernelGGL((k_fused<MODEL, T, A, I_, PREP, L_, E_>), grid, block, lds, c->stream, src, q, p, n, npad, jlen, \
+                       S, slice, fused_window<T>(slice, L_, E_), flags, t.jtile, e, \
+                       late)
 #define MD_FUSED_L(I_)                          \
     switch (L) {                                \
-    case 1: MD_FUSED(I_, 1); break;             \
-    case 2: MD_FUSED(I_, 2); break;             \
-    case 4: MD_FUSED(I_, 4); break;             \
-    default: MD_FUSED(I_, 8); break;            \
+    case 1: MD_FUSED(I_, 1, 4); break;          \
+    case 2: MD_FUSED(I_, 2, 4); break;          \
+    case 4: MD_FUSED(I_, 4, 4); break;          \
+    default: MD_FUSED(I_, 8, 4); break;         \
     }
     const int ts = timed_begin(c, "k_fused");
-    switch (t.ipl) {
-    case 1: MD_FUSED_L(1); break;
-    case 2: MD_FUSED_L(2); break;
-    default: MD_FUSED_L(4); break;
-    }
+    // the built-in tiles (8 lane groups, one i a lane): entries by the length of the ranges
+    if (t.ipl == 1 && L == 8 && jlen <= 2 * kWave / 8) MD_FUSED(1, 8, 2);
+    else if (t.ipl == 1 && L == 8 && jlen > 4 * kWave / 8 && sizeof(T) == 4) MD_FUSED(1, 8, 8);
+    else if (t.ipl == 1) MD_FUSED_L(1)
+    else if (t.ipl == 2) MD_FUSED_L(2)
+    else MD_FUSED_L(4)
 #undef MD_FUSED_L
 #undef MD_FUSED
     const hipError_t err = hipGetLastError();

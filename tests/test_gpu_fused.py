@@ -177,3 +177,15 @@ def test_fused_step_is_graph_capturable():
         np.testing.assert_array_equal(host(qg), host(qe))
         np.testing.assert_array_equal(host(pg), host(pe))
         np.testing.assert_array_equal(host(fg), host(fe))
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 1023, 1024, 1025, 2047, 2049, 3073, 4096])
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("model,eps,dt", [(RING, 0.01, 0.05), (GRAV2D, 1e-3, 0.01)])
+def test_window_entries(model, eps, dt, prec, n):
+    """The built-in tiles at the edges of the window's entries (ranges of 16, 32, 48 and 64 j, one or
+    two windows each): the staged form's bits, and md_force's."""
+    a = _run(model, prec, n, eps, dt, 2, (1, 4, 64, 128), md.LAUNCH_STAGED, seed=n)
+    b = _run(model, prec, n, eps, dt, 2, (1, 4, 64, 128), md.LAUNCH_FUSED, seed=n)
+    for x, y in zip(a, b):
+        np.testing.assert_array_equal(x, y)
