@@ -237,8 +237,10 @@ int force_pairs(md_ctx *c, double *q, double *f)
     return MD_OK;
 }
 
+// positions_only: up to the last drift (whose positions go to snap); the force there, the
+// last kick and f are left out.
 int step_pairs(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nsteps, double *snap = nullptr,
-               size_t snap_stride = 0)
+               size_t snap_stride = 0, bool positions_only = false)
 {
     double B0, B1, D0, D1;
     yoshida(&B0, &B1, &D0, &D1);
@@ -263,7 +265,7 @@ int step_pairs(md_ctx *c, double *q, double *p, double *f, double dt, int64_t ns
             MD_TRY(fused(stage, B1 * dt, 0.0, D0 * dt, next()), "step: fused stage");
             if (s + 1 < nsteps)
                 MD_TRY(fused(stage | UPD_KICK2, B0 * dt, B0 * dt, D0 * dt, next()), "step: fused stage");
-            else
+            else if (!positions_only)
                 MD_TRY(fused(UPD_F_FROM_PART | UPD_STORE_F | UPD_KICK1, B0 * dt, 0.0, 0.0, nullptr),
                        "step: last kick");
         }
@@ -275,6 +277,7 @@ int step_pairs(md_ctx *c, double *q, double *p, double *f, double dt, int64_t ns
         MD_TRY(update_(c, stage, B1 * dt, 0.0, D1 * dt, q, p, f, next()), "step: update");
         MD_TRY(pair_(c, q), "step: pair kernel");
         MD_TRY(update_(c, stage, B1 * dt, 0.0, D0 * dt, q, p, f, next()), "step: update");
+        if (positions_only && s + 1 == nsteps) break;
         MD_TRY(pair_(c, q), "step: pair kernel");
         if (s + 1 < nsteps)
             MD_TRY(update_(c, stage | UPD_KICK2, B0 * dt, B0 * dt, D0 * dt, q, p, f, next()), "step: update");
@@ -370,21 +373,22 @@ int reverse_hmf(md_ctx *c, const double *q0, const double *P, size_t slot, doubl
 hipError_t hmf_force(md_ctx *c, double *q, double *f)
 {
     if (hmf_small(c)) return launch_hmf_small_eval(c, q, nullptr, nullptr, f, nullptr, nullptr);
-    hipError_t e = launch_hmf_begin(c);
-    if (e == hipSuccess) e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, q, nullptr, nullptr, false);
+    hipError_t e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, q, nullptr, nullptr, false);
     if (e == hipSuccess) e = launch_hmf_pass(c, 1, HMF_STORE_F, 0.0, 0.0, 0.0, q, nullptr, f, false);
     return e;
 }
 
 // snap (FP64 state only): the angles after every drift are also written to
 // consecutive slots of snap, snap_stride doubles apart.
+// positions_only: as step_pairs.
 int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nsteps, double *snap = nullptr,
-             size_t snap_stride = 0)
+             size_t snap_stride = 0, bool positions_only = false)
 {
     double B0, B1, D0, D1;
     yoshida(&B0, &B1, &D0, &D1);
     if (hmf_small(c)) {
-        MD_TRY(launch_hmf_small_steps(c, B0 * dt, B1 * dt, D0 * dt, D1 * dt, nsteps, q, p, f, snap, snap_stride),
+        MD_TRY(launch_hmf_small_steps(c, B0 * dt, B1 * dt, D0 * dt, D1 * dt, nsteps, q, p, f, snap, snap_stride,
+                                      positions_only),
                "step: stages");
         return MD_OK;
     }
@@ -393,7 +397,6 @@ int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nste
     int64_t slot = 0;
     auto next = [&]() { return snap ? snap + (size_t)(slot++) * snap_stride : nullptr; };
     int k = 0;  // pass index: pass k reads the magnetization sums of pass k - 1
-    MD_TRY(launch_hmf_begin(c), "step: magnetization sums");
     MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_F | HMF_DRIFT | HMF_WRITE | HMF_REDUCE | HMF_IN64, B0 * dt, 0.0, D0 * dt, q, p, f,
                            f32, next()),
            "step: first pass");
@@ -406,7 +409,7 @@ int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nste
             MD_TRY(launch_hmf_pass(c, k++, stage | HMF_KICK2, B0 * dt, B0 * dt, D0 * dt, q, p, nullptr,
                                    f32, next()),
                    "step: pass");
-        else
+        else if (!positions_only)
             MD_TRY(launch_hmf_pass(c, k++, HMF_KICK_M | HMF_STORE_F | HMF_WRITE | HMF_OUT64, B0 * dt, 0.0, 0.0, q, p, f,
                                    f32),
                    "step: last pass");
@@ -414,8 +417,9 @@ int step_hmf(md_ctx *c, double *q, double *p, double *f, double dt, int64_t nste
     return MD_OK;
 }
 
-// md_step_vjp: recompute the steps from (q0, p0) into stage = [q | p | f | P_1 .. P_3n]
-// (one slot each), then sweep back.
+// md_step_vjp: recompute the kick positions of the steps from (q0, p0) into stage =
+// [q | p | f | P_1 .. P_3n] (one slot each; of 3 n + 1 force evaluations the last, at P_3n,
+// is not needed), then sweep back.
 int step_vjp(md_ctx *c, const double *q0, const double *p0, double dt, int64_t nsteps, double *lq, double *lp,
              double *stage)
 {
@@ -425,13 +429,13 @@ int step_vjp(md_ctx *c, const double *q0, const double *p0, double dt, int64_t n
     int st;
     if (c->model == MD_HMF) {
         MD_TRY(hmf_force(c, qw, fw), "vjp: force");
-        st = step_hmf(c, qw, pw, fw, dt, nsteps, P, slot);
+        st = step_hmf(c, qw, pw, fw, dt, nsteps, P, slot, true);
         if (st != MD_OK) return st;
         return reverse_hmf(c, q0, P, slot, dt, nsteps, lq, lp);
     }
     st = force_pairs(c, qw, fw);
     if (st != MD_OK) return st;
-    st = step_pairs(c, qw, pw, fw, dt, nsteps, P, slot);
+    st = step_pairs(c, qw, pw, fw, dt, nsteps, P, slot, true);
     if (st != MD_OK) return st;
     return reverse_pairs(c, q0, P, slot, dt, nsteps, lq, lp);
 }
@@ -1328,7 +1332,7 @@ int md_force_noalloc(int model, int prec, int64_t n, double eps, void *hip_strea
     double *qm = const_cast<double *>(q);
     hipError_t e = hipSuccess;
     if (model == MD_HMF) {
-        e = hmf_force(&c, qm, f);  // zeroes the fixed-point sums the previous call left
+        e = hmf_force(&c, qm, f);  // whatever fixed-point sums the previous call left
     } else {
         // every slot the combine reads is written by the pair kernel first
         e = launch_update(&c, UPD_PREP, 0.0, 0.0, 0.0, qm, nullptr, nullptr);

@@ -205,9 +205,8 @@ hipError_t launch_energy(md_ctx *c, const double *q, const double *p, double *ou
 hipError_t launch_magnetization(md_ctx *c, const double *q, double *out2)
 {
     if (hmf_small(c)) return launch_hmf_small_eval(c, q, nullptr, out2, nullptr, nullptr, finite_flag(c));
-    hipError_t e = launch_hmf_begin(c);
-    if (e == hipSuccess)
-        e = launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, const_cast<double *>(q), nullptr, nullptr, false);
+    const hipError_t e =
+        launch_hmf_pass(c, 0, HMF_REDUCE, 0.0, 0.0, 0.0, const_cast<double *>(q), nullptr, nullptr, false);
     if (e != hipSuccess) return e;
     return launch_hmf_magnetization(c, out2);
 }

@@ -8,11 +8,12 @@
 // for the next magnetization, and writes (t, p) back.  Stored sines/cosines
 // would add 32 B of HBM traffic per particle per stage to a bandwidth-bound
 // pass; two sincos evaluations cost less.  The magnetization is a grid-wide
-// dependency: each pass ends with FP64 block partials (wavefront butterfly, then
-// a fixed serial order over wavefronts), which every block adds in fixed point
-// (limbs of 2^-32 and 2^-64, 64-bit integer atomics into kMSlots slots) to one of
-// three buffers, and every block of the next pass sums the slots exactly, in
-// integers, and converts the total once to FP64 (no launch between passes).
+// dependency: each pass ends with FP64 block partials (lane exchanges, then a fixed
+// serial order over wavefronts), which every block adds in fixed point (limbs of 2^-32
+// and 2^-64, 64-bit integer atomics into kMSlots slots) to one of three buffers; every
+// wavefront of the next pass sums the slots exactly, in integers, and converts the total
+// once to FP64 (no launch between passes).  The second pass of a call takes the first's
+// partials instead, as limbs again (partials_mean).
 // Integer sums do not depend on the order of the atomics, so M is reproducible,
 // and it is the exact sum of the FP64 block partials rounded once.  That is for
 // grids of at most kHmfInPassM blocks (N <= 2.1e6); on larger ones every block
@@ -121,6 +122,48 @@ __device__ __forceinline__ void limbs_mean(const long long *__restrict__ acc, in
     my = ((double)lane_value<32>(t) * 0x1p-32 + (double)lane_value<48>(t) * 0x1p-64) / (double)n;
 }
 
+// The same M from the g block partials (sum cos, sum sin) of a pass 0, by a block of 256
+// (a barrier): each partial as its limbs, added in integers, so the same bits.  Pass 1 of a
+// call takes it, so that no launch has to zero a limb buffer before pass 0.  Over the whole
+// block, kMeanBatch loads a thread in flight: by each wavefront for itself the conversions
+// cost more than that launch.  md_force, us, with it, by each wavefront, and so: N = 1e6
+// 12.9, 17.8, 12.4; N = 16,384 11.3, 9.3, 8.9.
+constexpr int kMeanBatch = 2;
+
+__device__ __forceinline__ void partials_mean(const double *__restrict__ red, int g, int n, long long (&lds)[4][4],
+                                              double &mx, double &my)
+{
+    long long a[4] = {0, 0, 0, 0};
+    for (int b0 = threadIdx.x; b0 < g; b0 += 256 * kMeanBatch) {
+        double x[kMeanBatch][2];
+#pragma unroll
+        for (int j = 0; j < kMeanBatch; ++j) {
+            const int b = b0 + 256 * j;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) x[j][k] = b < g ? red[2 * b + k] : 0.0;
+        }
+#pragma unroll
+        for (int j = 0; j < kMeanBatch; ++j) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                long long hi, lo;
+                to_limbs(x[j][k], hi, lo);
+                a[2 * k] += hi;
+                a[2 * k + 1] += lo;
+            }
+        }
+    }
+    const int lane = threadIdx.x & (kWave - 1);
+    const long long t = wave_sum4(a[0], a[1], a[2], a[3]);
+    if (lane % 16 == 0) lds[lane / 16][threadIdx.x / kWave] = t;
+    __syncthreads();
+    long long s[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s[k] = (lds[k][0] + lds[k][1]) + (lds[k][2] + lds[k][3]);
+    mx = ((double)s[0] * 0x1p-32 + (double)s[1] * 0x1p-64) / (double)n;
+    my = ((double)s[2] * 0x1p-32 + (double)s[3] * 0x1p-64) / (double)n;
+}
+
 // One kick/drift/reduce pass over all particles (grid-stride over a grid fixed
 // per n, so every partial sum is reproducible).  T: state type; W: elements per
 // vector access; U: vectors per thread and iteration.  HMF_REDUCE writes the block
@@ -132,6 +175,8 @@ __device__ __forceinline__ void limbs_mean(const long long *__restrict__ acc, in
 // kernel (no code of the limbs).  Launched with 256 threads.
 // f: read by HMF_KICK_F, written by HMF_STORE_F.  macc: the limb sums, three buffers
 // [kMSlots][kMLimbs] in turn: buf is read, the next added to, the one after it zeroed.
+// HMF_FIRST (pass 0): nothing is added.  HMF_SECOND (pass 1): M comes from pass 0's partials,
+// 2 kHmfInPassM before this pass's red.
 // FP32 state: HMF_IN64 takes the state from th64, p64 instead (angles wrapped),
 // HMF_OUT64 writes it there.  FP64 state: the drifted angles also go to snap (both x64).
 template <typename T, int W, int U, bool LIMBS>
@@ -142,6 +187,7 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
                                                   double *__restrict__ x64, double *__restrict__ p64)
 {
     __shared__ double lds[2][4];
+    __shared__ long long mlds[4][4];
     double *__restrict__ th64 = x64;  // FP32 state
     double *__restrict__ snap = x64;  // FP64 state
     constexpr int B = kMSlots * kMLimbs;  // words per limb buffer; the three in turn: read, add, zero
@@ -155,7 +201,8 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
     if (flags & (HMF_KICK_M | HMF_STORE_F)) {
         if constexpr (LIMBS) {
             double dmx, dmy;
-            limbs_mean(mrd, n, dmx, dmy);
+            if (flags & HMF_SECOND) partials_mean(red - 2 * kHmfInPassM, grid, n, mlds, dmx, dmy);
+            else limbs_mean(mrd, n, dmx, dmy);
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 M[0] = dmx;
                 M[1] = dmy;
@@ -276,7 +323,7 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
         if (threadIdx.x < kWave && lane % 32 == 0) {
             const double b = ((lds[k][0] + lds[k][1]) + lds[k][2]) + lds[k][3];
             red[2 * blockIdx.x + k] = b;
-            if constexpr (LIMBS) {
+            if (LIMBS && !(flags & HMF_FIRST)) {
                 unsigned long long *w =
                     reinterpret_cast<unsigned long long *>(mwr + (blockIdx.x % kMSlots) * kMLimbs + 2 * k);
                 long long hi, lo;
@@ -288,16 +335,13 @@ __global__ __launch_bounds__(256) void k_hmf_pass(T *__restrict__ th, T *__restr
     }
 }
 
-// Zeroes one limb buffer (the first of a call's passes adds into it).
-__global__ __launch_bounds__(256) void k_hmf_zero_limbs(long long *__restrict__ acc) { acc[threadIdx.x] = 0; }
-
-// M from the limb sums of one buffer (one wavefront, lane l loads slot l), to
-// M[0..1] and (if given) out[0..1].
-__global__ __launch_bounds__(64) void k_hmf_limbs_to_m(const long long *__restrict__ acc, int n,
-                                                       double *__restrict__ out, double *__restrict__ M)
+// M from the g block partials of a pass 0 (one block), to M[0..1] and (if given) out[0..1].
+__global__ __launch_bounds__(256) void k_hmf_limbs_to_m(const double *__restrict__ red, int g, int n,
+                                                          double *__restrict__ out, double *__restrict__ M)
 {
+    __shared__ long long lds[4][4];
     double mx, my;
-    limbs_mean(acc, n, mx, my);
+    partials_mean(red, g, n, lds, mx, my);
     if (threadIdx.x == 0) {
         if (out) {
             out[0] = mx;
@@ -333,12 +377,15 @@ __global__ __launch_bounds__(1024) void k_hmf_finalize(const double *__restrict_
             s += vs[k];
         }
     }
-    c = block_sum<1024>(c, lds[0]);
-    s = block_sum<1024>(s, lds[1]);
-    if (threadIdx.x == 0) {
-        M[0] = c / (double)n;
-        M[1] = s / (double)n;
-    }
+    // lane 0 of each wavefront has its sum cos, lane 32 its sum sin; then the first
+    // wavefront's rows of lanes add the wavefronts'
+    const int lane = threadIdx.x & (kWave - 1), k = lane / 32;
+    const double t = wave_sum2(c, s);
+    if (lane % 32 == 0) lds[k][threadIdx.x / kWave] = t;
+    __syncthreads();
+    if (threadIdx.x >= kWave) return;
+    const double m = row_sum(lds[k][lane % 16]) / (double)n;
+    if (lane % 32 == 0) M[k] = m;
 }
 
 // ------------------------------------------------------------------- adjoint --
@@ -566,13 +613,6 @@ const double *hmf_partials(const md_ctx *c) { return c->red; }
 // through the one-block kernel over the FP64 partials.
 static bool hmf_in_pass(const md_ctx *c) { return hmf_grid(c->n) <= kHmfInPassM; }  // n <= 2,097,152
 
-hipError_t launch_hmf_begin(md_ctx *c)
-{
-    if (!hmf_in_pass(c)) return hipSuccess;
-    hipLaunchKernelGGL(k_hmf_zero_limbs, dim3(1), dim3(kMSlots * kMLimbs), 0, c->stream, c->macc);
-    return hipGetLastError();
-}
-
 hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kick2, double drift, double *th,
                            double *p, double *f, bool f32state, double *snap)
 {
@@ -583,7 +623,12 @@ hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kic
     // ones: the one-block kernel over the FP64 partials after a reducing pass, and
     // M read from c->scal.
     const bool in_pass = hmf_in_pass(c);
+    // the partials alternate between two halves of the scratch when a pass reads them; the
+    // energy and the one-block kernels take the first half's
+    static_assert(4 * kHmfInPassM <= kRedSlots, "two halves of block partials");
+    double *red = in_pass && k == 1 ? c->red + 2 * kHmfInPassM : c->red;
     const int buf = (k + 2) % 3;
+    if (k < 2) flags |= k == 0 ? HMF_FIRST : HMF_SECOND;
     const bool vec = (f32state ? vec_width(true, c->th32, c->p32, f) : vec_width(false, th, p, f)) > 1;
     // the vector and unroll that give a thread hmf_block / 256 particles (two iterations
     // of kUnroll 16-byte vectors at most); W = 1 where a pointer is not 16-byte aligned
@@ -591,7 +636,7 @@ hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kic
     const int ts = timed_begin(c, "k_hmf_pass");
 #define MD_HMF_PASS(T_, W_, U_, L_, TH_, P_, X_)                                                                 \
     hipLaunchKernelGGL((k_hmf_pass<T_, W_, U_, L_>), dim3(g), dim3(256), 0, c->stream, TH_, P_, c->macc, c->scal, n, \
-                       g, flags, buf, f, c->red, kick1, kick2, drift, X_, p)
+                       g, flags, buf, f, red, kick1, kick2, drift, X_, p)
 #define MD_HMF_FORM(T_, V_, TH_, P_, X_)                                                     \
     do {                                                                                     \
         if (!in_pass && vec) MD_HMF_PASS(T_, V_, kUnroll, false, TH_, P_, X_);               \
@@ -618,7 +663,8 @@ hipError_t launch_hmf_magnetization(md_ctx *c, double *out2)
 {
     if (!hmf_in_pass(c))  // the reducing pass's one-block kernel left M in c->scal
         return hipMemcpyAsync(out2, c->scal, 2 * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
-    hipLaunchKernelGGL(k_hmf_limbs_to_m, dim3(1), dim3(kWave), 0, c->stream, c->macc, (int)c->n, out2, c->scal);
+    hipLaunchKernelGGL(k_hmf_limbs_to_m, dim3(1), dim3(256), 0, c->stream, c->red, hmf_grid(c->n), (int)c->n, out2,
+                       c->scal);
     return hipGetLastError();
 }
 

@@ -93,10 +93,12 @@ struct StepCoef {
 };
 
 // nsteps >= 1 Yoshida steps.  snap (nullable): the angles after each drift, stride apart.
+// positions_only: nothing past the last of them.
 template <typename T, int P>
 __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_step(double *__restrict__ q, double *__restrict__ p,
                                                                   double *__restrict__ f, int n, int threads, StepCoef a,
-                                                                  int nsteps, double *__restrict__ snap, size_t stride)
+                                                                  int nsteps, double *__restrict__ snap, size_t stride,
+                                                                  int positions_only)
 {
     const int B = small_block<P>(threads);
     __shared__ double lds[2][2][kSmallWaves];
@@ -126,6 +128,7 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_step(double *__r
                 if (i < n) snap[(size_t)m * stride + i] = (double)th[k];
             }
         }
+        if (positions_only && m == last) return;
         sincos_n(th, s, c);
         double v[2];
         small_sums(s, c, n, B, v);
@@ -347,7 +350,7 @@ static_assert(kHmfSmallN <= 32 * small_threads(32), "every particle has a thread
 }  // namespace
 
 hipError_t launch_hmf_small_steps(md_ctx *c, double b0, double b1, double d0, double d1, int64_t nsteps, double *q,
-                                  double *p, double *f, double *snap, size_t snap_stride)
+                                  double *p, double *f, double *snap, size_t snap_stride, bool positions_only)
 {
     const StepCoef a{b0, b1, d0, d1};
     const int n = (int)c->n;
@@ -355,11 +358,12 @@ hipError_t launch_hmf_small_steps(md_ctx *c, double b0, double b1, double d0, do
     for (int64_t done = 0; done < nsteps && err == hipSuccess;) {
         const int k = (int)(nsteps - done < kHmfSmallSteps ? nsteps - done : kHmfSmallSteps);
         double *sn = snap ? snap + (size_t)(3 * done) * snap_stride : nullptr;
+        const int only = positions_only && done + k == nsteps;
         const int ts = timed_begin(c, "k_hmf_small_step");
 #define K64(P_) k_hmf_small_step<double, P_>
 #define K32(P_) k_hmf_small_step<float, P_>
-        if (c->prec == MD_FP64) MD_SMALL(K64, q, p, f, n, B, a, k, sn, snap_stride);
-        else MD_SMALL(K32, q, p, f, n, B, a, k, sn, snap_stride);
+        if (c->prec == MD_FP64) MD_SMALL(K64, q, p, f, n, B, a, k, sn, snap_stride, only);
+        else MD_SMALL(K32, q, p, f, n, B, a, k, sn, snap_stride, only);
 #undef K64
 #undef K32
         err = hipGetLastError();

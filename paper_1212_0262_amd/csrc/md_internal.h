@@ -34,6 +34,8 @@ enum : int {
     HMF_WRITE = 1 << 6,     // write t, p back
     HMF_IN64 = 1 << 7,      // FP32 state: read t, p from the FP64 arrays (the first pass of a call)
     HMF_OUT64 = 1 << 8,     // FP32 state: write t, p to the FP64 arrays (the last pass)
+    HMF_FIRST = 1 << 9,     // pass 0 and pass 1 of a call (set by launch_hmf_pass)
+    HMF_SECOND = 1 << 10,
 };
 
 constexpr int kWave = 64;           // lanes per wavefront (CDNA)
@@ -206,26 +208,24 @@ hipError_t launch_update_fused(md_ctx *c, int flags, double kick1, double kick2,
 hipError_t launch_fused(md_ctx *c, int flags, double kick1, double kick2, double drift, double *q, double *p,
                         double *f, const void *in, void *out, double *snap);
 // hmf.hip
-// The passes of one call are numbered k = 0, 1, ...: pass k takes M from the limb
-// sums pass k - 1 added, adds its own to buffer k mod 3 and zeroes buffer
-// (k + 1) mod 3.  launch_hmf_begin zeroes buffer 0 before the first pass of a call
-// whose passes read M.
+// The passes of one call are numbered k = 0, 1, ...: pass 1 takes M from the block partials
+// of pass 0, pass k > 1 from the limb sums pass k - 1 added; pass k > 0 adds its own to buffer
+// k mod 3, and every pass zeroes buffer (k + 1) mod 3.
 // f: read by HMF_KICK_F or written by HMF_STORE_F.
 // snap (nullable, FP64 state only): with HMF_DRIFT, the drifted angles are also written there.
-hipError_t launch_hmf_begin(md_ctx *c);
 hipError_t launch_hmf_pass(md_ctx *c, int k, int flags, double kick1, double kick2, double drift, double *th, double *p,
                            double *f, bool f32state, double *snap = nullptr);
 hipError_t launch_hmf_adj_pass(md_ctx *c, int k, const double *th, int flags, double h, double h2, double a,
                                double *lq, double *lp, double *out, const double *th_next);
-// M from the limb sums of a call's pass 0, to out2[0..1] and the context scalars.
+// M from the partials of a call's pass 0, to out2[0..1] and the context scalars.
 hipError_t launch_hmf_magnetization(md_ctx *c, double *out2);
-const double *hmf_partials(const md_ctx *c);  // block partials of the latest reducing pass
+const double *hmf_partials(const md_ctx *c);  // block partials of a call's pass 0
 // hmf_small.hip (n <= kHmfSmallN): whole calls in one launch.  b0 .. d1: the kicks and
 // drifts of eq. 4 times dt.  Outputs of eval (nullable): M, the force, the energies of
 // (q, p) and their (or M's) finiteness.
 inline bool hmf_small(const md_ctx *c) { return c->n <= kHmfSmallN; }
 hipError_t launch_hmf_small_steps(md_ctx *c, double b0, double b1, double d0, double d1, int64_t nsteps, double *q,
-                                  double *p, double *f, double *snap, size_t snap_stride);
+                                  double *p, double *f, double *snap, size_t snap_stride, bool positions_only);
 hipError_t launch_hmf_small_eval(md_ctx *c, const double *q, const double *p, double *out2, double *f, double *out3,
                                  unsigned *flag);
 hipError_t launch_hmf_small_hvp(md_ctx *c, const double *q, const double *w, double *out);
