@@ -22,6 +22,8 @@
 #include "md_internal.h"
 #include "pair_terms.h"
 
+#include <type_traits>
+
 namespace md {
 namespace {
 
@@ -362,6 +364,101 @@ __global__ __launch_bounds__(W * kWave) void k_batch_sym(const PairItem *__restr
         batch_sym_item<MODEL, T, A, false, W>(it, r0, r1, beps, npad, part, jw);
 }
 
+// The same item shared by 2 NS wavefronts of a block: wavefront (h, s) takes the i half h
+// against the s-th run of 8 / NS 64-j blocks, so that the serial length of an item is 1 / NS
+// of k_batch_sym's.  The j sums of every (h, 64-j block) and the i sums of every s meet in
+// LDS after one barrier.  A run is a whole number of the 128 j after which MD_MIXED folds its
+// FP32 sums, and the folds are added in the same order, so its bits are k_batch_sym's; the
+// running compensation of MD_MIXED_KAHAN would be cut, so it keeps k_batch_sym.
+template <int MODEL, typename T, typename A, bool SYM, int NS>
+__device__ __forceinline__ void batch_sym_split_item(
+    const PairItem &it, const T *__restrict__ r0, const T *__restrict__ r1, const double *__restrict__ beps, int npad,
+    double *__restrict__ part, double (&iw)[NS][MODEL == MD_GRAV2D ? 2 : 1][kBatchSymTile],
+    double (&jw)[2][MODEL == MD_GRAV2D ? 2 : 1][kBatchSymTile])
+{
+    constexpr int D = MODEL == MD_GRAV2D ? 2 : 1;
+    constexpr int HALF = kWave * kSymIpl, RUN = kBatchSymTile / kWave / NS;
+    static_assert(2 * HALF == kBatchSymTile && RUN % 2 == 0, "two i halves; runs of whole 128-j folds");
+    const double eb = beps[it.b];
+    const T e = MODEL == MD_GRAV2D ? (T)eb : sizeof(T) == 4 ? (T)(2.0 * eb) : (T)(1.0 + eb);
+    const T pad = sym_pad<MODEL, T>();
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int h = wave / NS, s = wave % NS;
+    const int ih = it.i0 + h * HALF, jr = it.j0 + s * RUN * kWave;
+    // this wavefront's 64-j blocks that hold a particle
+    const int nblk = min(RUN, (it.j1 - jr + kWave - 1) / kWave);
+    A acc[D][kSymIpl];
+    if (nblk > 0 && ih < it.i1) {
+        T u0[kSymIpl], u1[kSymIpl];
+#pragma unroll
+        for (int k = 0; k < kSymIpl; ++k) {
+            const int i = ih + k * kWave + lane;
+            const int ic = min(i, it.i1 - 1);
+            u0[k] = i < it.i1 ? r0[ic] : pad;
+            u1[k] = i < it.i1 ? r1[ic] : pad;
+        }
+        sym_tile<MODEL, T, A, SYM>(
+            u0, u1, e, lane, nblk,
+            [&](int blk, T &v0, T &v1) {
+                const int j = jr + blk * kWave + lane;
+                const int jc = min(j, it.j1 - 1);
+                v0 = j < it.j1 ? r0[jc] : pad;
+                v1 = j < it.j1 ? r1[jc] : pad;
+            },
+            [&](int blk, int m, A (&sj)[D]) {
+#pragma unroll
+                for (int d = 0; d < D; ++d) jw[h][d][(s * RUN + blk) * kWave + m] = sj[d].get();
+            },
+            acc);
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+#pragma unroll
+        for (int k = 0; k < kSymIpl; ++k) iw[s][d][h * HALF + k * kWave + lane] = acc[d][k].get();
+    __syncthreads();
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        for (int x = threadIdx.x; x < kBatchSymTile; x += 2 * NS * kWave) {
+            if (it.i0 + x < it.i1) {
+                double t = iw[0][d][x];
+#pragma unroll
+                for (int r = 1; r < NS; ++r) t += iw[r][d][x];
+                part[(size_t)(D * it.slot + d) * npad + it.i0 + x] = t;
+            }
+            if (SYM && it.j0 + x < it.j1)  // (the i tile of a pair is whole: both halves have sums)
+                part[(size_t)(D * it.slot_j + d) * npad + it.j0 + x] = jw[0][d][x] + jw[1][d][x];
+        }
+    }
+}
+
+template <int MODEL, typename T, typename A, int NS>
+__global__ __launch_bounds__(2 * NS * kWave) void k_batch_sym_split(const PairItem *__restrict__ items, int n_soff,
+                                                                    const T *__restrict__ r0,
+                                                                    const T *__restrict__ r1,
+                                                                    const double *__restrict__ beps, int npad,
+                                                                    double *__restrict__ part)
+{
+    __shared__ double iw[NS][MODEL == MD_GRAV2D ? 2 : 1][kBatchSymTile];
+    __shared__ double jw[2][MODEL == MD_GRAV2D ? 2 : 1][kBatchSymTile];
+    const PairItem it = items[blockIdx.x];
+    if ((int)blockIdx.x < n_soff)
+        batch_sym_split_item<MODEL, T, A, true, NS>(it, r0, r1, beps, npad, part, iw, jw);
+    else
+        batch_sym_split_item<MODEL, T, A, false, NS>(it, r0, r1, beps, npad, part, iw, jw);
+}
+
+// Where an item is shared: with few tile pairs the launch is as long as one item, and as the
+// items end the SIMDs run empty; with many there is nothing to gain.  Measured md_step, us a
+// step, by k_batch_sym and shared (Ring FP64; Ring and 2D in MD_MIXED):
+//      33 tile pairs (8 realizations of 1000 .. 2000)    139 -> 62;  103 -> 43;  94 -> 39
+//     109 (8 of 96 .. 8170)                              141 -> 66;  105 -> 45;  97 -> 42
+//     881 (47 of 1222 .. 5616)                           304 -> 252; 187 -> 148; 148 -> 125
+//    3695 (128 of 1000 .. 8000)                          963 -> 872; 533 -> 480; 435 -> 386
+//   11672 (128 of 1000 .. 16384)                 2492 -> 2467; 1328 -> 1321; 1112 -> 1091
+//   23331 (256 of 1000 .. 16384)                 4882 -> 4862; 2585 -> 2595; 2206 -> 2206
+constexpr int kBatchSplit = 4;
+constexpr int kBatchSplitPairs = 16384;
+
 template <int MODEL, typename T, typename A>
 hipError_t sym_launch(md_ctx *c)
 {
@@ -371,8 +468,17 @@ hipError_t sym_launch(md_ctx *c)
     const PairItem *items = reinterpret_cast<const PairItem *>(B.d_sitems);
     constexpr int W = kBatchSymTile / (kWave * kSymIpl);
     const int ts = timed_begin(c, "k_batch_sym");
-    hipLaunchKernelGGL((k_batch_sym<MODEL, T, A, W>), dim3((unsigned)(B.n_soff + B.n_sdiag)), dim3(W * kWave), 0,
-                       c->stream, items, B.n_soff, r0, r0 + npad, B.d_eps, npad, c->part);
+    const dim3 grid((unsigned)(B.n_soff + B.n_sdiag));
+    bool split = false;
+    if constexpr (!std::is_same_v<A, AccKahan>) {
+        split = B.n_soff <= kBatchSplitPairs;
+        if (split)
+            hipLaunchKernelGGL((k_batch_sym_split<MODEL, T, A, kBatchSplit>), grid, dim3(2 * kBatchSplit * kWave), 0,
+                               c->stream, items, B.n_soff, r0, r0 + npad, B.d_eps, npad, c->part);
+    }
+    if (!split)
+        hipLaunchKernelGGL((k_batch_sym<MODEL, T, A, W>), grid, dim3(W * kWave), 0, c->stream, items, B.n_soff, r0,
+                           r0 + npad, B.d_eps, npad, c->part);
     const hipError_t err = hipGetLastError();
     timed_end(c, ts);
     return err;

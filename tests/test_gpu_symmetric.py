@@ -531,3 +531,34 @@ def test_split_tiles_and_sums(model, eps, prec, n):
     assert torch.equal(f, g)
     err = np.abs(host(f)[:, rows] - fo).max() / np.abs(fo).max()
     assert err < force_tol(model, prec, n, run=256), err
+
+
+# ------------------------------------------- ensembles, a tile pair shared --
+
+@pytest.mark.parametrize("model,prec", [(RING, md.FP64), (RING, md.MIXED), (GRAV2D, md.MIXED)])
+def test_shared_tile_pairs(model, prec):
+    """Ensembles of few tile pairs share each among eight wavefronts: realizations that end
+    on and beside a tile, a 256-i half and a 128-j run, against the oracle; repeatable; and
+    as in an ensemble of more than 16384 tile pairs, which are not shared: the same bits in
+    MD_MIXED (its FP32 runs are the same), FP64 rounding otherwise."""
+    sizes = [1, 64, 255, 257, 511, 512, 513, 576, 577, 640, 641, 769, 1024, 1025, 1664, 1665, 4000]
+    eps = EPS if model == GRAV2D else 0.01
+    q = np.concatenate([_state(model, n, 60 + n)[0] for n in sizes], axis=1)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    f = _batch_force(model, prec, q, off, [eps] * len(sizes), md.LAUNCH_SYMMETRIC)
+    assert np.array_equal(f, _batch_force(model, prec, q, off, [eps] * len(sizes), md.LAUNCH_SYMMETRIC))
+    for b, n in enumerate(sizes):
+        fb, qb = f[:, off[b]:off[b + 1]], q[:, off[b]:off[b + 1]]
+        if n == 1:
+            assert np.all(fb == 0.0)
+        else:
+            check(f"shared tile pairs model={model} prec={prec} N_b={n}", rel_inf(fb, oracle.force(model, qb, eps)),
+                  force_tol(model, prec, n, run=256))
+    more = [40_000] * 6  # 3081 tile pairs each
+    qm = np.concatenate([q] + [_state(model, n, 90 + k)[0] for k, n in enumerate(more)], axis=1)
+    om = np.concatenate([off, off[-1] + np.cumsum(more)])
+    g = _batch_force(model, prec, qm, om, [eps] * (len(om) - 1), md.LAUNCH_SYMMETRIC)[:, :off[-1]]
+    if prec == md.MIXED:
+        assert np.array_equal(f, g)
+    else:
+        assert rel_inf(f, g) < force_tol(model, prec, max(sizes))
