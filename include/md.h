@@ -194,8 +194,8 @@ int md_max_j_split(int64_t n);
  *                     the pair operands;
  *   MD_LAUNCH_FUSED   one launch per force evaluation (small N, where latency
  *                     dominates): a block owns one i tile and all its j ranges,
- *                     the partials are added in LDS and the same block runs the
- *                     stage on its own particles.
+ *                     adds the partials (through LDS and lane exchanges) and
+ *                     runs the stage on its own particles.
  *                     The j ranges, folds and order of additions are the staged
  *                     ones, so both forms give bit-identical results for the same
  *                     tiles.  Needs n <= 65536 and tiles a block can hold:
@@ -210,7 +210,7 @@ int md_max_j_split(int64_t n);
  *                     added to both particles with opposite signs (the terms of
  *                     the gradient of eq. 3 and of eq. 9 are odd in the pair's
  *                     difference), which halves the pair evaluations of the
- *                     all-pairs sum.  The particles are cut into tiles of 1024;
+ *                     all-pairs sum.  The particles are cut into tiles (md_get_sym_tile);
  *                     one block takes a tile pair (a, b), a < b, and writes its
  *                     i-side and j-side sums to separate slots (FP32 for
  *                     MD_MIXED, FP64 otherwise), the blocks

@@ -15,7 +15,9 @@
 // Reverse sweep: a drift q += a p is undone by lp += a lq, a kick p += h F(q) by
 // lq -= h H(q) lp (F = -grad V).  One fused elementwise kernel combines the
 // Hessian-vector partials, applies the kick and the next drift in reverse order,
-// and refreshes the operands of the next product.
+// and refreshes the operands of the next product.  The FP64 products of small systems
+// do all of that in the launch of the product (k_hvp_fused), those of larger ones take
+// each pair once for both particles (k_hvp_split, k_hvp_ring_split, k_hvp_sym).
 #include "device.h"
 #include "md_internal.h"
 #include "pair_terms.h"

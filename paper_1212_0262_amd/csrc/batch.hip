@@ -15,7 +15,7 @@
 // N_b^2 does not leave a tail.  Each item writes its own slot of the partial
 // buffer; the update kernel adds a particle's slots in chunk order, so results
 // do not depend on the schedule (bitwise reproducible).  The symmetric form
-// (k_batch_sym) instead takes tile pairs within each realization, each pair of
+// (k_batch_sym, and k_batch_sym_split where tile pairs are few) instead takes tile pairs within each realization, each pair of
 // particles evaluated once.
 #include "device.h"
 #include "energy_terms.h"

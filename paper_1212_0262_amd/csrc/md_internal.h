@@ -65,7 +65,7 @@ constexpr int64_t kFusedAutoN2D = 6144; // ... and up to this n for 2D gravity
 // 17.6 / 18.6, 5000 25.9 / 23.4 (2D).
 constexpr int64_t kFusedForceN = 2048, kFusedHvpN = 4096;
 constexpr int kSymTile = 1024;          // particles per tile of the symmetric form (4 waves x 64 x 4 i)
-constexpr int kBatchSymTile = 512;     // tiles of the ensembles' symmetric form (2 waves x 64 x 4 i)
+constexpr int kBatchSymTile = 512;     // tiles of the ensembles' symmetric form (2 i halves of 64 x 4)
 constexpr int kSymTileSmall = 512;      // ... for smaller n (2 waves x 64 x 4 i; sym_tile_n), and 256
                                         // (shared by up to 4 waves) for smaller n still
 constexpr int64_t kSymMinN = 2048;      // the symmetric form needs two tiles at least

@@ -11,14 +11,16 @@
 //   * j-split: the j range is cut into j_split pieces computed by different
 //     blocks (grid.y) so that small N still fills 256 CUs; the partial sums are
 //     added in a fixed order by the update kernel (deterministic).
-// The fused small-N stage (k_fused, below) keeps the same j ranges and order but
-// moves them into one block per i tile, streams j through LDS, and adds the
-// partials and runs the update in the same launch.
 //   * self pair: contributes exactly zero (2D: dx = dy = 0; Ring: the numerator
 //     sin(ti)cos(tj) - cos(ti)sin(tj) is formed from rounded products, without
 //     fused multiply-add, so it is exactly 0 at j = i), so no mask is needed.
 //   * ragged N: the j loop bound is uniform; lanes with i >= N load particle
 //     N-1 and do not store.
+// The fused small-N stage (k_fused, below) keeps the same j ranges and order but
+// moves them into one block per i tile, streams j through LDS, and adds the
+// partials and runs the update in the same launch.
+// The symmetric form (k_sym, k_sym_split) takes each pair once for both particles,
+// in tiles.
 // Accumulation policies (md_prec): FP32 partial per j-tile folded into FP64;
 // Kahan-compensated FP32 per pair; FP64 add per pair; plain FP64.
 #include "device.h"
