@@ -66,7 +66,7 @@ SYM_FLOPS_PER_EVAL = 14      # symmetric form, per pair evaluated: 2 sub, 2 FMA 
 PAIR_KERNEL_SRCS = [os.path.join(ROOT, "paper_1212_0262_amd", "csrc", f) for f in ("pair.hip", "pair_terms.h", "device.h")]
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "grav2d_pair_mixed_n262144_pmc.txt")
 HMF_TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hmf_pass_n1e7_pmc.txt")
-HMF_KERNEL_SRCS = [os.path.join(ROOT, "paper_1212_0262_amd", "csrc", f) for f in ("hmf.hip", "device.h")]
+HMF_KERNEL_SRCS = [os.path.join(ROOT, "paper_1212_0262_amd", "csrc", f) for f in ("hmf.hip", "hmf_terms.h", "device.h")]
 GOLDEN_DIR = os.path.join(ROOT, "tests", "golden")
 GATE_BAR = {"mixed": 1e-5, "fp64": 1e-6}   # |E - E_oracle| / |E0| at every report time
 
@@ -437,7 +437,7 @@ def hmf_workload(md, torch, args):
         "roofline": {"bound": "hbm", "achieved": round(fp["pass_algorithmic_GBs"], 1), "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": round(fp["pass_algorithmic_GBs"] / PEAK_HBM_GBS, 4),
                      "traffic": hmf_traffic_from_profile(),
-                     "kernel": "k_hmf_pass<double, 2, false>", "kernel_timed_as": fp["pass_timed_as"],
+                     "kernel": "k_hmf_pass<double, 2, 2, false>", "kernel_timed_as": fp["pass_timed_as"],
                      "kernel_ms_avg": round(fp["pass_ms_avg"], 5), "bytes_per_launch": HMF_N * HMF_BYTES["fp64"] // 3,
                      "step_GBs": round(fp["algorithmic_GBs"], 1),
                      "bytes_per_particle_step": HMF_BYTES["fp64"]},
