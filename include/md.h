@@ -352,8 +352,9 @@ int md_magnetization(md_ctx *c, const double *q, double *out_dev2);
  * form of eqs. 6 and 7: (H w)_i = w_i (cos q_i Mx + sin q_i My) - cos q_i Cw
  * - sin q_i Sw with Cw, Sw the averages of cos q_j w_j and sin q_j w_j, O(N).
  * MD_FP64 contexts whose force takes the symmetric launch form (md_get_launch; the Ring
- * up to n = 65536) take it for the product too: each pair evaluated once for both
- * particles, the per-tile sums added in a fixed order (reproducible bit for bit).
+ * up to n = 65536) take it for the product too, and 2D ones with MD_LAUNCH_AUTO from
+ * n = 6145 on: each pair evaluated once for both particles, the per-tile sums added in a
+ * fixed order (reproducible bit for bit).
  * Where md_step takes the fused form and n <= 4096 an FP64 product is one launch
  * (unless out overlaps q or w).
  *

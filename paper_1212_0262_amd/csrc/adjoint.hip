@@ -747,10 +747,13 @@ __global__ __launch_bounds__(kSplitWaves *kWave) void k_adj_update_split(
 }
 
 // The symmetric product (k_hvp_sym, k_hvp_split, k_hvp_ring_split) where the force takes the
-// symmetric form: FP64, 2D, and the Ring in tiles of 256.
+// symmetric form: FP64, 2D, and the Ring in tiles of 256; and the 2D one, whose pairs cost
+// twice the force's, from kSymHvpN under MD_LAUNCH_AUTO.
 bool hvp_sym(const md_ctx *c)
 {
-    if (c->prec != MD_FP64 || c->batch || launch_form(c) != MD_LAUNCH_SYMMETRIC) return false;
+    if (c->prec != MD_FP64 || c->batch) return false;
+    if (c->model == MD_GRAV2D && c->launch == MD_LAUNCH_AUTO && c->n >= kSymHvpN && c->n <= kSymMaxN) return true;
+    if (launch_form(c) != MD_LAUNCH_SYMMETRIC) return false;
     return c->model == MD_GRAV2D || sym_tile_n(c->model, c->prec, c->n) == kWave * kSymIpl;
 }
 

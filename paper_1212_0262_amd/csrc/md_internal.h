@@ -70,6 +70,13 @@ constexpr int kSymTileSmall = 512;      // ... for smaller n (2 waves x 64 x 4 i
                                         // (shared by up to 4 waves) for smaller n still
 constexpr int64_t kSymMinN = 2048;      // the symmetric form needs two tiles at least
 constexpr int64_t kSymMaxN = 1 << 20;   // and at most 1024 tiles (its partial slots: 8 d n^2 / 1024 bytes)
+// The 2D FP64 product takes the symmetric form from here under MD_LAUNCH_AUTO, before the
+// force does: its pair term is twice the force's against the same slot sums.  Up to
+// kFusedAutoN2D the built-in tiles (64 j ranges) have the staged product ahead (N = 5120 24.2 /
+// 26.1, 6144 32.2 / 35.7).  Measured, us per product and per reverse sweep of two steps with its
+// forward, staged -> symmetric: N = 6145 39.6 -> 39.3, 408 -> 387; 7168 43.2 -> 35.3, 496 -> 399; 9216
+// 59.3 -> 48.1, 672 -> 554; 12,288 97.4 -> 73.8, 1035 -> 851.
+constexpr int64_t kSymHvpN = kFusedAutoN2D + 1;
 // MD_LAUNCH_AUTO takes the symmetric form from this n (measured crossovers).  Ring FP64,
 // us per force evaluation, staged / symmetric: N = 4096 16.2 / 17.4, 5120 25.0 / 18.8,
 // 7168 37.7 / 26.5, 10,240 57.6 / 40.5.

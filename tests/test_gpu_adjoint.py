@@ -414,3 +414,32 @@ def test_ring_symmetric_product(n):
     for x, y in zip(*out):
         assert np.abs(x - y).max() <= 1e-11 * np.abs(y).max()
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [6145, 6400, 7169, 13_311])
+def test_2d_product_symmetric_before_the_force(n):
+    """2D FP64 under the automatic form, above the fused sizes: the staged force with the symmetric
+    product (ragged with pads), against the oracle; the bits of the symmetric form, also with out
+    in w's place; and a sweep as the staged form's."""
+    q, p = _state(GRAV2D, n, seed=n)
+    q[:, 5] = q[:, n - 1] = q[:, 300]
+    rng = np.random.default_rng(n)
+    w, lp = rng.normal(size=q.shape), rng.normal(size=q.shape)
+    ho = oracle.hvp(GRAV2D, q, w, 1e-3)
+    ctx = md.md_init(GRAV2D, md.FP64, n, 1e-3)
+    assert md.md_get_launch(ctx) == md.LAUNCH_STAGED
+    hw = md.md_hvp(ctx, dev(q), dev(w))
+    assert np.abs(host(hw) - ho).max() <= 1e-13 * np.abs(ho).max()
+    wd = dev(w)
+    assert torch.equal(hw, md.md_hvp(ctx, dev(q), wd, wd))
+    out = []
+    for mode in (md.LAUNCH_AUTO, md.LAUNCH_STAGED, md.LAUNCH_SYMMETRIC):
+        md.md_set_launch(ctx, mode)
+        assert torch.equal(md.md_hvp(ctx, dev(q), dev(w)), hw) or mode == md.LAUNCH_STAGED
+        a, b = dev(w), dev(lp)
+        md.md_step_vjp(ctx, dev(q), dev(p), 0.01, 2, a, b)
+        out.append((host(a), host(b)))
+    for other in out[1:]:
+        for x, y in zip(out[0], other):
+            assert np.abs(x - y).max() <= 1e-11 * np.abs(y).max()
+    ctx.close()
