@@ -608,13 +608,31 @@ BatchLayout batch_layout(int model, int prec, const Batch &B)
     return L;
 }
 
-Tiles batch_default_tiles(const Batch &B)
+// An ensemble's built-in tiles.  The forms that add in FP64 take one wavefront a work item (a
+// block of four waits for its slowest at every ragged end) and, the fewer the 64-i blocks, the
+// more j chunks (8 to 32, about 2^17 items at most): an item's uniform j loads leave it waiting for
+// memory, so the SIMDs need many.  MD_MIXED and MD_MIXED_KAHAN keep the chunks that fix their FP32
+// sums; realizations of at most 256 particles, one block each whose wavefronts share the j, keep
+// it too (100 of 64 .. 200: 11.9 us, 13.4 with one wavefront).  Measured, us per evaluation with
+// its update, four wavefronts and 8 chunks -> these, 2D FP64 and 2D MD_MIXED_PAIRF64: 8 realizations of
+// 1000 .. 2000 27.5 -> 19.8, 23.5 -> 19.2; 15 of 439 .. 6212 69 -> 51, 59 -> 45; 47 of 1222 .. 5616
+// 173 -> 160, 154 -> 139; 30 of 500 .. 16,000 381 -> 343, 339 -> 305; 128 of 1000 .. 8000 612 -> 584, 550 ->
+// 525; 1000 of 500 .. 2000 463 -> 442, 415 -> 392.  (400 of 5000 .. 16,384: 32 chunks 12,416, 8 12,107.)
+Tiles batch_default_tiles(const Batch &B, int prec)
 {
     Tiles t;
     t.ipl = 1;
-    t.waves = 4;
-    t.jsplit = B.smax < 8 ? B.smax : 8;
     t.jtile = 128;
+    if ((prec == MD_FP64 || prec == MD_MIXED_PAIRF64) && B.nmax > 256) {
+        int64_t blocks = 0;
+        for (int b = 0; b < B.nb; ++b) blocks += div_up(B.off[b + 1] - B.off[b], 64);
+        t.waves = 1;
+        t.jsplit = blocks <= 4096 ? 32 : blocks <= 8192 ? 16 : 8;
+    } else {
+        t.waves = 4;
+        t.jsplit = 8;
+    }
+    if (t.jsplit > B.smax) t.jsplit = B.smax;
     return t;
 }
 
@@ -912,7 +930,7 @@ int md_batch_init(md_ctx **out, int model, int prec, int nb, const int64_t *offs
     B->d_off = reinterpret_cast<int64_t *>(c->ws + L.off);
     B->d_sitems = c->ws + L.sitems;
     B->d_srows = c->ws + L.srows;
-    c->tiles = batch_default_tiles(*B);
+    c->tiles = batch_default_tiles(*B, prec);
     build_lists(*B, c->tiles);
     hipError_t e = hipGetDevice(&c->dev);
     const hipMemcpyKind h2d = hipMemcpyHostToDevice;
@@ -949,7 +967,7 @@ int md_set_tiles(md_ctx *c, int i_per_lane, int waves, int j_split, int j_tile)
 {
     if (!c) return MD_EINVAL;
     c->err.clear();
-    const Tiles d = c->batch ? batch_default_tiles(*c->batch) : default_tiles(c->model, c->prec, c->n);
+    const Tiles d = c->batch ? batch_default_tiles(*c->batch, c->prec) : default_tiles(c->model, c->prec, c->n);
     const int smax = c->batch ? c->batch->smax : max_j_split(c->n);
     Tiles t;
     t.ipl = i_per_lane ? i_per_lane : d.ipl;

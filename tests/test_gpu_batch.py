@@ -203,3 +203,28 @@ def test_batch_graph_replay_matches_eager():
         _ = (qd * 2.0).sum().item()  # eager work between replays
         np.testing.assert_array_equal(host(qg), ref[r][0])
         np.testing.assert_array_equal(host(pg), ref[r][1])
+
+
+@pytest.mark.parametrize("model,eps", [(RING, 0.01), (GRAV2D, 1e-3)])
+@pytest.mark.parametrize("prec", [md.FP64, md.MIXED_PAIRF64])
+@pytest.mark.parametrize("sizes,tiles", [([256] * 3 + [1], (1, 4, 4, 128)), ([257, 64, 1], (1, 1, 4, 128)),
+                                         ([2049, 63, 700], (1, 1, 32, 128)), ([2049] + [65] * 2100, (1, 1, 16, 128)),
+                                         ([1100] + [65] * 4200, (1, 1, 8, 128))])
+def test_built_in_tiles(model, eps, prec, sizes, tiles):
+    """The built-in tiles of the forms that add in FP64, by the ensemble's 64-i blocks: forces
+    of the largest, the last and a few realizations against the oracle."""
+    q, _, off = ensemble(model, sizes, seed=43)
+    ctx = md.md_batch_init(model, prec, off, eps)
+    assert md.md_get_tiles(ctx) == tiles
+    md.md_set_launch(ctx, md.LAUNCH_STAGED)
+    qd = dev(q)
+    f = torch.empty_like(qd)
+    md.md_force(ctx, qd, f)
+    fg, qs = split(host(f), off), split(q, off)
+    for b in {0, 1, len(sizes) // 2, len(sizes) - 1}:
+        if sizes[b] > 1:
+            check(f"built-in tiles model={model} prec={prec} N_b={sizes[b]}",
+                  rel_inf(fg[b], oracle.force(model, qs[b], eps)), force_tol(model, prec, sizes[b]))
+        else:
+            assert np.all(fg[b] == 0.0)
+    ctx.close()
