@@ -133,12 +133,13 @@ hipError_t launch_finite_flag(md_ctx *c, const double *vals, int count)
     return hipGetLastError();
 }
 
-// The i groups and j ranges of the pair sum: groups of 64 i (1 a lane) up to n = 16,384,
+// The i groups and j ranges of the pair sum: groups of 64 i (1 a lane) up to n = 32,768,
 // where blocks are few, of 256 (4 a lane: a window's LDS read serves four) above, and
 // j ranges of 256 (one 64-j window for each of a block's wavefronts) doubled while there
 // are more than kEnergyManyBlocks blocks, up to 4096, and within kEnergyBlocks partials.
 // Measured, md_energy in us, 1 / 4 a lane: 2D n = 4097 14.0 / 25.7, 8192 21.1 / 25.7,
-// 16,384 49.4 / 55.2; Ring FP64 18.9 / 32.9, 30.2 / 37.0, 84.7 / 89.2.  Blocks at most
+// 16,384 47.2 / 54.3, 20,000 58.8 / 81.0, 32,768 132 / 146, 65,536 476 / 458; Ring FP64 18.9 / 32.9,
+// 30.2 / 37.0, 79.4 / 90.3, 105 / 123, 246 / 266, 915 / 893.  Blocks at most
 // 8192 / 16,384 / 32,768 / 65,536 (4 a lane): 2D n = 65,536 490 / 512 / 545 / 622,
 // 262,144 6856 / 6346 / 6139 / 6100.
 struct EnergyGrid {
@@ -148,7 +149,7 @@ struct EnergyGrid {
 EnergyGrid energy_grid(int64_t n)
 {
     EnergyGrid g;
-    g.ipl = n > 16384 ? 4 : 1;
+    g.ipl = n > 32768 ? 4 : 1;
     const int64_t per = (int64_t)kWave * g.ipl;
     const int64_t ng = (n + per - 1) / per;
     int64_t jlen = 4 * kWave;

@@ -53,10 +53,17 @@ def energy(model, prec, q, p, eps):
     return out
 
 
-# groups of 64 i up to n = 16384, of 256 above; windows of 64 j, ranges of 256 and up
+# groups of 64 i (of 256 above n = 32768, below); windows of 64 j, ranges of 256 and up
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 256, 257, 321, 5003, 16384, 16385])
 @pytest.mark.parametrize("model,eps", [(md.GRAV2D, 1e-3), (md.RING, 1e-2), (md.RING, 1e-5)])
 def test_energy_sizes(n, model, eps):
+    q, p = inputs.uniform_state(model, n, seed=n)
+    check(model, q, p, eps, energy(model, md.FP64, q, p, eps))
+
+
+@pytest.mark.parametrize("model,eps", [(md.GRAV2D, 1e-3), (md.RING, 1e-2), (md.RING, 1e-5)])
+def test_energy_wide_groups(model, eps):
+    n = 32_769
     q, p = inputs.uniform_state(model, n, seed=n)
     check(model, q, p, eps, energy(model, md.FP64, q, p, eps))
 
