@@ -138,8 +138,8 @@ hipError_t launch_finite_flag(md_ctx *c, const double *vals, int count)
 // j ranges of 256 (one 64-j window for each of a block's wavefronts) doubled while there
 // are more than kEnergyManyBlocks blocks, up to 4096, and within kEnergyBlocks partials.
 // Measured, md_energy in us, 1 / 4 a lane: 2D n = 4097 14.0 / 25.7, 8192 21.1 / 25.7,
-// 16,384 47.2 / 54.3, 20,000 58.8 / 81.0, 32,768 132 / 146, 65,536 476 / 458; Ring FP64 18.9 / 32.9,
-// 30.2 / 37.0, 79.4 / 90.3, 105 / 123, 246 / 266, 915 / 893.  Blocks at most
+// 16,384 47.2 / 54.3, 20,000 58.8 / 81.0, 32,768 132 / 146, 65,536 476 / 458; Ring 22.5 / 43.1,
+// 39.8 / 59.3, 120 / 153, 171 / 204, 440 / 484, 1646 / 1705.  Blocks at most
 // 8192 / 16,384 / 32,768 / 65,536 (4 a lane): 2D n = 65,536 490 / 512 / 545 / 622,
 // 262,144 6856 / 6346 / 6139 / 6100.
 struct EnergyGrid {

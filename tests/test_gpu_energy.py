@@ -112,3 +112,39 @@ def test_batch_energy_sizes(model, eps):
     again = md.md_batch_init(model, md.FP64, off, eps)
     assert torch.equal(md.md_energy(again, dev(q), dev(p)).cpu(), torch.from_numpy(out))
     again.close()
+
+
+@pytest.mark.parametrize("eps", [1e-12, 1e-6, 1e-4, 1e-2, 1.0])
+def test_ring_pair_energy_is_relative(eps):
+    """One pair of every separation, 1e-7 to pi: V to 8 roundings of 2^-53 relative, however close
+    the pair and small eps (a chord off by 2^-53 absolutely is 1e-14 out at eps = 1e-4).  The
+    roundings: ti - tj 1, the chord 2, the root 2 with its operand, the sums' scale and the
+    prefactor 2.5."""
+    nb = 2000
+    rng = np.random.default_rng(3)
+    q = np.empty((1, 2 * nb))
+    q[0, ::2] = rng.uniform(-np.pi / 2, np.pi / 2, nb)
+    q[0, 1::2] = q[0, ::2] + 10 ** rng.uniform(-7, 0, nb) * np.sign(-q[0, ::2])
+    q[0, 1::40] = -q[0, ::40] * rng.uniform(0, 1, nb // 20)
+    wide = q.astype(np.longdouble)
+    h = np.sin((wide[0, ::2] - wide[0, 1::2]) / 2)
+    want = -1 / (np.sqrt(2 * h * h + np.longdouble(eps)) * np.sqrt(np.longdouble(2)) * 2)
+    ctx = md.md_batch_init(md.RING, md.FP64, 2 * np.arange(nb + 1), eps)
+    got = host(md.md_energy(ctx, dev(q), dev(np.zeros_like(q))))[:, 1]
+    ctx.close()
+    err = float(np.abs(got / want - 1).max())
+    k = int(np.abs(got / want - 1).argmax())
+    print(f"eps={eps}: err {err:.2e}", flush=True)
+    assert err < 8 * 2.0 ** -53, err
+    one = energy(md.RING, md.MIXED, q[:, 2 * k:2 * k + 2], np.zeros((1, 2)), eps)
+    assert one[1] == got[k]
+
+
+@pytest.mark.parametrize("angle", [2.0 ** 29 - 1, 2.0 ** 29 + 1, 2.0 ** 32])
+def test_ring_energy_past_the_reduction(angle):
+    """Angles on both sides of the range of the chord's reduction, among the i, the j and both
+    (multiples of 2^-20: every difference is exact)."""
+    q, p = inputs.uniform_state(md.RING, 700, seed=8)
+    q = np.round(q * 2.0 ** 20) / 2.0 ** 20
+    q[0, [3, 299, 650]] = (angle, -angle, angle)
+    check(md.RING, q, p, 1e-2, energy(md.RING, md.FP64, q, p, 1e-2))
