@@ -78,8 +78,11 @@ constexpr int64_t kSymMaxN = 1 << 20;   // and at most 1024 tiles (its partial s
 // 59.3 -> 48.1, 672 -> 554; 12,288 97.4 -> 73.8, 1035 -> 851.
 constexpr int64_t kSymHvpN = kFusedAutoN2D + 1;
 // MD_LAUNCH_AUTO takes the symmetric form from this n (measured crossovers).  Ring FP64,
-// us per force evaluation, staged / symmetric: N = 4096 16.2 / 17.4, 5120 25.0 / 18.8,
-// 7168 37.7 / 26.5, 10,240 57.6 / 40.5.
+// us per force evaluation, staged / symmetric: N = 4096 16.2 / 17.4, 4608 21.4 / 18.0,
+// 7168 36.0 / 25.2, 9216 48.2 / 33.2.
+// Ring FP64 below kRingExactN, where MD_LAUNCH_AUTO once took the staged form: the symmetric
+// form keeps its exact zero for particles at the same angle (k_sym_split in pair.hip).
+constexpr int64_t kRingExactN = 10240;
 inline int64_t sym_auto_n(int model, int prec)
 {
     if (model != MD_RING)

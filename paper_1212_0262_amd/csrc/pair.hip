@@ -343,10 +343,14 @@ __global__ __launch_bounds__(W * kWave) void k_sym(const T *__restrict__ r0, con
 // N = 13,312 69 -> 54, 16,384 84 -> 72, 20,480 123 -> 105, 32,768 256 -> 248; 2D mixed
 // 16,384 51 -> 44, 20,480 73 -> 63; Ring FP64 13,312 80 -> 59, 20,480 142 -> 118, 32,768
 // 308 -> 287; Ring mixed 16,384 64 -> 52.
+// EXACT (Ring FP64, below kRingExactN): the numerator that is exactly 0 for particles at the same
+// angle, as the staged form's (which larger systems leave for one FMA's rounding):
+// one more FP64 instruction an evaluation.  Ring FP64, us a step, one FMA / exact / staged:
+// N = 4608 52.4 / 54.0 / 64.1, 7168 73.0 / 75.7 / 108, 9216 95.9 / 99.6 / 145.
 template <typename A>
 constexpr int kSymSplit = std::is_same_v<A, AccKahan> ? 1 : kJW32<A> ? 2 : 4;
 
-template <int MODEL, typename T, typename A, bool SYM, int NS>
+template <int MODEL, typename T, typename A, bool SYM, int NS, bool EXACT>
 __device__ __forceinline__ void sym_split_block(const T *__restrict__ r0, const T *__restrict__ r1, int n, int npad,
                                                 T e, sym_slot_t<A> *__restrict__ part, int a, int b,
                                                 double (&lds)[NS][MODEL == MD_GRAV2D ? 2 : 1][kWave * kSymIpl])
@@ -371,8 +375,9 @@ __device__ __forceinline__ void sym_split_block(const T *__restrict__ r0, const 
         for (int d = 0; d < D; ++d) part[(size_t)(D * a + d) * npad + j0 + blk * kWave + m] = (sym_slot_t<A>)sj[d].get();
     };
     constexpr bool kShare = MODEL == MD_GRAV2D && sizeof(T) == 8;  // as sym_block
-    if (!kShare || (b + 1) * TILE > n) sym_tile<MODEL, T, A, SYM, false>(u0, u1, e, lane, NB, load, jsum, acc);
-    else sym_tile<MODEL, T, A, SYM, kShare>(u0, u1, e, lane, NB, load, jsum, acc);
+    constexpr bool kExact = !SYM || EXACT;
+    if (!kShare || (b + 1) * TILE > n) sym_tile<MODEL, T, A, SYM, false, kExact>(u0, u1, e, lane, NB, load, jsum, acc);
+    else sym_tile<MODEL, T, A, SYM, kShare, kExact>(u0, u1, e, lane, NB, load, jsum, acc);
     if constexpr (NS == 1) {
 #pragma unroll
         for (int k = 0; k < kSymIpl; ++k)
@@ -396,7 +401,7 @@ __device__ __forceinline__ void sym_split_block(const T *__restrict__ r0, const 
     }
 }
 
-template <int MODEL, typename T, typename A>
+template <int MODEL, typename T, typename A, bool EXACT>
 __global__ __launch_bounds__(kSymSplit<A> *kWave) void k_sym_split(const T *__restrict__ r0, const T *__restrict__ r1,
                                                                    int n, int npad, int ntile, T e,
                                                                    sym_slot_t<A> *__restrict__ part)
@@ -407,9 +412,9 @@ __global__ __launch_bounds__(kSymSplit<A> *kWave) void k_sym_split(const T *__re
     if (t < noff) {
         int a, b;
         sym_tile_pair(t, ntile, a, b);
-        sym_split_block<MODEL, T, A, true, NS>(r0, r1, n, npad, e, part, a, b, lds);
+        sym_split_block<MODEL, T, A, true, NS, EXACT>(r0, r1, n, npad, e, part, a, b, lds);
     } else {
-        sym_split_block<MODEL, T, A, false, NS>(r0, r1, n, npad, e, part, t - noff, t - noff, lds);
+        sym_split_block<MODEL, T, A, false, NS, EXACT>(r0, r1, n, npad, e, part, t - noff, t - noff, lds);
     }
 }
 
@@ -431,9 +436,12 @@ hipError_t sym_launch(md_ctx *c)
     else if (tile == kSymTileSmall)
         hipLaunchKernelGGL((k_sym<MODEL, T, A, 2>), dim3((unsigned)nblk), dim3(2 * kWave), 0, c->stream, ops,
                            ops + npad, (int)c->n, npad, ntile, e, slots);
+    else if (MODEL == MD_RING && sizeof(T) == 8 && c->n < kRingExactN)
+        hipLaunchKernelGGL((k_sym_split<MODEL, T, A, MODEL == MD_RING && sizeof(T) == 8>), dim3((unsigned)nblk),
+                           dim3(kSymSplit<A> * kWave), 0, c->stream, ops, ops + npad, (int)c->n, npad, ntile, e, slots);
     else
-        hipLaunchKernelGGL((k_sym_split<MODEL, T, A>), dim3((unsigned)nblk), dim3(kSymSplit<A> * kWave), 0, c->stream,
-                           ops, ops + npad, (int)c->n, npad, ntile, e, slots);
+        hipLaunchKernelGGL((k_sym_split<MODEL, T, A, false>), dim3((unsigned)nblk), dim3(kSymSplit<A> * kWave), 0,
+                           c->stream, ops, ops + npad, (int)c->n, npad, ntile, e, slots);
     const hipError_t err = hipGetLastError();
     timed_end(c, ts);
     return err;

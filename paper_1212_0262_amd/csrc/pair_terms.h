@@ -386,7 +386,10 @@ __host__ __device__ constexpr T sym_pad()
 // number (particles closer than about 1e38 to each other, eps in [1e-75, 1e75],
 // the range md_init takes) and no pad particle among the operands (the pads' s
 // would overflow the product), so blocks that hold pads take SHARE = false.
-template <int MODEL, typename T, typename A, bool SYM, bool SHARE = false, typename Load, typename JSum>
+// EXACT (Ring): the numerator that is exactly 0 for two particles at the same angle; a
+// diagonal tile needs it (i with itself).
+template <int MODEL, typename T, typename A, bool SYM, bool SHARE = false, bool EXACT = !SYM, typename Load,
+          typename JSum>
 __device__ __forceinline__ void sym_tile(const T (&u0)[kSymIpl], const T (&u1)[kSymIpl], T e, int lane, int nblk,
                                          Load &&load, JSum &&jsum, A (&acc)[MODEL == MD_GRAV2D ? 2 : 1][kSymIpl])
 {
@@ -451,7 +454,7 @@ __device__ __forceinline__ void sym_tile(const T (&u0)[kSymIpl], const T (&u1)[k
                     }
                 } else {
                     T p, q;  // a tile pair meets each pair once, never i with itself
-                    ring_factors<T, !SYM>(u0[k], u1[k], v0, v1, e, p, q);
+                    ring_factors<T, EXACT>(u0[k], u1[k], v0, v1, e, p, q);
                     acc[0][k].add(p, q);
                     if (SYM) sj[0].add(-p, q);
                 }

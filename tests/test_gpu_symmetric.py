@@ -474,6 +474,19 @@ def test_ring_fp64_symmetric_coincident_angles():
     assert np.abs(fs).max() <= 1.01 * bound
 
 
+@pytest.mark.parametrize("n", [2048, 4608, 5001, 10_239])
+def test_ring_fp64_coincident_angles_are_exact_zeros(n):
+    """Ring FP64 of fewer than 10,240 particles: the forces of an all-equal state are exactly 0 in
+    the automatic and in the symmetric form, as in the staged one."""
+    q = np.full((1, n), 0.7)
+    for launch in (md.LAUNCH_AUTO, md.LAUNCH_SYMMETRIC, md.LAUNCH_STAGED):
+        ctx = md.md_init(RING, md.FP64, n, 0.01)
+        md.md_set_launch(ctx, launch)
+        f = torch.empty_like(dev(q))
+        assert torch.all(md.md_force(ctx, dev(q), f) == 0.0), launch
+        ctx.close()
+
+
 def test_ring_fp32_symmetric_coincident_angles():
     """Ring FP32 forms, symmetric launch: a tile pair forms the half-angle
     numerator a = 2 sin(d/2) as one product and one FMA (one rounding fewer than
