@@ -176,7 +176,11 @@ int md_set_stream(md_ctx *c, void *hip_stream);
  *                in a fixed order: 1 .. md_max_j_split(n)
  *   j_tile       j per FP32 partial sum before the FP64 fold (MD_MIXED):
  *                a multiple of 16 in [16, 4096]
- * 0 in any field keeps the built-in choice for this n.  MD_HMF ignores it.
+ * 0 in any field keeps the built-in choice for this n; 0 in all of them gives the
+ * built-in tiles back.  MD_HMF ignores it.
+ * Tiles set here also keep MD_LAUNCH_AUTO and the Hessian-vector products to the forms
+ * that they apply to: Ring MD_FP64 steps stay staged up to n = 10239, the Ring's FP64
+ * products at every n, the 2D ones below MD_SYMMETRIC_AUTO_N.
  */
 int md_set_tiles(md_ctx *c, int i_per_lane, int waves, int j_split, int j_tile);
 
@@ -245,7 +249,8 @@ int md_max_j_split(int64_t n);
  *                     or MD_FP64, MD_SYMMETRIC_AUTO_N_COMP with the
  *                     compensated forms; for the Ring MD_SYMMETRIC_AUTO_N_RING
  *                     with the FP32 forms and MD_SYMMETRIC_AUTO_N_RING64 with
- *                     MD_FP64: measured crossovers on MI355X), else staged;
+ *                     MD_FP64: measured crossovers on MI355X; for tiles the caller
+ *                     has set see md_set_tiles), else staged;
  *                     for ensembles, symmetric when it applies and their tile
  *                     pairs a < b outnumber their diagonal tiles.
  * md_get_launch returns the form md_step will take (STAGED, FUSED or
@@ -352,11 +357,11 @@ int md_magnetization(md_ctx *c, const double *q, double *out_dev2);
  * form of eqs. 6 and 7: (H w)_i = w_i (cos q_i Mx + sin q_i My) - cos q_i Cw
  * - sin q_i Sw with Cw, Sw the averages of cos q_j w_j and sin q_j w_j, O(N).
  * MD_FP64 contexts whose force takes the symmetric launch form (md_get_launch; the Ring
- * up to n = 65536) take it for the product too, and 2D ones with MD_LAUNCH_AUTO from
- * n = 6145 on: each pair evaluated once for both particles, the per-tile sums added in a
+ * up to n = 65536 and with built-in tiles) take it for the product too, and 2D ones with MD_LAUNCH_AUTO from
+ * n = 6145 on (unless md_set_tiles has set tiles): each pair evaluated once for both particles, the per-tile sums added in a
  * fixed order (reproducible bit for bit).
  * Where md_step takes the fused form and n <= 4096 an FP64 product is one launch
- * (unless out overlaps q or w).
+ * (unless out overlaps q or w, or md_set_tiles has set tiles).
  *
  * md_step_vjp: reverse-mode derivative of nsteps Yoshida steps started from the
  * state (q0, p0) (e.g. a checkpoint kept during the forward run).  On entry

@@ -748,13 +748,15 @@ __global__ __launch_bounds__(kSplitWaves *kWave) void k_adj_update_split(
 
 // The symmetric product (k_hvp_sym, k_hvp_split, k_hvp_ring_split) where the force takes the
 // symmetric form: FP64, 2D, and the Ring in tiles of 256; and the 2D one, whose pairs cost
-// twice the force's, from kSymHvpN under MD_LAUNCH_AUTO.
+// twice the force's, from kSymHvpN under MD_LAUNCH_AUTO.  The Ring's and the latter not where
+// the caller has set tiles: the staged product runs with them.
 bool hvp_sym(const md_ctx *c)
 {
     if (c->prec != MD_FP64 || c->batch) return false;
-    if (c->model == MD_GRAV2D && c->launch == MD_LAUNCH_AUTO && c->n >= kSymHvpN && c->n <= kSymMaxN) return true;
+    if (c->model == MD_GRAV2D && c->launch == MD_LAUNCH_AUTO && !c->tiles_set && c->n >= kSymHvpN && c->n <= kSymMaxN)
+        return true;
     if (launch_form(c) != MD_LAUNCH_SYMMETRIC) return false;
-    return c->model == MD_GRAV2D || sym_tile_n(c->model, c->prec, c->n) == kWave * kSymIpl;
+    return c->model == MD_GRAV2D || (!c->tiles_set && sym_tile_n(c->model, c->prec, c->n) == kWave * kSymIpl);
 }
 
 int prep_kind(const md_ctx *c)
@@ -804,10 +806,12 @@ hipError_t hvp_launch(md_ctx *c, const void *qsrc, const void *wsrc, dim3 grid, 
 
 }  // namespace
 
-// The fused product applies: FP64, a single system that takes the fused form, small n.
+// The fused product applies: FP64, a single system that takes the fused form, small n.  It has
+// its own 64 j ranges: tiles that the caller has set keep the staged product.
 bool hvp_fused(const md_ctx *c)
 {
-    return c->prec == MD_FP64 && c->n <= kFusedHvpN && !c->batch && c->model != MD_HMF && launch_form(c) == MD_LAUNCH_FUSED;
+    return c->prec == MD_FP64 && c->n <= kFusedHvpN && !c->batch && !c->tiles_set && c->model != MD_HMF &&
+           launch_form(c) == MD_LAUNCH_FUSED;
 }
 
 hipError_t launch_hvp_fused(md_ctx *c, const double *pos, const double *w_in, int w_stride, int flags, double h,

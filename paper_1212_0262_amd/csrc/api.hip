@@ -211,7 +211,9 @@ int form_of(const md_ctx *c)
         const bool s = c->launch == MD_LAUNCH_SYMMETRIC || (c->launch == MD_LAUNCH_AUTO && batch_sym_auto(*c->batch));
         return s && c->batch->sym ? MD_LAUNCH_SYMMETRIC : MD_LAUNCH_STAGED;
     }
-    if (c->launch == MD_LAUNCH_SYMMETRIC || (c->launch == MD_LAUNCH_AUTO && c->n >= sym_auto_n(c->model, c->prec)))
+    int64_t auto_n = sym_auto_n(c->model, c->prec);
+    if (c->tiles_set && c->model == MD_RING && c->prec == MD_FP64) auto_n = kRingExactN;
+    if (c->launch == MD_LAUNCH_SYMMETRIC || (c->launch == MD_LAUNCH_AUTO && c->n >= auto_n))
         if (sym_ok(c)) return MD_LAUNCH_SYMMETRIC;
     if (c->launch == MD_LAUNCH_STAGED || c->launch == MD_LAUNCH_SYMMETRIC || !fused_ok(c, c->tiles))
         return MD_LAUNCH_STAGED;
@@ -986,6 +988,7 @@ int md_set_tiles(md_ctx *c, int i_per_lane, int waves, int j_split, int j_tile)
         return fail(c, MD_EUNSUPPORTED, "the fused launch needs j_split / (lane groups) <= %d wavefronts and "
                     "i_per_lane * d * 512 <= %d / wavefronts LDS bytes", kFusedMaxWaves, kFusedLdsBytes);
     c->tiles = t;
+    c->tiles_set = i_per_lane || waves || j_split || j_tile;
     if (c->batch) {
         build_lists(*c->batch, t);
         DeviceGuard g(c->dev);

@@ -81,7 +81,8 @@ constexpr int64_t kSymHvpN = kFusedAutoN2D + 1;
 // us per force evaluation, staged / symmetric: N = 4096 16.2 / 17.4, 4608 21.4 / 18.0,
 // 7168 36.0 / 25.2, 9216 48.2 / 33.2.
 // Ring FP64 below kRingExactN, where MD_LAUNCH_AUTO once took the staged form: the symmetric
-// form keeps its exact zero for particles at the same angle (k_sym_split in pair.hip).
+// form keeps its exact zero for particles at the same angle (k_sym_split in pair.hip), and
+// tiles that the caller has set keep the staged form itself.
 constexpr int64_t kRingExactN = 10240;
 inline int64_t sym_auto_n(int model, int prec)
 {
@@ -169,6 +170,7 @@ struct md_ctx {
     bool forced = false;                 // md_force has run (md_step needs f = force(q))
     bool checkable = false;              // an energy or magnetization has set the finiteness flag
     md::Tiles tiles;
+    bool tiles_set = false;      // md_set_tiles gave them (any field): the forms they apply to are kept
     md::Batch *batch = nullptr;  // non-null for a batched ensemble (owned)
     md::Timing *timing = nullptr;  // non-null while md_timing_begin is on (owned)
     std::string err;

@@ -251,6 +251,54 @@ def test_launch_form_and_refusals():
         c.close()
 
 
+@pytest.mark.parametrize("model,n,tiles", [(RING, 5000, (2, 4, 16, 128)), (RING, 10_239, (1, 2, 32, 128)),
+                                           (GRAV2D, 7000, (2, 4, 16, 128)), (GRAV2D, 13_311, (1, 1, 8, 128)),
+                                           (GRAV2D, 900, (1, 4, 8, 128)), (RING, 4096, (2, 4, 16, 128))])
+def test_set_tiles_act_under_auto(model, n, tiles):
+    """MD_FP64 under the automatic form: tiles that the caller sets are the ones the steps and the
+    products run with (the staged or, for small n, fused step's bits and the staged product's);
+    with the built-in tiles given back, what a new context does."""
+    eps = 0.01 if model == RING else 1e-3
+    q = dev(inputs.ring_waterbag(n, seed=n)[0] if model == RING else inputs.grav2d_disk(n, seed=n)[0])
+    w = torch.flip(q, [1])
+
+    def run(ctx):
+        f = md.md_force(ctx, q, torch.empty_like(q))
+        a = [q.clone(), torch.zeros_like(q), f]
+        md.md_step(ctx, *a, 0.01, 1)
+        return a + [md.md_hvp(ctx, q, w)]
+
+    auto, staged, plain = (md.md_init(model, md.FP64, n, eps) for _ in range(3))
+    md.md_set_tiles(auto, *tiles)
+    assert md.md_get_launch(auto) in (md.LAUNCH_STAGED, md.LAUNCH_FUSED)
+    md.md_set_launch(staged, md.LAUNCH_STAGED)
+    md.md_set_tiles(staged, *tiles)
+    for x, y in zip(run(auto), run(staged)):
+        assert torch.equal(x, y)
+    md.md_set_tiles(auto)
+    assert md.md_get_launch(auto) == md.md_get_launch(plain)
+    for x, y in zip(run(auto), run(plain)):
+        assert torch.equal(x, y)
+    for c in (auto, staged, plain):
+        c.close()
+
+
+def test_set_tiles_act_on_the_ring_product():
+    """Ring MD_FP64 where the steps are symmetric: the product runs staged with the caller's tiles."""
+    n, tiles = 12_000, (2, 4, 16, 128)
+    q = dev(inputs.ring_waterbag(n, seed=n)[0])
+    w = torch.flip(q, [1])
+    out = []
+    for launch in (md.LAUNCH_AUTO, md.LAUNCH_SYMMETRIC, md.LAUNCH_STAGED):
+        ctx = md.md_init(RING, md.FP64, n, 0.01)
+        md.md_set_tiles(ctx, *tiles)
+        md.md_set_launch(ctx, launch)
+        assert md.md_get_launch(ctx) == (launch or md.LAUNCH_SYMMETRIC)
+        out.append(md.md_hvp(ctx, q, w))
+        ctx.close()
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[2])
+
+
 def test_symmetric_step_graph_replays():
     n, dt = 5000, 0.01
     q0, p0 = inputs.grav2d_disk(n, seed=31)
