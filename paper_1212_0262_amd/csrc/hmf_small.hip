@@ -265,16 +265,20 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_hvp(const double
 // The reverse sweep over nsteps recorded steps (reverse_hmf in api.hip): products at
 // P_3n, .., P_1, then at q0 (the position before the first drift), each followed by its
 // kick(s) and, but for the last, the drift before it.  pos: P_1 .. P_3n, stride apart.
+// A run of many steps is cut into several sweeps, the last steps' first: last says whether
+// P_3n ends the run (else the kick of the step after it comes too); with q0 null the run
+// starts earlier and the product there is the next sweep's first.
 template <int P>
 __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_vjp(const double *__restrict__ q0,
                                                                  const double *__restrict__ pos, size_t stride, int n,
-                                                                 int threads, StepCoef a, int64_t nsteps, double *__restrict__ lq,
-                                                                 double *__restrict__ lp)
+                                                                 int threads, StepCoef a, int nsteps, int last,
+                                                                 double *__restrict__ lq, double *__restrict__ lp)
 {
     const int B = small_block<P>(threads);
     __shared__ double lds[2][4][kSmallWaves];
     double x[P], w[P], th[P], s[P], c[P], v[4];
-    auto load = [&](int64_t m) {  // positions m (0 = q0), for the next product
+    const int top = 3 * nsteps, bottom = q0 ? 0 : 1;
+    auto load = [&](int m) {  // positions m (0 = q0), for the next product
         const double *__restrict__ src = m > 0 ? pos + (size_t)(m - 1) * stride : q0;
 #pragma unroll
         for (int k = 0; k < P; ++k) {
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_vjp(const double
             th[k] = i < n ? src[i] : 0.0;
         }
     };
-    load(3 * nsteps);
+    load(top);
 #pragma unroll
     for (int k = 0; k < P; ++k) {
         const int i = threadIdx.x + k * B;
@@ -290,12 +294,12 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_vjp(const double
         w[k] = i < n ? lp[i] : 0.0;
     }
     int r = 0;  // m mod 3
-    for (int64_t m = 3 * nsteps; m >= 0; --m, r = r == 0 ? 2 : r - 1) {
+    for (int m = top; m >= bottom; --m, r = r == 0 ? 2 : r - 1) {
         sincos_n(th, s, c);
-        if (m > 0) load(m - 1);  // in flight under the sums
+        if (m > bottom) load(m - 1);  // in flight under the sums
         small_hvp_means(s, c, w, n, B, lds[m & 1], v);
         const double kick = r == 0 ? a.b0 : a.b1;
-        const bool two = r == 0 && m > 0 && m < 3 * nsteps;  // the kicks of two steps at one position
+        const bool two = r == 0 && m > 0 && (m < top || !last);  // the kicks of two steps at one position
 #pragma unroll
         for (int k = 0; k < P; ++k) {
             const double hw = small_hw(s[k], c[k], w[k], v);
@@ -397,10 +401,19 @@ hipError_t launch_hmf_small_vjp(md_ctx *c, double b0, double b1, double d0, doub
 {
     const StepCoef a{b0, b1, d0, d1};
     const int n = (int)c->n;
+    hipError_t err = hipSuccess;
+    for (int64_t end = nsteps; end > 0 && err == hipSuccess;) {
+        const int k = (int)(end < kHmfSmallSteps ? end : kHmfSmallSteps);
+        const int64_t begin = end - k;
+        const double *const from = begin == 0 ? q0 : nullptr;
+        const double *const at = pos + (size_t)(3 * begin) * stride;
 #define K(P_) k_hmf_small_vjp<P_>
-    MD_SMALL(K, q0, pos, stride, n, B, a, nsteps, lq, lp);
+        MD_SMALL(K, from, at, stride, n, B, a, k, (int)(end == nsteps), lq, lp);
 #undef K
-    return hipGetLastError();
+        err = hipGetLastError();
+        end = begin;
+    }
+    return err;
 }
 
 }  // namespace md

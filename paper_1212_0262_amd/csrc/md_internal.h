@@ -52,7 +52,7 @@ constexpr int kMLimbs = 4;  // sum cos: 2^-32 and 2^-64 limbs; sum sin: the same
 constexpr int kMWords = 3 * kMSlots * kMLimbs;
 constexpr int kHmfInPassM = 1024;  // grids of at most this many blocks use the fixed-point sums
 constexpr int64_t kHmfSmallN = 8192;      // HMF systems one workgroup takes whole (hmf_small.hip)
-constexpr int64_t kHmfSmallSteps = 4096;  // most steps of one of its launches (some 15 ms)
+constexpr int64_t kHmfSmallSteps = 4096;  // most steps of one of its launches, also a sweep's (up to 0.1 s)
 constexpr int kEnergyBlock = 256;
 constexpr int64_t kFusedMaxN = 65536;   // contexts up to this n carry the fused stage's operand buffers
 constexpr int kFusedMaxWaves = 16;      // wavefronts per fused block

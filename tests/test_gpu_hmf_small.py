@@ -5,6 +5,8 @@ form that larger systems take.
 Tolerances: FP64 trajectories 1e-11 and energies 1e-12 of K + |V| + n/2, the FP32 state
 1e-5 (positions and momenta of order 1, 2^-24 a stage), as the parity tests.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -123,4 +125,55 @@ def test_many_steps_and_graph():
         md.md_step(ctx, *want, 0.01, 50)
         torch.cuda.synchronize()
         assert all(torch.equal(x, y) for x, y in zip(c, want))
+    ctx.close()
+
+
+def test_many_steps_recorded_and_swept():
+    """More steps than one launch takes: the recording, the recomputation and the sweep, each against
+    two halves of the run, bit for bit."""
+    n, dt, head, tail = 100, 0.01, 4097, 4098
+    q0, p0 = (dev(x) for x in inputs.hmf_waterbag(n, seed=9))
+    ctx = md.md_init(md.HMF, md.FP64, n)
+    lq, lp = (torch.randn(1, n, dtype=torch.float64, device=q0.device) for _ in range(2))
+    whole = [q0.clone(), p0.clone(), md.md_force(ctx, q0, torch.empty_like(q0))]
+    halves = [x.clone() for x in whole]
+    stage = md.md_step_record(ctx, *whole, dt, head + tail)
+    first = md.md_step_record(ctx, *halves, dt, head)
+    mid = [x.clone() for x in halves]
+    second = md.md_step_record(ctx, *halves, dt, tail)
+    assert all(torch.equal(x, y) for x, y in zip(whole, halves))
+    assert torch.equal(stage, torch.cat([first, second]))
+    a, b, c, d, e, f = (x.clone() for x in (lq, lp) * 3)
+    md.md_step_vjp_recorded(ctx, q0, dt, head + tail, a, b, stage)
+    md.md_step_vjp_recorded(ctx, mid[0], dt, tail, c, d, second)
+    md.md_step_vjp_recorded(ctx, q0, dt, head, c, d, first)
+    md.md_step_vjp(ctx, q0, p0, dt, head + tail, e, f)
+    assert torch.equal(a, e) and torch.equal(b, f)
+    # the halves' sweeps apply the joint's two kicks from two equal products, the whole run's
+    # from one: the same sums, the same bits
+    assert torch.equal(a, c) and torch.equal(b, d)
+    ctx.close()
+
+
+@pytest.mark.parametrize("steps,launches", [(4096, 1), (4097, 2), (8193, 3)])
+def test_a_launch_takes_a_bounded_number_of_steps(steps, launches):
+    """The kernels of md_step and md_step_vjp_recorded, counted in a captured graph."""
+    n = 64
+    ctx = md.md_init(md.HMF, md.FP64, n)
+    q, p = (dev(x) for x in inputs.hmf_waterbag(n, seed=9))
+    f = md.md_force(ctx, q, torch.empty_like(q))
+    stage = torch.zeros(md.md_record_stage_bytes(ctx, steps), dtype=torch.uint8, device=q.device)
+    lq, lp = torch.zeros_like(q), torch.zeros_like(q)
+    s = torch.cuda.Stream()
+    md.md_set_stream(ctx, s)
+    s.wait_stream(torch.cuda.current_stream())
+    for call in (lambda: md.md_step(ctx, q, p, f, 1e-3, steps),
+                 lambda: md.md_step_vjp_recorded(ctx, q, 1e-3, steps, lq, lp, stage)):
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g, stream=s):
+            call()
+        nodes = ctypes.c_size_t(0)
+        assert md.load().hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+        assert nodes.value == launches
+    torch.cuda.synchronize()
     ctx.close()
