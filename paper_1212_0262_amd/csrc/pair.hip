@@ -696,13 +696,30 @@ __global__ __launch_bounds__(64) void k_update_vec(const SlotT *__restrict__ par
 // The arguments of k_fused that only its end needs: the kernel reads them from the argument
 // segment itself, once the operands' loads are out.  Left to the compiler, their load (a
 // memory round trip) is waited for before the first window's.  They lie at kLateOffset: the
-// arguments before take 24 + 32 bytes and e.
+// arguments before take 24 + 32 bytes and e (checked against the kernel's type at its launch).
 struct FusedLate {
     void *out;
     double *f, *snap;
     double pref, kick1, kick2, drift;
 };
-constexpr int kLateOffset = 64;
+constexpr size_t kLateOffset = 64;
+
+// Whether a kernel's last argument is a FusedLate at kLateOffset of its argument segment (the
+// arguments in order, each at its own alignment).
+template <typename K>
+struct LateArgument;
+template <typename... Args>
+struct LateArgument<void(Args...)> {
+    static constexpr bool placed()
+    {
+        size_t end = 0, at = 0;
+        bool late = false;
+        ((at = (end + alignof(Args) - 1) / alignof(Args) * alignof(Args), end = at + sizeof(Args),
+          late = std::is_same_v<Args, FusedLate>),
+         ...);
+        return late && at == kLateOffset;
+    }
+};
 
 __device__ __forceinline__ FusedLate fused_late()
 {
@@ -1041,10 +1058,12 @@ hipError_t fused_ipl(md_ctx *c, int flags, double kick1, double kick2, double dr
     const size_t lds = (size_t)slice * S;
     const T *src = static_cast<const T *>(in);
     const FusedLate late{out, f, snap, pref, kick1, kick2, drift};
-#define MD_FUSED(I_, L_, E_)                                                                                              \
-    hipLaunchKernelGGL((k_fused<MODEL, T, A, I_, PREP, L_, E_>), grid, block, lds, c->stream, src, q, p, n, npad, jlen, \
-                       S, slice, fused_window<T>(slice, L_, E_), flags, t.jtile, e, \
-                       late)
+#define MD_FUSED(I_, L_, E_)                                                                                            \
+    do {                                                                                                                \
+        static_assert(LateArgument<decltype(k_fused<MODEL, T, A, I_, PREP, L_, E_>)>::placed(), "fused_late reads it"); \
+        hipLaunchKernelGGL((k_fused<MODEL, T, A, I_, PREP, L_, E_>), grid, block, lds, c->stream, src, q, p, n, npad,   \
+                           jlen, S, slice, fused_window<T>(slice, L_, E_), flags, t.jtile, e, late);                    \
+    } while (0)
 #define MD_FUSED_L(I_)                          \
     switch (L) {                                \
     case 1: MD_FUSED(I_, 1, 4); break;          \
