@@ -730,9 +730,12 @@ __device__ __forceinline__ FusedLate fused_late()
     return FusedLate{l->out, l->f, l->snap, l->pref, l->kick1, l->kick2, l->drift};
 }
 
-// E: entries a lane fetches per operand row and window.
+// E: entries a lane fetches per operand row and window, or 0: windows of all that the slice
+// holds, loaded when they are due (fused_ipl).  Those blocks are mostly few wavefronts with 48
+// KiB of LDS, and the compiler is told to plan for four wavefronts a SIMD: aiming at eight it
+// saves registers by waiting for every two LDS reads.
 template <int MODEL, typename T, typename A, int IPL, int PREP, int L, int E>
-__global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double *__restrict__ q,
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4, E > 0 ? 8 : 4))) void k_fused(const T *__restrict__ in, double *__restrict__ q,
                                                 double *__restrict__ p, int n, int npad, int jlen, int S,
                                                 int slice_bytes, int CHL, int flags, int jtile, T e,
                                                 FusedLate)
@@ -764,8 +767,8 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double
     // through LDS) and after: 2D FP64 n = 301 5.19 -> 4.15, 2000 6.40 -> 5.20, 4000 12.3 ->
     // 10.5; 2D mixed 301 4.86 -> 3.97; 2D Kahan 301 5.05 -> 4.16; Ring FP64 2048 7.02 -> 6.14,
     // 4000 14.9 -> 13.7; Ring mixed 2048 5.93 -> 5.07.
-    constexpr int kCols = E * kWave / L;
-    T x0[E], x1[E];
+    constexpr int kCols = E > 0 ? E * kWave / L : 1;
+    T x0[E > 0 ? E : 1], x1[E > 0 ? E : 1];
     auto fetch = [&](int t) {
 #pragma unroll
         for (int m = 0; m < E; ++m) {
@@ -776,8 +779,7 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double
             x1[m] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(r1) + at);
         }
     };
-    constexpr bool kAhead = IPL == 1 || sizeof(T) == 4;  // FP64 with more i a lane: no registers to spare
-    if (kAhead && wlen > 0) fetch(0);
+    if (E > 0 && wlen > 0) fetch(0);
     T a0[IPL], a1[IPL];
 #pragma unroll
     for (int k = 0; k < IPL; ++k) {
@@ -828,20 +830,47 @@ __global__ __launch_bounds__(1024) void k_fused(const T *__restrict__ in, double
     for (int t = 0; t < wlen; t += 16) {
         if (off == 0) {
             wave_sync();  // the previous window's reads are done
-            if (!kAhead) fetch(t);
             const int cnt = min(CHL, wlen - t);  // none past the wavefront's longest range
+            if constexpr (E > 0) {
 #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const int x = m * kWave + lane, gg = x / kCols, c = x % kCols;
-                const int j = (w * L + gg) * jlen + t + c;
-                const bool in = c < cnt && j < n;
-                if (L > 1 || in) {  // the rest into the pad between the groups: no branch
-                    win[gg * WS + (in ? c : CHL)] = x0[m];
-                    win[(L + gg) * WS + (in ? c : CHL)] = x1[m];
+                for (int m = 0; m < E; ++m) {
+                    const int x = m * kWave + lane, gg = x / kCols, c = x % kCols;
+                    const int j = (w * L + gg) * jlen + t + c;
+                    const bool in = c < cnt && j < n;
+                    if (L > 1 || in) {  // the rest into the pad between the groups: no branch
+                        win[gg * WS + (in ? c : CHL)] = x0[m];
+                        win[(L + gg) * WS + (in ? c : CHL)] = x1[m];
+                    }
+                }
+            } else {  // 64-j columns of every group, eight loads a row before their first LDS write
+                constexpr int FB = 8 / L;
+                for (int e0 = 0; e0 < cnt; e0 += FB * kWave) {
+                    T y0[FB][L], y1[FB][L];
+#pragma unroll
+                    for (int m = 0; m < FB; ++m)
+#pragma unroll
+                        for (int gg = 0; gg < L; ++gg) {
+                            const int ee = e0 + m * kWave + lane;
+                            const int j = (w * L + gg) * jlen + t + ee;
+                            const int jc = ee < cnt && j < n ? j : 0;
+                            y0[m][gg] = r0[jc];
+                            y1[m][gg] = r1[jc];
+                        }
+#pragma unroll
+                    for (int m = 0; m < FB; ++m)
+#pragma unroll
+                        for (int gg = 0; gg < L; ++gg) {
+                            const int ee = e0 + m * kWave + lane;
+                            const int j = (w * L + gg) * jlen + t + ee;
+                            if (ee < cnt && j < n) {
+                                win[gg * WS + ee] = y0[m][gg];
+                                win[(L + gg) * WS + ee] = y1[m][gg];
+                            }
+                        }
                 }
             }
             wave_sync();
-            if (kAhead && t + CHL < wlen) fetch(t + CHL);
+            if (E > 0 && t + CHL < wlen) fetch(t + CHL);
         }
         const T *w0 = win + g * WS + off;
         const T *w1 = win + (L + g) * WS + off;
@@ -1033,12 +1062,12 @@ hipError_t update(md_ctx *c, int flags, double kick1, double kick2, double drift
 }
 
 // j per lane group of a fused wavefront's LDS window: what its slice holds of two rows
-// (groups one element apart), a multiple of 16, and what one fetch loads.
+// (groups one element apart), a multiple of 16, and what one fetch loads (E > 0).
 template <typename T>
 int fused_window(int slice, int L, int E)
 {
     const int chl = (slice / (2 * (int)sizeof(T) * L) - (L > 1 ? 1 : 0)) / 16 * 16;
-    return std::min(chl, E * kWave / L);
+    return E > 0 ? std::min(chl, E * kWave / L) : chl;
 }
 
 template <int MODEL, typename T, typename A, int PREP>
@@ -1064,15 +1093,18 @@ hipError_t fused_ipl(md_ctx *c, int flags, double kick1, double kick2, double dr
         hipLaunchKernelGGL((k_fused<MODEL, T, A, I_, PREP, L_, E_>), grid, block, lds, c->stream, src, q, p, n, npad,   \
                            jlen, S, slice, fused_window<T>(slice, L_, E_), flags, t.jtile, e, late);                    \
     } while (0)
-#define MD_FUSED_L(I_)                          \
-    switch (L) {                                \
-    case 1: MD_FUSED(I_, 1, 4); break;          \
-    case 2: MD_FUSED(I_, 2, 4); break;          \
-    case 4: MD_FUSED(I_, 4, 4); break;          \
-    default: MD_FUSED(I_, 8, 4); break;         \
+#define MD_FUSED_L(I_)                                   \
+    switch (L) {                                         \
+    case 1: MD_FUSED(I_, 1, 0); break;                   \
+    case 2: MD_FUSED(I_, 2, 0); break;                   \
+    case 4: MD_FUSED(I_, 4, 0); break;                   \
+    default: MD_FUSED(I_, 8, (I_ == 1 ? 4 : 0)); break;  \
     }
     const int ts = timed_begin(c, "k_fused");
-    // the built-in tiles (8 lane groups, one i a lane): entries by the length of the ranges
+    // The built-in tiles (8 lane groups, one i a lane): short ranges, so windows in registers ahead
+    // of their use, entries by the length of the ranges.  Others, which the caller has set, have
+    // longer ranges: large windows.  us a step at N = 4000, windows in registers / large: Ring FP64
+    // tiles (1, 4, 6, 16) 132 / 109, (1, 4, 1, 128) 669 / 563; 2D mixed (2, 4, 16, 128) 58.7 / 53.2.
     if (t.ipl == 1 && L == 8 && jlen <= 2 * kWave / 8) MD_FUSED(1, 8, 2);
     else if (t.ipl == 1 && L == 8 && jlen > 4 * kWave / 8 && sizeof(T) == 4) MD_FUSED(1, 8, 8);
     else if (t.ipl == 1) MD_FUSED_L(1)

@@ -189,3 +189,16 @@ def test_window_entries(model, eps, dt, prec, n):
     b = _run(model, prec, n, eps, dt, 2, (1, 4, 64, 128), md.LAUNCH_FUSED, seed=n)
     for x, y in zip(a, b):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("tiles", [(1, 4, 1, 128), (2, 4, 2, 64), (1, 4, 6, 16), (4, 4, 3, 128), (2, 4, 16, 128)])
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("model,eps,dt", [(RING, 0.01, 0.05), (GRAV2D, 1e-3, 0.01)])
+def test_large_windows(model, eps, dt, prec, tiles):
+    """Tiles other than the built-in ones, with ranges of several windows and of several loads a
+    window, ragged: the staged form's bits."""
+    for n in (6500, 9001):
+        a = _run(model, prec, n, eps, dt, 1, tiles, md.LAUNCH_STAGED, seed=n)
+        b = _run(model, prec, n, eps, dt, 1, tiles, md.LAUNCH_FUSED, seed=n)
+        for x, y in zip(a, b):
+            np.testing.assert_array_equal(x, y)
