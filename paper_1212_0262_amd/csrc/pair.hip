@@ -1105,8 +1105,10 @@ hipError_t fused_ipl(md_ctx *c, int flags, double kick1, double kick2, double dr
     // of their use, entries by the length of the ranges.  Others, which the caller has set, have
     // longer ranges: large windows.  us a step at N = 4000, windows in registers / large: Ring FP64
     // tiles (1, 4, 6, 16) 132 / 109, (1, 4, 1, 128) 669 / 563; 2D mixed (2, 4, 16, 128) 58.7 / 53.2.
-    if (t.ipl == 1 && L == 8 && jlen <= 2 * kWave / 8) MD_FUSED(1, 8, 2);
-    else if (t.ipl == 1 && L == 8 && jlen > 4 * kWave / 8 && sizeof(T) == 4) MD_FUSED(1, 8, 8);
+    // In FP64 eight entries leave no registers.
+    const bool built_in = t.ipl == 1 && L == 8;
+    if (built_in && jlen <= 2 * kWave / 8) MD_FUSED(1, 8, 2);
+    else if (built_in && jlen > 4 * kWave / 8) MD_FUSED(1, 8, (sizeof(T) == 4 ? 8 : 4));
     else if (t.ipl == 1) MD_FUSED_L(1)
     else if (t.ipl == 2) MD_FUSED_L(2)
     else MD_FUSED_L(4)
