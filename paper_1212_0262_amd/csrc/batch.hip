@@ -448,7 +448,9 @@ __global__ __launch_bounds__(2 * NS * kWave) void k_batch_sym_split(const PairIt
 }
 
 // Where an item is shared: with few tile pairs the launch is as long as one item, and as the
-// items end the SIMDs run empty; with many there is nothing to gain.  Measured md_step, us a
+// items end the SIMDs run empty; with many there is nothing to gain.  And not where the diagonal
+// tiles outnumber the tile pairs (the symmetric form asked for with small realizations): most
+// of a short tile's eight wavefronts have no particles.  Measured md_step, us a
 // step, by k_batch_sym and shared (Ring FP64; Ring and 2D in MD_MIXED):
 //      33 tile pairs (8 realizations of 1000 .. 2000)    139 -> 62;  103 -> 43;  94 -> 39
 //     109 (8 of 96 .. 8170)                              141 -> 66;  105 -> 45;  97 -> 42
@@ -456,6 +458,9 @@ __global__ __launch_bounds__(2 * NS * kWave) void k_batch_sym_split(const PairIt
 //    3695 (128 of 1000 .. 8000)                          963 -> 872; 533 -> 480; 435 -> 386
 //   11672 (128 of 1000 .. 16384)                 2492 -> 2467; 1328 -> 1321; 1112 -> 1091
 //   23331 (256 of 1000 .. 16384)                 4882 -> 4862; 2585 -> 2595; 2206 -> 2206
+//    9000 and 9000 diagonal (3000 of 1300)       6190 -> 5873; 3362 -> 3257; 2857 -> 2649
+//    2000 and 4000 diagonal (2000 of 600)        1847 -> 1760; 1045 -> 1063; 762 -> 815
+//       0 and 4000 diagonal (4000 of 100)        260 -> 381; 169 -> 243; 134 -> 255
 constexpr int kBatchSplit = 4;
 constexpr int kBatchSplitPairs = 16384;
 
@@ -471,7 +476,7 @@ hipError_t sym_launch(md_ctx *c)
     const dim3 grid((unsigned)(B.n_soff + B.n_sdiag));
     bool split = false;
     if constexpr (!std::is_same_v<A, AccKahan>) {
-        split = B.n_soff <= kBatchSplitPairs;
+        split = B.n_soff >= B.n_sdiag && B.n_soff <= kBatchSplitPairs;
         if (split)
             hipLaunchKernelGGL((k_batch_sym_split<MODEL, T, A, kBatchSplit>), grid, dim3(2 * kBatchSplit * kWave), 0,
                                c->stream, items, B.n_soff, r0, r0 + npad, B.d_eps, npad, c->part);

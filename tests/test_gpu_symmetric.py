@@ -535,6 +535,25 @@ def test_ring_fp64_coincident_angles_are_exact_zeros(n):
         ctx.close()
 
 
+@pytest.mark.parametrize("model,prec", [(RING, md.MIXED), (RING, md.FP64), (GRAV2D, md.MIXED)])
+def test_ensemble_items_shared_or_not(model, prec):
+    """Small realizations whose diagonal tiles outnumber their tile pairs (an item per two wavefronts)
+    and the same beside a large one (an item per eight): MD_MIXED the same bits, FP64 to its
+    rounding; both against the oracle."""
+    small, eps = [700, 100, 513, 1024], 0.01 if model == RING else 1e-3
+    q, _, off = _ensemble(model, small + [5000], seed=71)
+    n = off[len(small)]
+    alone = _batch_force(model, prec, q[:, :n], off[:len(small) + 1], [eps] * len(small), md.LAUNCH_SYMMETRIC)
+    beside = _batch_force(model, prec, q, off, [eps] * (len(small) + 1), md.LAUNCH_SYMMETRIC)[:, :n]
+    if prec == md.MIXED:
+        assert np.array_equal(alone, beside)
+    for b, nb in enumerate(small):
+        part = slice(off[b], off[b + 1])
+        want = oracle.force(model, q[:, part], eps)
+        check(f"model={model} prec={prec} N_b={nb} alone", rel_inf(alone[:, part], want), force_tol(model, prec, nb))
+        check(f"model={model} prec={prec} N_b={nb} beside", rel_inf(beside[:, part], want), force_tol(model, prec, nb))
+
+
 def test_ring_fp32_symmetric_coincident_angles():
     """Ring FP32 forms, symmetric launch: a tile pair forms the half-angle
     numerator a = 2 sin(d/2) as one product and one FMA (one rounding fewer than
