@@ -539,38 +539,50 @@ int make_batch(int model, int prec, int nb, const int64_t *off, const double *ep
     return MD_OK;
 }
 
-// Pair items for the current tiles (largest first) and the rows' chunk counts.
+// Pair items for the current tiles (largest first) and the rows' chunk counts.  A realization
+// has four kinds of item at most, the whole and the last i blocks by the whole and the last
+// chunks: the kinds are sorted by their items' cost, not the items.
 void build_lists(Batch &B, const Tiles &t)
 {
     const int64_t chunk = batch_chunk(B, t.jsplit);
     const int64_t iblock = (int64_t)kWave * t.ipl * t.waves;
-    struct Item {
+    struct Kind {
         int64_t cost;
-        int v[8];
+        int b, i_first, i_end, s_first, s_end;
     };
-    std::vector<Item> items;
+    std::vector<Kind> kinds;
+    kinds.reserve(4 * (size_t)B.nb);
     B.rows.clear();
+    size_t count = 0;
     for (int b = 0; b < B.nb; ++b) {
         const int64_t o = B.off[b], n = B.off[b + 1] - B.off[b];
-        const int S = (int)div_up(n, chunk);
+        const int S = (int)div_up(n, chunk), I = (int)div_up(n, iblock);
         for (int64_t i0 = o; i0 < o + n; i0 += 256) {
             const int r[4] = {b, (int)i0, (int)(i0 + 256 < o + n ? i0 + 256 : o + n), S};
             B.rows.insert(B.rows.end(), r, r + 4);
         }
-        for (int64_t i0 = o; i0 < o + n; i0 += iblock) {
-            const int64_t i1 = i0 + iblock < o + n ? i0 + iblock : o + n;
-            for (int s = 0; s < S; ++s) {
-                const int64_t j0 = o + s * chunk;
-                const int64_t j1 = j0 + chunk < o + n ? j0 + chunk : o + n;
-                items.push_back({(i1 - i0) * (j1 - j0), {b, (int)i0, (int)i1, s, (int)j0, (int)j1, 0, 0}});
+        const int64_t ilast = n - (I - 1) * iblock, jlast = n - (S - 1) * chunk;
+        if (I > 1 && S > 1) kinds.push_back({iblock * chunk, b, 0, I - 1, 0, S - 1});
+        if (I > 1) kinds.push_back({iblock * jlast, b, 0, I - 1, S - 1, S});
+        if (S > 1) kinds.push_back({ilast * chunk, b, I - 1, I, 0, S - 1});
+        kinds.push_back({ilast * jlast, b, I - 1, I, S - 1, S});
+        count += (size_t)I * S;
+    }
+    std::stable_sort(kinds.begin(), kinds.end(), [](const Kind &x, const Kind &y) { return x.cost > y.cost; });
+    B.items.resize(count * 8);
+    int *out = B.items.data();
+    for (const Kind &k : kinds) {
+        const int64_t o = B.off[k.b], end = B.off[k.b + 1];
+        for (int i = k.i_first; i < k.i_end; ++i) {
+            const int64_t i0 = o + i * iblock, i1 = std::min(i0 + iblock, end);
+            for (int s = k.s_first; s < k.s_end; ++s, out += 8) {
+                const int64_t j0 = o + s * chunk, j1 = std::min(j0 + chunk, end);
+                const int it[8] = {k.b, (int)i0, (int)i1, s, (int)j0, (int)j1, 0, 0};
+                std::copy(it, it + 8, out);
             }
         }
     }
-    std::stable_sort(items.begin(), items.end(), [](const Item &x, const Item &y) { return x.cost > y.cost; });
-    B.items.resize(items.size() * 8);
-    for (size_t k = 0; k < items.size(); ++k)
-        for (int m = 0; m < 8; ++m) B.items[k * 8 + m] = items[k].v[m];
-    B.n_items = (int)items.size();
+    B.n_items = (int)count;
 }
 
 struct BatchLayout {
@@ -610,29 +622,45 @@ BatchLayout batch_layout(int model, int prec, const Batch &B)
     return L;
 }
 
-// An ensemble's built-in tiles.  The forms that add in FP64 take one wavefront a work item (a
-// block of four waits for its slowest at every ragged end) and, the fewer the 64-i blocks, the
-// more j chunks (8 to 32, about 2^17 items at most): an item's uniform j loads leave it waiting for
-// memory, so the SIMDs need many.  MD_MIXED and MD_MIXED_KAHAN keep the chunks that fix their FP32
-// sums; realizations of at most 256 particles, one block each whose wavefronts share the j, keep
-// it too (100 of 64 .. 200: 11.9 us, 13.4 with one wavefront).  Measured, us per evaluation with
-// its update, four wavefronts and 8 chunks -> these, 2D FP64 and 2D MD_MIXED_PAIRF64: 8 realizations of
-// 1000 .. 2000 27.5 -> 19.8, 23.5 -> 19.2; 15 of 439 .. 6212 69 -> 51, 59 -> 45; 47 of 1222 .. 5616
-// 173 -> 160, 154 -> 139; 30 of 500 .. 16,000 381 -> 343, 339 -> 305; 128 of 1000 .. 8000 612 -> 584, 550 ->
-// 525; 1000 of 500 .. 2000 463 -> 442, 415 -> 392.  (400 of 5000 .. 16,384: 32 chunks 12,416, 8 12,107.)
+// An ensemble's built-in tiles: four wavefronts a work item (256 i) and 8 j chunks; or one
+// wavefront (64 i) and, the fewer the 64-i blocks, the more chunks (8 to 32: at most 2^17
+// items up to 8192 blocks, 8 a block above).  The one is ahead in the forms that add in FP64
+//   * where blocks are few and the largest realization has more than 8 chunks of 64 (an item's
+//     uniform j loads leave it waiting for memory, so the SIMDs need many): up to 512 blocks;
+//   * where blocks of 256 i would be padded, by the realizations' ragged ends or short ones
+//     (and, with the same chunks either way, where they fill the chip: from 256 blocks).
+// It is not where it has neither (one j chunk's operands are then fetched by four CUs instead of
+// one), nor for realizations of at most 256 particles (100 of 64 .. 200: 11.9 us, 13.4 with
+// one wavefront).  MD_MIXED and MD_MIXED_KAHAN keep the chunks that fix their FP32 sums; of an
+// ensemble that MD_LAUNCH_AUTO runs in the symmetric form the lists, which it does not read,
+// stay short.
+// Measured, us per evaluation, four wavefronts / one, 2D FP64 and Ring FP64 (staged):
+//   four taken: 8 of 257 9.6 / 8.9, 12.5 / 14.6; 32 of 400 10.4 / 10.1, 13.0 / 15.6; 100 of 500
+//     17.5 / 17.2, 23.6 / 24.3; 64 of 1000 26.8 / 27.4, 38.2 / 39.4; 64 of 4000 315 / 328, 480 / 480;
+//     64 of 12,000 2641 / 2677, 4096 / 4140;
+//   one: 64 of 257 11.9 / 10.1, 16.0 / 15.2; 8 of 640 10.7 / 7.8, 15.9 / 12.5; 8 of 1000 .. 2000
+//     20.4 / 17.0, 29.3 / 21.3; 300 of 65 .. 500 17.1 / 15.2, 25.8 / 22.4; 1000 of 300 52 / 39, 80 /
+//     57; 100 of 600 23.3 / 20.9, 31.7 / 28.7; 60 of 2000 .. 9000 510 / 483; 128 of 1000 .. 8000 615 / 593.
 Tiles batch_default_tiles(const Batch &B, int prec)
 {
     Tiles t;
     t.ipl = 1;
+    t.waves = 4;
+    t.jsplit = 8;
     t.jtile = 128;
     if ((prec == MD_FP64 || prec == MD_MIXED_PAIRF64) && B.nmax > 256) {
-        int64_t blocks = 0;
-        for (int b = 0; b < B.nb; ++b) blocks += div_up(B.off[b + 1] - B.off[b], 64);
-        t.waves = 1;
-        t.jsplit = blocks <= 4096 ? 32 : blocks <= 8192 ? 16 : 8;
-    } else {
-        t.waves = 4;
-        t.jsplit = 8;
+        int64_t blocks = 0, padded = 0;  // of 64 i, and as whole blocks of 256
+        for (int b = 0; b < B.nb; ++b) {
+            const int64_t n = B.off[b + 1] - B.off[b];
+            blocks += div_up(n, 64);
+            padded += 4 * div_up(n, 256);
+        }
+        const bool one = B.smax > 8 ? blocks <= 512 || (50 * padded >= 51 * blocks && !batch_sym_auto(B))
+                                    : padded >= 2 * blocks || (blocks >= 256 && 4 * padded >= 5 * blocks);
+        if (one) {
+            t.waves = 1;
+            t.jsplit = blocks <= 4096 ? 32 : blocks <= 8192 ? 16 : 8;
+        }
     }
     if (t.jsplit > B.smax) t.jsplit = B.smax;
     return t;

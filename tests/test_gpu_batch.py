@@ -228,3 +228,26 @@ def test_built_in_tiles(model, eps, prec, sizes, tiles):
         else:
             assert np.all(fg[b] == 0.0)
     ctx.close()
+
+
+@pytest.mark.parametrize("model,eps", [(RING, 0.01), (GRAV2D, 1e-3)])
+@pytest.mark.parametrize("prec", [md.FP64, md.MIXED_PAIRF64])
+@pytest.mark.parametrize("sizes,tiles", [([257] * 8, (1, 4, 4, 128)), ([257] * 51, (1, 4, 4, 128)),
+                                         ([257] * 52, (1, 1, 4, 128)), ([500] * 100, (1, 4, 7, 128)),
+                                         ([640] * 51, (1, 1, 10, 128)), ([1024] * 33, (1, 4, 8, 128))])
+def test_built_in_tiles_of_even_ensembles(model, eps, prec, sizes, tiles):
+    """As above, either side of the padded blocks' and the few blocks' limits; and the work lists,
+    which are ordered by kinds of item: every realization's force, some of them ragged."""
+    q, _, off = ensemble(model, sizes, seed=44)
+    ctx = md.md_batch_init(model, prec, off, eps)
+    assert md.md_get_tiles(ctx) == tiles
+    for t in (None, (2, 2, 3, 64), (1, 1, 1, 128)):
+        if t:
+            md.md_set_tiles(ctx, *t)
+        md.md_set_launch(ctx, md.LAUNCH_STAGED)
+        f = torch.empty_like(dev(q))
+        fg, qs = split(host(md.md_force(ctx, dev(q), f)), off), split(q, off)
+        for b in (0, 1, len(sizes) // 2, len(sizes) - 1):
+            check(f"even ensemble model={model} prec={prec} N_b={sizes[b]} tiles={t}",
+                  rel_inf(fg[b], oracle.force(model, qs[b], eps)), force_tol(model, prec, sizes[b]))
+    ctx.close()
