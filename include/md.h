@@ -337,7 +337,7 @@ int md_check(md_ctx *c);
 /*
  * HMF magnetization of eq. 7 at positions q: out_dev2[0] = Mx, out_dev2[1] = My.
  * The sum is reproducible bit for bit and the same one md_force and md_step use
- * (FP64 state): for n <= 8192 the sum of one workgroup in a fixed order, for n <=
+ * (FP64 state): for n <= 4096 the sum of one workgroup in a fixed order, for n <=
  * 2097152 the exact sum of the FP64 block partials (in 64-bit fixed
  * point) rounded once to FP64, above that the block partials added in FP64 in a
  * fixed order.  MD_HMF contexts only.  Records finiteness for md_check as
@@ -409,7 +409,7 @@ int md_step_vjp_recorded(md_ctx *c, const double *q0, double dt, int64_t nsteps,
  * events recorded on the context's stream; later launches run untimed.  The
  * dominant kernel is the one that evaluates the pairs: the tile-pair kernel of the
  * symmetric form (not its diagonal tiles), the pair kernel of the staged form, the
- * fused kernel, the HMF stage pass (not the one-block sum after it; for n <= 8192 the
+ * fused kernel, the HMF stage pass (not the one-block sum after it; for n <= 4096 the
  * kernel that takes a whole call's stages); for ensembles the tile-pair
  * or the pair kernel; in md_hvp and the reverse sweeps, the Ring and 2D
  * Hessian-vector product's pair kernel (the timed launches of a call sequence are

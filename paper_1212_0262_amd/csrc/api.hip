@@ -1168,7 +1168,7 @@ int md_hvp(md_ctx *c, const double *q, const double *w, double *out)
     DeviceGuard g(c->dev);
     if (g.err != hipSuccess) return dev_fail(c, g.err, "md_hvp: set device");
     double *wm = const_cast<double *>(w);
-    if (c->model == MD_HMF && hmf_small(c)) {
+    if (c->model == MD_HMF && hmf_small_hvp(c)) {
         MD_TRY(launch_hmf_small_hvp(c, q, w, out), "hvp");
         return MD_OK;
     }

@@ -165,7 +165,7 @@ EnergyGrid energy_grid(int64_t n)
 // [kRedSlots/2, kRedSlots/2 + kKinGrid) kinetic partials.
 hipError_t launch_energy(md_ctx *c, const double *q, const double *p, double *out3)
 {
-    if (c->model == MD_HMF && hmf_small(c))
+    if (c->model == MD_HMF && hmf_small_energy(c))
         return launch_hmf_small_eval(c, q, p, nullptr, nullptr, out3, finite_flag(c));
     const int n = (int)c->n;
     const int64_t len = (int64_t)dims(c->model) * n;

@@ -2,19 +2,20 @@
 // registers: a whole md_step call, or a whole reverse sweep, in one launch.
 //
 // The magnetization joins every particle at each stage.  Across blocks that takes a
-// kernel boundary a stage (hmf.hip), 6.5 to 7.3 us however few the particles: the
+// kernel boundary a stage (hmf.hip), 3 to 4 us however few the particles: the
 // launch, a memory round trip for (t, p), the sums' way through memory.  Here one block
 // of up to 512 threads keeps t, p and the sincos of t of P particles a thread in
 // registers for all stages of the call, so a stage is one sincos per particle (the
 // kick reuses the sincos the previous stage summed), a register reduction and one
 // barrier.  Bound by FP64 issue on one CU (36 instructions of sincos a particle) above
 // about 1000 particles and by the chain sincos - reduction - barrier below.
-// Measured (MI355X), us per step before and after, FP64 / FP32 state: n = 100 15.6 / 17.9
-// -> 1.5 / 1.5; 2001 22.0 / 19.4 -> 3.7 / 3.9; 4096 20.5 / 18.3 -> 5.8 / 4.5; 8192 20.8 /
-// 18.6 -> 12.2 / 11.6.  Four steps' md_step_vjp at n = 2001: 235 -> 51 us.
+// Measured (MI355X), us per step by hmf.hip's passes and so, FP64 / FP32 state: n = 100 11.8 /
+// 8.7 and 1.6 / 1.6; 2001 11.9 / 9.1 and 3.8 / 4.2; 4096 12.0 / 9.1 and 6.0 / 4.9.  Four steps'
+// md_step_vjp at n = 2001: 112 and 46 us.  (The limits are in md_internal.h.)
 //
-// Sums: each thread's particles t, t + threads, ... in order, then small_means.  md_force, md_magnetization, md_energy and
-// the reverse sweep of these systems take the same sums, so they agree bit for bit.
+// Sums: each thread's particles t, t + threads, ... in order, then small_means.  md_force,
+// md_magnetization, md_energy and the reverse sweep of these systems take the same sums, so
+// they agree bit for bit.
 #include "device.h"
 #include "hmf_terms.h"
 #include "md_internal.h"
@@ -326,7 +327,7 @@ __global__ __launch_bounds__(small_threads(P)) void k_hmf_small_vjp(const double
 // up to eight wavefronts of 8, then four of 32: each wavefront repeats the reduction, so
 // fewer, fuller ones are faster while the registers last.  Measured, us per FP64 step:
 // n = 1000 2.55 (4 wavefronts of 4 a lane; 16 of 1 4.39, with the reduction of each sum by
-// itself); n = 4096 5.81 (8 of 8; 4 of 16 6.62); n = 8192 12.2 (4 of 32).
+// itself); n = 4096 5.81 (8 of 8; 4 of 16 6.62); n = 8192 12.2 (4 of 32, products and energies only).
 int small_per_thread(int64_t n)
 {
     if (n > 8 * small_threads(8)) return 32;
@@ -334,21 +335,23 @@ int small_per_thread(int64_t n)
     while (p < 8 && n > (int64_t)4 * kWave * p) p *= 2;
     return p;
 }
-static_assert(kHmfSmallN <= 32 * small_threads(32), "every particle has a thread");
+static_assert(kHmfSmallN <= 8 * small_threads(8), "up to 8 particles a thread in steps and sweeps");
+static_assert(kHmfSmallHvpN <= 32 * small_threads(32) && kHmfSmallEnergyN <= 32 * small_threads(32), "a thread each");
 
-#define MD_SMALL(K_, ...)                                                                          \
-    do {                                                                                           \
-        const int per = small_per_thread(c->n);                                                    \
-        const int64_t waves = (c->n + (int64_t)kWave * per - 1) / ((int64_t)kWave * per);          \
-        const int B = per > 8 ? small_threads(per) : (int)(waves * kWave);                         \
-        const dim3 block((unsigned)B);                                                             \
-        switch (per) {                                                                             \
-        case 1: hipLaunchKernelGGL((K_(1)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
-        case 2: hipLaunchKernelGGL((K_(2)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
-        case 4: hipLaunchKernelGGL((K_(4)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
-        case 8: hipLaunchKernelGGL((K_(8)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;     \
-        default: hipLaunchKernelGGL((K_(32)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;   \
-        }                                                                                          \
+// Launches K_(particles a thread), of MOST_ at most.
+#define MD_SMALL(MOST_, K_, ...)                                                                       \
+    do {                                                                                               \
+        const int per = small_per_thread(c->n);                                                        \
+        const int64_t waves = (c->n + (int64_t)kWave * per - 1) / ((int64_t)kWave * per);              \
+        const int B = per > 8 ? small_threads(per) : (int)(waves * kWave);                             \
+        const dim3 block((unsigned)B);                                                                 \
+        switch (per) {                                                                                 \
+        case 1: hipLaunchKernelGGL((K_(1)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;         \
+        case 2: hipLaunchKernelGGL((K_(2)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;         \
+        case 4: hipLaunchKernelGGL((K_(4)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;         \
+        case 8: hipLaunchKernelGGL((K_(8)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;         \
+        default: hipLaunchKernelGGL((K_(MOST_)), dim3(1), block, 0, c->stream, __VA_ARGS__); break;    \
+        }                                                                                              \
     } while (0)
 
 }  // namespace
@@ -366,8 +369,8 @@ hipError_t launch_hmf_small_steps(md_ctx *c, double b0, double b1, double d0, do
         const int ts = timed_begin(c, "k_hmf_small_step");
 #define K64(P_) k_hmf_small_step<double, P_>
 #define K32(P_) k_hmf_small_step<float, P_>
-        if (c->prec == MD_FP64) MD_SMALL(K64, q, p, f, n, B, a, k, sn, snap_stride, only);
-        else MD_SMALL(K32, q, p, f, n, B, a, k, sn, snap_stride, only);
+        if (c->prec == MD_FP64) MD_SMALL(8, K64, q, p, f, n, B, a, k, sn, snap_stride, only);
+        else MD_SMALL(8, K32, q, p, f, n, B, a, k, sn, snap_stride, only);
 #undef K64
 #undef K32
         err = hipGetLastError();
@@ -382,7 +385,7 @@ hipError_t launch_hmf_small_eval(md_ctx *c, const double *q, const double *p, do
 {
     const int n = (int)c->n;
 #define K(P_) k_hmf_small_eval<P_>
-    MD_SMALL(K, q, p, n, B, c->scal, out2, f, out3, flag);
+    MD_SMALL(32, K, q, p, n, B, c->scal, out2, f, out3, flag);
 #undef K
     return hipGetLastError();
 }
@@ -391,7 +394,7 @@ hipError_t launch_hmf_small_hvp(md_ctx *c, const double *q, const double *w, dou
 {
     const int n = (int)c->n;
 #define K(P_) k_hmf_small_hvp<P_>
-    MD_SMALL(K, q, w, n, B, out);
+    MD_SMALL(32, K, q, w, n, B, out);
 #undef K
     return hipGetLastError();
 }
@@ -408,7 +411,7 @@ hipError_t launch_hmf_small_vjp(md_ctx *c, double b0, double b1, double d0, doub
         const double *const from = begin == 0 ? q0 : nullptr;
         const double *const at = pos + (size_t)(3 * begin) * stride;
 #define K(P_) k_hmf_small_vjp<P_>
-        MD_SMALL(K, from, at, stride, n, B, a, k, (int)(end == nsteps), lq, lp);
+        MD_SMALL(8, K, from, at, stride, n, B, a, k, (int)(end == nsteps), lq, lp);
 #undef K
         err = hipGetLastError();
         end = begin;

@@ -51,8 +51,16 @@ constexpr int kMSlots = 64;
 constexpr int kMLimbs = 4;  // sum cos: 2^-32 and 2^-64 limbs; sum sin: the same
 constexpr int kMWords = 3 * kMSlots * kMLimbs;
 constexpr int kHmfInPassM = 1024;  // grids of at most this many blocks use the fixed-point sums
-constexpr int64_t kHmfSmallN = 8192;      // HMF systems one workgroup takes whole (hmf_small.hip)
-constexpr int64_t kHmfSmallSteps = 4096;  // most steps of one of its launches, also a sweep's (up to 0.1 s)
+// HMF systems that one workgroup takes whole (hmf_small.hip): steps, force, magnetization and
+// reverse sweeps (one limit: they share their sums bit for bit); products; energies.  Above 4096
+// a thread has 32 slots, filled or not.  Measured, us, passes / one workgroup:
+//   replayed from a graph: FP64 step n = 4096 9.7 / 6.1, 4097 9.7 / 12.3, 8192 9.7 / 12.3; FP32 state
+//     9.1 / 4.9, 9.0 / 11.6, 9.1 / 11.9; force 5.3 / 4.0, 5.3 / 6.8, 5.4 / 7.2; M 5.9 / 3.6, 5.8 / 6.2;
+//   call by call (the host's launches bound the passes): step 4097 11.4 / 12.3, 8192 11.2 / 12.5; force
+//     4097 8.8 / 6.6; sweep of four steps 4096 55 / 35, 4097 52 / 83, 8192 52 / 88; product 6144 9.5 / 8.9,
+//     7000 9.5 / 9.5, 8192 9.2 / 10.3; energies 8192 10.7 / 6.6.
+constexpr int64_t kHmfSmallN = 4096, kHmfSmallHvpN = 6144, kHmfSmallEnergyN = 8192;
+constexpr int64_t kHmfSmallSteps = 4096;  // most steps of one of its launches, also a sweep's (25 and 35 ms)
 constexpr int kEnergyBlock = 256;
 constexpr int64_t kFusedMaxN = 65536;   // contexts up to this n carry the fused stage's operand buffers
 constexpr int kFusedMaxWaves = 16;      // wavefronts per fused block
@@ -232,10 +240,12 @@ hipError_t launch_hmf_adj_pass(md_ctx *c, int k, const double *th, int flags, do
 // M from the partials of a call's pass 0, to out2[0..1] and the context scalars.
 hipError_t launch_hmf_magnetization(md_ctx *c, double *out2);
 const double *hmf_partials(const md_ctx *c);  // block partials of a call's pass 0
-// hmf_small.hip (n <= kHmfSmallN): whole calls in one launch.  b0 .. d1: the kicks and
+// hmf_small.hip (n <= kHmfSmallN and the like): whole calls in one launch.  b0 .. d1: the kicks and
 // drifts of eq. 4 times dt.  Outputs of eval (nullable): M, the force, the energies of
 // (q, p) and their (or M's) finiteness.
 inline bool hmf_small(const md_ctx *c) { return c->n <= kHmfSmallN; }
+inline bool hmf_small_hvp(const md_ctx *c) { return c->n <= kHmfSmallHvpN; }
+inline bool hmf_small_energy(const md_ctx *c) { return c->n <= kHmfSmallEnergyN; }
 hipError_t launch_hmf_small_steps(md_ctx *c, double b0, double b1, double d0, double d1, int64_t nsteps, double *q,
                                   double *p, double *f, double *snap, size_t snap_stride, bool positions_only);
 hipError_t launch_hmf_small_eval(md_ctx *c, const double *q, const double *p, double *out2, double *f, double *out3,

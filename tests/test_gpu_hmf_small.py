@@ -177,3 +177,31 @@ def test_a_launch_takes_a_bounded_number_of_steps(steps, launches):
         assert nodes.value == launches
     torch.cuda.synchronize()
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", [md.FP64, md.MIXED_F32STATE])
+@pytest.mark.parametrize("n,kernel,launches", [(4096, "k_hmf_small_step", 1), (4097, "k_hmf_pass", 10),
+                                               (8192, "k_hmf_pass", 10)])
+def test_steps_leave_the_one_workgroup_where_it_is_slower(n, kernel, launches, prec):
+    """Above 4096 particles the passes are ahead (12.0 against 12.3 us a step at 4097, 9.7 against 12.5
+    at 8192)."""
+    ctx = md.md_init(md.HMF, prec, n)
+    q, p = (dev(x) for x in inputs.hmf_waterbag(n, seed=n))
+    f = md.md_force(ctx, q, torch.empty_like(q))
+    md.md_timing_begin(ctx, 16)
+    md.md_step(ctx, q, p, f, 0.1, 3)
+    _, count, name = md.md_timing_end(ctx)
+    assert (name, count) == (kernel, launches)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [4097, 6144, 6145, 8192, 8193])
+def test_energies_and_products_between_the_limits(n):
+    """Energies (one workgroup up to 8192) and products (up to 6144) beside steps by passes."""
+    q, p = inputs.hmf_waterbag(n, seed=n)
+    w = np.random.default_rng(n).normal(size=(1, n))
+    ctx = md.md_init(md.HMF, md.FP64, n)
+    e, eo = host(md.md_energy(ctx, dev(q), dev(p))), np.asarray(oracle.energy(md.HMF, q, p, 0.0))
+    assert np.abs(e - eo).max() < 1e-12 * (abs(eo[0]) + abs(eo[1]) + n / 2)
+    assert np.abs(host(md.md_hvp(ctx, dev(q), dev(w))) - oracle.hvp(md.HMF, q, w, 0.0)).max() < 1e-11
+    ctx.close()
