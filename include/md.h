@@ -410,10 +410,11 @@ int md_step_vjp_recorded(md_ctx *c, const double *q0, double dt, int64_t nsteps,
  * dominant kernel is the one that evaluates the pairs: the tile-pair kernel of the
  * symmetric form (not its diagonal tiles), the pair kernel of the staged form, the
  * fused kernel, the HMF stage pass (not the one-block sum after it; for n <= 4096 the
- * kernel that takes a whole call's stages); for ensembles the tile-pair
+ * kernel that takes a whole call's stages, or one evaluation); for ensembles the tile-pair
  * or the pair kernel; in md_hvp and the reverse sweeps, the Ring and 2D
  * Hessian-vector product's pair kernel (the timed launches of a call sequence are
- * those of every such kernel it runs, and the name is the last one's).  Launches enqueued while the stream is being captured into
+ * those of every such kernel it runs, and the name is the last one's; k_sym, k_batch_sym
+ * and k_hvp_sym also name the kernels in which wavefronts share a tile pair).  Launches enqueued while the stream is being captured into
  * a graph are not timed.  It creates 2 max_launches HIP events (host-side
  * objects: no workspace or device memory is taken); calling it again starts over.
  * md_timing_end: waits for the last timed launch, writes the summed duration of

@@ -385,9 +385,12 @@ hipError_t launch_hmf_small_eval(md_ctx *c, const double *q, const double *p, do
 {
     const int n = (int)c->n;
 #define K(P_) k_hmf_small_eval<P_>
+    const int ts = timed_begin(c, "k_hmf_small_eval");
     MD_SMALL(32, K, q, p, n, B, c->scal, out2, f, out3, flag);
 #undef K
-    return hipGetLastError();
+    const hipError_t err = hipGetLastError();
+    timed_end(c, ts);
+    return err;
 }
 
 hipError_t launch_hmf_small_hvp(md_ctx *c, const double *q, const double *w, double *out)

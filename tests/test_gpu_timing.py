@@ -156,3 +156,19 @@ def test_capture_is_not_timed_and_replays_match_eager():
         np.testing.assert_array_equal(host(pg), host(pe))
         np.testing.assert_array_equal(host(fg), host(fe))
     ctx.close()
+
+
+@pytest.mark.parametrize("n,name,counts", [(1000, "k_hmf_small_eval", (1, 1, 1)), (100_000, "k_hmf_pass", (2, 1, 1))])
+def test_hmf_evaluations_are_timed(n, name, counts):
+    """md_force, md_magnetization and md_energy, in the one-workgroup form and by passes."""
+    q0, p0 = _state(md.HMF, n)
+    q, p = dev(q0), dev(p0)
+    ctx = md.md_init(md.HMF, md.FP64, n)
+    f = torch.empty_like(q)
+    for call, launches in zip((lambda: md.md_force(ctx, q, f), lambda: md.md_magnetization(ctx, q),
+                               lambda: md.md_energy(ctx, q, p)), counts):
+        md.md_timing_begin(ctx, 8)
+        call()
+        ms, count, kname = md.md_timing_end(ctx)
+        assert (kname, count) == (name, launches) and ms > 0.0
+    ctx.close()
