@@ -100,8 +100,9 @@ enum md_status {
  * combination.  The figure covers every tile configuration md_set_tiles
  * accepts for this n, and every launch form the context can take: for
  * MD_GRAV2D and MD_RING with 2048 <= n <= 1048576 it
- * includes the symmetric form's partial slots, 8 d n'^2 / 1024 bytes with n' = n
- * rounded up to a multiple of 1024 (1.07 GB for 2D at n = 262144).
+ * includes the symmetric form's partial slots, 8 d n'^2 / T bytes with n' = n
+ * rounded up to a multiple of 1024 and T its tile (md_get_sym_tile: 256 up to
+ * n = 65536; 1.07 GB for 2D at n = 262144).
  */
 size_t md_workspace_bytes(int model, int prec, int64_t n);
 

@@ -77,7 +77,7 @@ constexpr int kBatchSymTile = 512;     // tiles of the ensembles' symmetric form
 constexpr int kSymTileSmall = 512;      // ... for smaller n (2 waves x 64 x 4 i; sym_tile_n), and 256
                                         // (shared by up to 4 waves) for smaller n still
 constexpr int64_t kSymMinN = 2048;      // the symmetric form needs two tiles at least
-constexpr int64_t kSymMaxN = 1 << 20;   // and at most 1024 tiles (its partial slots: 8 d n^2 / 1024 bytes)
+constexpr int64_t kSymMaxN = 1 << 20;   // and at most 1024 tiles (partial slots: 8 d n^2 / T bytes, T from sym_tile_n)
 // The 2D FP64 product takes the symmetric form from here under MD_LAUNCH_AUTO, before the
 // force does: its pair term is twice the force's against the same slot sums.  Up to
 // kFusedAutoN2D the built-in tiles (64 j ranges) have the staged product ahead (N = 5120 24.2 /
@@ -85,7 +85,11 @@ constexpr int64_t kSymMaxN = 1 << 20;   // and at most 1024 tiles (its partial s
 // forward, staged -> symmetric: N = 6145 39.6 -> 39.3, 408 -> 387; 7168 43.2 -> 35.3, 496 -> 399; 9216
 // 59.3 -> 48.1, 672 -> 554; 12,288 97.4 -> 73.8, 1035 -> 851.
 constexpr int64_t kSymHvpN = kFusedAutoN2D + 1;
-// MD_LAUNCH_AUTO takes the symmetric form from this n (measured crossovers).  Ring FP64,
+// MD_LAUNCH_AUTO takes the symmetric form from this n: crossovers measured with one wavefront a
+// tile pair.  With shared pairs they lie lower (us a step, staged / symmetric: 2D FP64 7168 79 / 66;
+// 2D mixed 7168 61 / 71, 9216 81 / 73; Ring mixed 9216 90 / 85; per-pair FP64 7168 72 / 62 and
+// 74 / 58; Kahan, not shared, 13,312 214 / 237 and 189 / 200, 14,336 245 / 237 and 216 / 199).  They
+// are kept from then: moving one regroups the sums of every n it passes.  Ring FP64, re-measured,
 // us per force evaluation, staged / symmetric: N = 4096 16.2 / 17.4, 4608 21.4 / 18.0,
 // 7168 36.0 / 25.2, 9216 48.2 / 33.2.
 // Ring FP64 below kRingExactN, where MD_LAUNCH_AUTO once took the staged form: the symmetric
@@ -167,7 +171,7 @@ struct md_ctx {
     void *ops = nullptr;      // pair operands: 2D [2][npad] FP32 copy; Ring [2][npad] cos,sin (FP32 or FP64)
     void *wops = nullptr;     // the Hessian-vector product's vector as operands: FP32 [d][npad] (mixed
                               // forms), FP64 [2][npad] with pads (2D FP64, symmetric form)
-    double *part = nullptr;   // pair partials [jsplit][d][npad]; symmetric form: [npad / kSymTile][d][npad]
+    double *part = nullptr;   // pair partials [jsplit][d][npad]; symmetric form: [npad / sym_tile_n][d][npad]
     double *red = nullptr;    // reduction partials [kRedSlots]
     double *scal = nullptr;   // small device scalars (HMF magnetization, ...)
     long long *macc = nullptr;  // HMF magnetization sums, fixed point: [3][kMSlots][kMLimbs]

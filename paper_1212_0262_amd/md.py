@@ -250,7 +250,7 @@ def md_get_launch(ctx: Context) -> int:
 
 
 def md_get_sym_tile(ctx: Context) -> int:
-    """Particles per tile of the symmetric form (1024 or 512) if md_step takes it, else 0."""
+    """Particles per tile of the symmetric form (256, 512 or 1024) if md_step takes it, else 0."""
     r = int(load().md_get_sym_tile(ctx.handle))
     ctx._check(min(r, 0), "md_get_sym_tile")
     return r
